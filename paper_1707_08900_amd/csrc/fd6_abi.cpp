@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <limits>
 #include <type_traits>
 #include <algorithm>
 #include <array>
@@ -286,6 +287,21 @@ int timed(fd6_box* b, std::vector<std::pair<hipEvent_t, hipEvent_t>>& log, F&& f
 constexpr double kAlpha[3] = {0.0, -5.0 / 9.0, -153.0 / 128.0};
 constexpr double kBeta[3] = {1.0 / 3.0, 15.0 / 16.0, 8.0 / 15.0};
 
+// Constants of substep s (1, 2, 3) for time step dt, in the precision of the
+// update.  b and c derive from dt as that precision holds it.  A dt so small
+// that 1 / dt overflows makes no increment that a state could hold: c stays
+// finite and multiplies in - prev = 0.
+template <typename T, typename TW>
+RKCoef<TW> make_rk(int s, double dt) {
+    const double h = (double)TW(dt), big = (double)std::numeric_limits<TW>::max();
+    RKCoef<TW> r{TW(kAlpha[s - 1]), TW(kBeta[s - 1]), TW(dt), TW(kBeta[s - 1] * h), TW(0)};
+    if (!std::is_same<T, TW>::value)
+        r.c = s == 1 ? TW(4.0) : s == 2 ? TW(80.0 / 51.0) : TW(0);
+    else if (s > 1)
+        r.c = TW(std::max(kAlpha[s - 1] / (kBeta[s - 2] * h), -big));
+    return r;
+}
+
 template <typename T>
 Coef<T> make_coef(const fd6_params& p) {
     const double h[3] = {p.dx, p.dy, p.dz};
@@ -316,6 +332,7 @@ Coef<T> make_coef(const fd6_params& p) {
     c.nu = T(p.nu);
     c.cs2 = T(p.cs * p.cs);
     c.nu3 = p.nu / 3.0;
+    c.n3 = T(c.nu3);
     double sg[3], sg4[3];
     for (int a = 0; a < 3; ++a) {
         sg[a] = p.nu / (180.0 * h[a] * h[a]);
@@ -376,8 +393,10 @@ int do_substep(fd6_box* b, int s, const RKCoef<TW>& rk, double* red_out = nullpt
     } else {
         T* dv = static_cast<T*>(b->div);
         rc = timed(b, b->ev_kernel, [&]() -> int {
-            HIPCHK(b, (launch_pass19a<T, TW>(g, in, out, w, dv, c, rk, s, b->tile, b->zchunk,
-                                             frc, b->stream)));
+            if (needs_ghosts)
+                HIPCHK(b, (launch_pass19a<T, TW>(g, in, out, w, dv, c, rk, s, frc, b->stream)));
+            else
+                HIPCHK(b, launch_div19<T>(g, in, dv, c, b->stream));
             return FD6_OK;
         });
         if (rc) return rc;
@@ -391,8 +410,12 @@ int do_substep(fd6_box* b, int s, const RKCoef<TW>& rk, double* red_out = nullpt
         }
         double* parts = (red_out && s == 3) ? b->partials : nullptr;
         rc = timed(b, b->ev_kernel, [&]() -> int {
-            HIPCHK(b, (launch_pass19b<T, TW>(g, dv, out, w, c, rk, s, b->tile, b->zchunk, parts,
-                                             kFusedPartials, &nparts, b->stream)));
+            if (needs_ghosts)
+                HIPCHK(b, (launch_pass19b<T, TW>(g, dv, out, w, c, rk, b->stream)));
+            else
+                HIPCHK(b, (launch_substep19<T, TW>(g, in, out, w, dv, c, rk, s, b->tile,
+                                                   b->zchunk, parts, kFusedPartials, &nparts,
+                                                   frc, b->stream)));
             return FD6_OK;
         });
         if (rc) return rc;
@@ -446,14 +469,15 @@ int fused12_substeps(fd6_box* b) {
         return FD6_EUNSUPPORTED;
     } else {
         const double dt = b->params.dt;
-        const RKCoef<TW> rk1{TW(kAlpha[0]), TW(kBeta[0]), TW(dt)};
-        const RKCoef<TW> rk2{TW(kAlpha[1]), TW(kBeta[1]), TW(dt)};
+        const RKCoef<TW> rk1 = make_rk<T, TW>(1, dt), rk2 = make_rk<T, TW>(2, dt);
         const Coef<T> c = make_coef<T>(b->params);
         int rc = timed(b, b->ev_kernel, [&]() -> int {
             HIPCHK(b, (launch_fused12<T, TW>(b->geom, fields_of<T>(b->state[b->cur]),
                                              fields_of<T>(b->state[b->cur ^ 1]),
                                              fields_of<TW>(b->w), c, rk1, rk2, b->zchunk,
                                              b->stream)));
+            HIPCHK(b, launch_unpack_w<T>(b->geom, fields_of<TW>(b->w),
+                                         fields_of<T>(b->state[b->cur]), b->stream));
             return FD6_OK;
         });
         if (rc) return rc;
@@ -475,8 +499,7 @@ int one_step(fd6_box* b, double* red_out) {
         s0 = 2;
     }
     for (int s = s0; s < 3; ++s) {
-        RKCoef<TW> rk{TW(kAlpha[s]), TW(kBeta[s]), TW(dt)};
-        int rc = do_substep<T, TW>(b, s + 1, rk, red_out);
+        int rc = do_substep<T, TW>(b, s + 1, make_rk<T, TW>(s + 1, dt), red_out);
         if (rc) return rc;
     }
     return FD6_OK;
@@ -545,12 +568,13 @@ int do_steps(fd6_box* b, int nsteps, double* red_out = nullptr) {
 
 template <typename T, typename TW>
 int do_rhs(fd6_box* b, double* const out[4]) {
-    // substep-1 arithmetic with dt = 1 leaves w = r; the result state is
+    // the z-sweeps have a form that leaves w = r and no new state; the direct
+    // kernels do the same through substep 1 with dt = 1, whose result state is
     // discarded by not swapping back
-    RKCoef<TW> rk{TW(0), TW(0), TW(1)};
+    RKCoef<TW> rk{TW(0), TW(0), TW(1), TW(0), TW(0)};
     int rc = force_sync<T>(b);
     if (rc) return rc;
-    rc = do_substep<T, TW>(b, 1, rk);
+    rc = do_substep<T, TW>(b, substep55_reads_ghosts(b->tile) ? 1 : 0, rk);
     if (rc) return rc;  // a failed substep returns before its in/out swap
     b->cur ^= 1;        // keep the original state current
     b->ghosts_ok[b->cur ^ 1] = false;
@@ -765,7 +789,7 @@ int upload_boxes(fd6_batch* b) {
         h[i].st[1] = fields_of<T>(b->st[1][i].data());
         h[i].w = fields_of<TW>(b->w[i].data());
         h[i].cf = make_coef<T>(b->params[i]);
-        h[i].dt = TW(b->params[i].dt);
+        for (int s = 1; s <= 3; ++s) h[i].rk[s - 1] = make_rk<T, TW>(s, b->params[i].dt);
     }
     HIPCHK(b, hipMemcpyAsync(b->boxes_dev, h.data(), sizeof(BatchBox<T, TW>) * b->n,
                              hipMemcpyHostToDevice, b->stream));
@@ -944,8 +968,7 @@ int batch_substeps(fd6_batch* b, hipStream_t st, int parity) {
     auto launch = b->aos ? launch_batch55_aos<T, TW> : launch_batch55<T, TW>;
     for (int s = 0; s < 3; ++s) {
         HIPCHK(b, launch(static_cast<const BatchBox<T, TW>*>(b->boxes_dev), b->items_dev,
-                         b->wg_first_dev, b->grid, parity, s + 1, b->tile, TW(kAlpha[s]),
-                         TW(kBeta[s]), st));
+                         b->wg_first_dev, b->grid, parity, s + 1, b->tile, st));
         parity ^= 1;
     }
     return FD6_OK;

@@ -45,10 +45,18 @@ struct Fields4 {
 };
 
 // RK3 substep constants (eq. 2N-RK_scheme): w <- alpha w + dt r,
-// out <- in + beta w.
+// out <- in + beta w.  Substep s leaves w = (out - in) / beta(s), and substep
+// s + 1 still finds that substep's input in the state set it writes to, so the
+// sweeps form w from the two states instead of storing it:
+//   out <- in + b (r + c (in - prev)),  b = beta(s) dt,
+//                                       c = alpha(s) / (beta(s - 1) dt).
+// alpha, beta and dt serve the kernels that keep w in memory: the direct ones,
+// and those with a register wider than the state, whose c is the multiple of
+// the state's rounding error that w takes up (0 for the direct ones' use).
 template <typename TW>
 struct RKCoef {
     TW alpha, beta, dt;
+    TW b, c;
 };
 
 // Finite-difference weights with the grid spacings folded in (Sec. 2.3).
@@ -70,10 +78,12 @@ struct Coef {
     // (nu folded in), mw[p][k-1]: mixed weights / 3 (nu folded in).
     T lw[3][3][4];
     T mw[3][3];
-    // 19-point method: nu-scaled plain second-derivative weights (nu lap u)
-    // and nu / 3 in FP64 for the pass-2 factor dt (nu / 3).
+    // 19-point method: nu-scaled plain second-derivative weights (nu lap u),
+    // and nu / 3 for the gradient of the divergence (in FP64 for the direct
+    // pass 2, whose factor is dt (nu / 3)).
     T lp[3][4];
     double nu3;
+    T n3;
     // Scale factors for stencils written with their integer weights
     // (second derivative 2, -27, 270, -490; mixed 270, -27, 2):
     //   sg[a]  = nu / (180 h_a^2),  sg4[a] = (4/3) sg[a]
@@ -124,6 +134,8 @@ hipError_t launch_zero_w(const Geom& g, Fields4<TW> w, hipStream_t s);
 
 // 55-point fused right-hand side + RK3 update for substep s (1, 2, 3) with
 // kernel shape `tile` and z-chunk length `zchunk` (0: chosen by the launcher).
+// s = 0 (z-sweep shapes): the right-hand side alone, written to w; the state
+// set `out` is not touched.  The z-sweep shapes leave w alone otherwise.
 // With partials != nullptr, substep 3 of a z-sweep shape whose grid has at
 // most part_cap workgroups also writes one FP64 diagnostics partial per
 // workgroup (kReduceSlots doubles each) and sets *nparts to their number;
@@ -145,12 +157,16 @@ hipError_t launch_substep55_aos(const Geom& g, Fields4<T> in, Fields4<T> out, Fi
                                 const ForceArgs<T>* frc, hipStream_t st);
 bool substep55_aos_tile_ok(int tile);
 // Substeps 1 and 2 of one step in a single launch (FP32 state and register,
-// either layout): in -> out after both substeps, w holding the substep-2
-// register.  rk1, rk2: the two substeps' coefficients.
+// either layout): in -> out after both substeps, w holding the substep-1
+// state.  rk1, rk2: the two substeps' coefficients.
 template <typename T, typename TW>
 hipError_t launch_fused12(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<TW> w,
                           const Coef<T>& c, const RKCoef<TW>& rk1, const RKCoef<TW>& rk2,
                           int zchunk, hipStream_t st);
+// Interior points of the substep-1 state that launch_fused12 left in w, into
+// the state set `dst` (the set substep 3 writes to and forms w from).
+template <typename T>
+hipError_t launch_unpack_w(const Geom& g, Fields4<T> w, Fields4<T> dst, hipStream_t st);
 // Whether a kernel shape reads the ghost zone of its input (the z-sweep
 // shapes resolve the periodic images in their loader instead).
 bool substep55_reads_ghosts(int tile);
@@ -163,7 +179,7 @@ struct BatchBox {
     Fields4<T> st[2];  // the two state sets; st[parity] is the substep input
     Fields4<TW> w;
     Coef<T> cf;
-    TW dt;
+    RKCoef<TW> rk[3];
 };
 struct BatchItem {
     int box, x0, y0, zb, ze;
@@ -175,36 +191,38 @@ constexpr int kMaxBatchGrid = 65536;
 int substep55_tile_dims(int tile, int* tx, int* ty);
 template <typename T, typename TW>
 hipError_t launch_batch55(const BatchBox<T, TW>* boxes, const BatchItem* items,
-                          const int* wg_first, int grid, int parity, int s, int tile, TW alpha,
-                          TW beta, hipStream_t st);
+                          const int* wg_first, int grid, int parity, int s, int tile,
+                          hipStream_t st);
 template <typename T, typename TW>
 int batch55_blocks_per_cu(int tile);
 // The same for ensembles whose boxes all use the array-of-structures layout.
 template <typename T, typename TW>
 hipError_t launch_batch55_aos(const BatchBox<T, TW>* boxes, const BatchItem* items,
                               const int* wg_first, int grid, int parity, int s, int tile,
-                              TW alpha, TW beta, hipStream_t st);
+                              hipStream_t st);
 template <typename T, typename TW>
 int batch55_blocks_per_cu_aos(int tile);
 
-// 19-point method: pass 1 (divergence, partial update) and pass 2 (the
-// (nu/3) grad div u term).  tile 0 runs the direct kernels, which read the
-// ghost zones of the state (pass 1) and of the divergence (pass 2); the
-// z-sweep shapes resolve periodic images themselves.
+// 19-point method.  The direct kernels (tile 0) are Algorithm 3 as printed:
+// pass 1 (divergence, partial update) and pass 2 (the (nu/3) grad div u term),
+// reading the ghost zones of the state and of the divergence.
 template <typename T, typename TW>
 hipError_t launch_pass19a(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, T* div,
-                          const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile, int zchunk,
+                          const Coef<T>& c, const RKCoef<TW>& rk, int s,
                           const ForceArgs<T>* frc, hipStream_t st);
 template <typename T, typename TW>
-hipError_t launch_pass19a_sweep(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<TW> w,
-                                T* div, const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile,
-                                int zchunk, const ForceArgs<T>* frc, hipStream_t st);
-// With partials != nullptr, substep 3 of a z-sweep shape also writes the FP64
-// diagnostics partials of the new state (as launch_substep55 does).
-template <typename T, typename TW>
 hipError_t launch_pass19b(const Geom& g, const T* div, Fields4<T> out, Fields4<TW> w,
-                          const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile, int zchunk,
-                          double* partials, int part_cap, int* nparts, hipStream_t st);
+                          const Coef<T>& c, const RKCoef<TW>& rk, hipStream_t st);
+// The z-sweep shapes split the work the other way: the divergence of the input
+// first, then the whole right-hand side and the update in one sweep over the
+// state and the divergence (s and partials as for launch_substep55).
+template <typename T>
+hipError_t launch_div19(const Geom& g, Fields4<T> in, T* div, const Coef<T>& c, hipStream_t st);
+template <typename T, typename TW>
+hipError_t launch_substep19(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<TW> w,
+                            const T* div, const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile,
+                            int zchunk, double* partials, int part_cap, int* nparts,
+                            const ForceArgs<T>* frc, hipStream_t st);
 
 // FP64 reductions: per-block partials then one fixed-order final block.
 constexpr int kReduceBlocks = 1024;

@@ -28,6 +28,32 @@ hipError_t launch_fused12(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<
                      : launch_fused12_vs<T, TW, 1>(g, in, out, w, c, rk1, rk2, zchunk, st);
 }
 
+namespace {
+template <typename T>
+__global__ __launch_bounds__(256) void unpack_w_kernel(Geom g, Fields4<T> w, Fields4<T> dst) {
+    const int rows = g.ny * g.nz;
+    for (int r = blockIdx.x; r < rows; r += gridDim.x) {
+        const int k = r / g.ny, j = r - k * g.ny;
+        const long long to = g.origin + (long long)k * g.plane + (long long)j * g.px;
+        const long long from = (long long)k * g.wplane + (long long)j * g.wpx;
+        for (int i = threadIdx.x; i < g.nx; i += blockDim.x)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                dst.f[q][(to + i) * g.vs] = w.f[q][(from + i) * g.vs];
+    }
+}
+}  // namespace
+
+template <typename T>
+hipError_t launch_unpack_w(const Geom& g, Fields4<T> w, Fields4<T> dst, hipStream_t st) {
+    const long long rows = (long long)g.ny * g.nz;
+    const unsigned grid = (unsigned)(rows < 8192 ? rows : 8192);
+    hipLaunchKernelGGL(unpack_w_kernel<T>, dim3(grid), dim3(256), 0, st, g, w, dst);
+    return hipGetLastError();
+}
+
+template hipError_t launch_unpack_w<float>(const Geom&, Fields4<float>, Fields4<float>,
+                                           hipStream_t);
 template hipError_t launch_fused12<float, float>(const Geom&, Fields4<float>, Fields4<float>,
                                                  Fields4<float>, const Coef<float>&,
                                                  const RKCoef<float>&, const RKCoef<float>&, int,

@@ -1,15 +1,14 @@
 // 19-point two-pass substep (Sec. 4.2, Algorithm 3, Appendix A).
 //
-// Pass 1 computes the divergence field d = D1x ux + D1y uy + D1z uz, the
-// right-hand side without the (nu/3) grad(div u) term, and the partial RK3
-// register and output.  Pass 2 adds dt (nu/3) D1_i d to w_i and
-// beta dt (nu/3) D1_i d to the output velocity.  Both passes read only
-// axis-aligned taps (19 points).
+// The direct kernels (one thread per point, taps through the caches from the
+// ghost zones) are Algorithm 3 as printed.  Pass 1 computes the divergence
+// field d = D1x ux + D1y uy + D1z uz, the right-hand side without the
+// (nu/3) grad(div u) term, and the partial RK3 register and output.  Pass 2
+// adds dt (nu/3) D1_i d to w_i and beta dt (nu/3) D1_i d to the output velocity.
+// Both passes read only axis-aligned taps (19 points).
 //
-// This file holds the direct kernels of both passes (one thread per point,
-// taps through the caches from the ghost zones), the z-sweep form of pass 2,
-// and the dispatch of both passes; the z-sweep form of pass 1 shares the
-// 55-point sweep.
+// The z-sweep shapes compute d first (substep19_div, here) and then the whole
+// update in one sweep, which shares the 55-point sweep's code.
 #include "sweep_common.hpp"
 
 namespace fd6 {
@@ -115,153 +114,147 @@ __global__ __launch_bounds__(256) void pass19b_kernel(Geom g, const T* __restric
     }
 }
 
-// z-sweep form of pass 2: a TX x TY column tile sweeps a z chunk of d.
-// Each step puts one plane of d (tile + 3-cell halo, periodic images
-// resolved by the loader) into LDS, forms its x and y first derivatives for
-// the thread's column (kept 3 planes), and pushes the centre value into a
-// register queue of 7 planes for the z derivative; output plane p - 3 is
-// completed from them.  Substep 3 neither reads nor writes w.
-template <typename T, int NH>
-struct Pass2Regs {
-    T q[8];      // column of d over planes (ring)
-    T dx[4], dy[4];  // x / y first derivatives of d, ring of 4 planes
-    T pf;        // prefetched interior value of the next plane
-    T ph[NH];    // prefetched halo values of the next plane
-    double red[4];  // RED: FP64 diagnostics of the thread's column
-    int bad;        // RED: points of the column with a non-finite value
+// The divergence of the velocity, d = D1x ux + D1y uy + D1z uz.  A workgroup
+// sweeps a z chunk of a kDivTX x kDivTY column tile.  Only ux needs its x
+// neighbours and only uy its y neighbours: one LDS plane each (rows of ux with
+// 3 cells more at both ends; uy with 3 rows more above and below), both of the
+// output plane o, while uz runs 3 planes ahead through a register queue.  A
+// thread loads one point of each field and at most one halo cell, one plane
+// ahead.  Bound by HBM: 12 bytes read and 4 written per point in FP32.
+constexpr int kDivTX = 64, kDivTY = 8;
+
+template <typename T>
+struct DivRegs {
+    T q[8];        // uz of the thread's column, ring over planes
+    T px, py, pz;  // prefetched ux, uy of the next output plane, uz 3 planes beyond
+    T ph;          // prefetched halo cell (ux or uy)
 };
 
-// As in the 55-point sweep, no memory operation of a step sits behind a
-// branch: a step with nothing to load or store uses descriptors of zero range.
-template <typename T, int TX, int TY, int NH>
-__device__ __forceinline__ void pass2_prefetch(Pass2Regs<T, NH>& R,
-                                               const SweepCtx<T, TX, TY>& X, const T* dv,
-                                               long long corner, unsigned bytes) {
-    const __amdgpu_buffer_rsrc_t rs = plane_rsrc(dv + corner, bytes);
-    R.pf = bload((T*)nullptr, rs, X.goff_int);
-#pragma unroll
-    for (int h = 0; h < NH; ++h) R.ph[h] = bload((T*)nullptr, rs, X.goff_h[h]);
+struct DivAddr {
+    unsigned in, halo, out;    // byte offsets from the ghost corner of a plane
+    int lx, ly, lh;            // LDS elements of this thread's ux, uy and halo cell
+    bool hx;                   // the halo cell belongs to ux
+    unsigned bytes;            // of a plane
+};
+
+template <typename T>
+__device__ __forceinline__ void div_load(DivRegs<T>& R, const DivAddr& A, const Geom& g,
+                                         const Fields4<T>& in, int o, bool xy, bool z) {
+    const long long oc = plane_corner(g, o);
+    const unsigned b = xy ? A.bytes : 0u;
+    const __amdgpu_buffer_rsrc_t rx = plane_rsrc(in.f[1] + oc, b);
+    const __amdgpu_buffer_rsrc_t ry = plane_rsrc(in.f[2] + oc, b);
+    R.px = bload((T*)nullptr, rx, A.in);
+    R.py = bload((T*)nullptr, ry, A.in);
+    // one of the two loads is out of range for every thread
+    const T hx = bload((T*)nullptr, rx, A.hx ? A.halo : kDropOffset);
+    const T hy = bload((T*)nullptr, ry, A.hx ? kDropOffset : A.halo);
+    R.ph = A.hx ? hx : hy;
+    R.pz = bload((T*)nullptr,
+                 plane_rsrc(in.f[3] + plane_corner(g, o + kR), z ? A.bytes : 0u), A.in);
 }
 
-template <int PH, int S, bool NT, bool RED, typename T, typename TW, int TX, int TY, int NH>
-__device__ __forceinline__ void pass2_step(int t0, int nplanes, int zb, Pass2Regs<T, NH>& R,
-                                           const SweepCtx<T, TX, TY>& X, T* lds, const Geom& g,
-                                           const T* dv, const Fields4<T>& out,
-                                           const Fields4<TW>& w, const Coef<T>& cf,
-                                           const RKCoef<TW>& rk, TW cgd) {
-    using Sh = SweepShape<T, TX, TY>;
-    constexpr int W = Sh::W;
+template <int PH, typename T>
+__device__ __forceinline__ void div_step(int t0, int nsteps, int zb, DivRegs<T>& R,
+                                         const DivAddr& A, T* lds, const Geom& g,
+                                         const Fields4<T>& in, T* dv, const Coef<T>& cf) {
+    constexpr int WX = kDivTX + 2 * kR;
+    constexpr int NX = kDivTY * WX, NB = NX + (kDivTY + 2 * kR) * kDivTX + 1;
     const int t = t0 + PH;
-    if (t >= nplanes) return;
-    const int p = zb - kR + t;  // plane loaded in this step
-    const int o = p - kR;       // output plane finished in this step
-    const bool outstep = t >= 2 * kR;
-    const long long ocorner = g.origin + (long long)o * g.plane - kR * g.px - kR;
-    const unsigned ob = outstep ? X.plane_bytes : 0u;
-    const unsigned wb = outstep ? X.wplane_bytes : 0u;
-    constexpr int CP = NT ? kNonTemporal : 0;
-    T ov[3] = {T(0), T(0), T(0)};
-    TW wv[3] = {TW(0), TW(0), TW(0)};
-    // RED (substep 3): lnrho of the output point, final since pass 1
-    T lr = T(0);
-    if constexpr (RED) lr = bload((T*)nullptr, plane_rsrc(out.f[0] + ocorner, ob), X.lane_o);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        ov[i] = bload<CP>((T*)nullptr, plane_rsrc(out.f[1 + i] + ocorner, ob), X.lane_o);
-        if constexpr (S != 3)
-            wv[i] = bload<CP>((TW*)nullptr,
-                              plane_rsrc(w.f[1 + i] + (long long)o * g.wplane, wb), X.lane_w);
-    }
-    T* buf = lds + (PH & 1) * Sh::FS;
-    const int ci = (threadIdx.x / TX + kR) * W + (threadIdx.x % TX + kR);
-    buf[ci] = R.pf;
-#pragma unroll
-    for (int h = 0; h < NH; ++h) buf[X.loff_h[h]] = R.ph[h];
-    pass2_prefetch<T, TX, TY, NH>(R, X, dv, plane_corner(g, p + 1),
-                                  t + 1 < nplanes ? X.plane_bytes : 0u);
+    if (t >= nsteps) return;
+    const int o = zb - 2 * kR + t;  // output plane of this step, from t = 6
+    T* buf = lds + (PH & 1) * NB;
+    buf[A.lx] = R.px;
+    buf[A.ly] = R.py;
+    buf[A.lh] = R.ph;
+    R.q[sl8(PH)] = R.pz;
+    div_load(R, A, g, in, o + 1, t + 1 >= 2 * kR && t + 1 < nsteps, t + 1 < nsteps);
     __syncthreads();
-
-    const T* B = buf + ci;
-    R.q[sl8(PH)] = B[0];
-    R.dx[PH & 3] = cf.d1[0][0] * (B[1] - B[-1]) + cf.d1[0][1] * (B[2] - B[-2]) +
-                   cf.d1[0][2] * (B[3] - B[-3]);
-    R.dy[PH & 3] = cf.d1[1][0] * (B[W] - B[-W]) + cf.d1[1][1] * (B[2 * W] - B[-2 * W]) +
-                   cf.d1[1][2] * (B[3 * W] - B[-3 * W]);
-    {
-        const T dz = cf.d1[2][0] * (R.q[sl8(PH - 2)] - R.q[sl8(PH - 4)]) +
-                     cf.d1[2][1] * (R.q[sl8(PH - 1)] - R.q[sl8(PH - 5)]) +
-                     cf.d1[2][2] * (R.q[sl8(PH)] - R.q[sl8(PH - 6)]);
-        constexpr int DO = (PH + 1) & 3;  // slot of plane p - 3
-        const T gd[3] = {R.dx[DO], R.dy[DO], dz};
-        T un[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const TW tq = cgd * TW(gd[i]);
-            if constexpr (S != 3)
-                bstore<CP>(wv[i] + tq, plane_rsrc(w.f[1 + i] + (long long)o * g.wplane, wb),
-                           X.lane_w);
-            un[i] = T(TW(ov[i]) + rk.beta * tq);
-            bstore<CP>(un[i], plane_rsrc(out.f[1 + i] + ocorner, ob), X.lane_o);
-        }
-        if constexpr (RED) {
-            if (outstep && X.lane_o != kDropOffset) red_point(R.red, R.bad, lr, un[0], un[1], un[2]);
-        }
-    }
+    const T* X = buf + A.lx;
+    const T* Y = buf + A.ly;
+    const T dx = cf.d1[0][0] * (X[1] - X[-1]) + cf.d1[0][1] * (X[2] - X[-2]) +
+                 cf.d1[0][2] * (X[3] - X[-3]);
+    const T dy = cf.d1[1][0] * (Y[kDivTX] - Y[-kDivTX]) +
+                 cf.d1[1][1] * (Y[2 * kDivTX] - Y[-2 * kDivTX]) +
+                 cf.d1[1][2] * (Y[3 * kDivTX] - Y[-3 * kDivTX]);
+    const T dz = cf.d1[2][0] * (R.q[sl8(PH - 2)] - R.q[sl8(PH - 4)]) +
+                 cf.d1[2][1] * (R.q[sl8(PH - 1)] - R.q[sl8(PH - 5)]) +
+                 cf.d1[2][2] * (R.q[sl8(PH)] - R.q[sl8(PH - 6)]);
+    const long long oc = g.origin + (long long)o * g.plane - kR * g.px - kR;
+    bstore(dx + dy + dz, plane_rsrc(dv + oc, t >= 2 * kR ? A.bytes : 0u), A.out);
 }
 
-// RED (substep 3 only): also the FP64 diagnostics of the new state, one
-// partial per workgroup at part[blockIdx.x * kReduceSlots ...].
-template <typename T, typename TW, int TX, int TY, int S, bool NT, bool RED = false>
-__global__ __launch_bounds__(TX* TY) void substep19_pass2(Geom g, const T* __restrict__ dv,
-                                                          Fields4<T> out, Fields4<TW> w,
-                                                          Coef<T> cf, RKCoef<TW> rk, TW cgd,
-                                                          SweepGrid m, double* part) {
-    static_assert(!RED || S == 3, "diagnostics of the final substep only");
-    using Sh = SweepShape<T, TX, TY>;
-    constexpr int NH = Sh::NH;
-    __shared__ T lds[2 * Sh::FS];
+template <typename T>
+__global__ __launch_bounds__(kDivTX* kDivTY) void substep19_div(Geom g, Fields4<T> in, T* dv,
+                                                                Coef<T> cf, SweepGrid m) {
+    constexpr int TX = kDivTX, TY = kDivTY, WX = TX + 2 * kR;
+    constexpr int NX = TY * WX, NB = NX + (TY + 2 * kR) * TX + 1;
+    static_assert(2 * kR * (TX + TY) <= TX * TY, "one halo cell per thread");
+    __shared__ T lds[2 * NB];
     const TileXY tl = sweep_tile_of(g, TX, TY, m);
-    if (tl.zb >= tl.ze) {  // not produced by sweep_grid; keeps every partial defined
-        if constexpr (RED) {
-            if (threadIdx.x == 0)
-                for (int i = 0; i < 5; ++i) part[(size_t)blockIdx.x * kReduceSlots + i] = 0.0;
-        }
-        return;
+    if (tl.zb >= tl.ze) return;
+    const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
+    DivAddr A;
+    A.bytes = (unsigned)(g.plane * (long long)sizeof(T));
+    // byte offset of the periodic image of cell (x, y), x < nx + 3, y < ny + 3
+    auto image = [&](int x, int y) -> unsigned {
+        if (x >= g.nx + kR || y >= g.ny + kR) return kDropOffset;
+        const int i = x < 0 ? x + g.nx : (x >= g.nx ? x - g.nx : x);
+        const int j = y < 0 ? y + g.ny : (y >= g.ny ? y - g.ny : y);
+        return (unsigned)(((j + kR) * g.px + (i + kR)) * (int)sizeof(T));
+    };
+    A.in = image(tl.tx + tx, tl.ty + ty);
+    A.out = tl.tx + tx < g.nx && tl.ty + ty < g.ny ? A.in : kDropOffset;
+    A.lx = ty * WX + tx + kR;
+    A.ly = NX + (ty + kR) * TX + tx;
+    // threads 0 .. 6 TX - 1: the rows of uy above and below the tile; the next
+    // 6 TY: the cells of ux left and right of it; the rest fill the spare cell
+    const int e = threadIdx.x - 2 * kR * TX;
+    A.hx = e >= 0;
+    if (e < 0) {
+        const int r = threadIdx.x / TX, row = r < kR ? r : r + TY;
+        A.halo = image(tl.tx + tx, tl.ty - kR + row);
+        A.lh = NX + row * TX + tx;
+    } else if (e < 2 * kR * TY) {
+        const int r = e / (2 * kR), c = e - r * 2 * kR, col = c < kR ? c : c + TX;
+        A.halo = image(tl.tx - kR + col, tl.ty + r);
+        A.lh = r * WX + col;
+    } else {
+        A.halo = kDropOffset;
+        A.lh = NB - 1;
     }
-    SweepCtx<T, TX, TY> X;
-    sweep_ctx_init<T, TW, TX, TY, false>(X, g, tl.tx, tl.ty);
-    Pass2Regs<T, NH> R;
+    DivRegs<T> R;
 #pragma unroll
     for (int s = 0; s < 8; ++s) R.q[s] = T(0);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) R.dx[s] = R.dy[s] = T(0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) R.red[i] = 0.0;
-    R.bad = 0;
-    const int zb = tl.zb;
-    const int nplanes = (tl.ze - zb) + 2 * kR;
-    pass2_prefetch<T, TX, TY, NH>(R, X, dv, plane_corner(g, zb - kR), X.plane_bytes);
-    for (int t0 = 0; t0 < nplanes; t0 += 8) {
-        pass2_step<0, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
-        pass2_step<1, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
-        pass2_step<2, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
-        pass2_step<3, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
-        pass2_step<4, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
-        pass2_step<5, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
-        pass2_step<6, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
-        pass2_step<7, S, NT, RED>(t0, nplanes, zb, R, X, lds, g, dv, out, w, cf, rk, cgd);
+    const int zb = tl.zb, nsteps = (tl.ze - tl.zb) + 2 * kR;
+    div_load(R, A, g, in, zb - 2 * kR, false, true);
+    for (int t0 = 0; t0 < nsteps; t0 += 8) {
+        div_step<0>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
+        div_step<1>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
+        div_step<2>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
+        div_step<3>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
+        div_step<4>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
+        div_step<5>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
+        div_step<6>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
+        div_step<7>(t0, nsteps, zb, R, A, lds, g, in, dv, cf);
     }
-    if constexpr (RED) red_store_n<Sh::NW>(R.red, R.bad, part);
 }
 
 }  // namespace
 
+template <typename T>
+hipError_t launch_div19(const Geom& g, Fields4<T> in, T* div, const Coef<T>& c, hipStream_t st) {
+    constexpr int blk = kDivTX * kDivTY;
+    const SweepGrid sg =
+        sweep_grid(g, kDivTX, kDivTY, 0, resident_blocks<substep19_div<T>>(blk));
+    hipLaunchKernelGGL(substep19_div<T>, dim3(sg.blocks), dim3(blk), 0, st, g, in, div, c, sg);
+    return hipGetLastError();
+}
+
 template <typename T, typename TW>
 hipError_t launch_pass19a(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, T* div,
-                          const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile, int zchunk,
+                          const Coef<T>& c, const RKCoef<TW>& rk, int s,
                           const ForceArgs<T>* frc, hipStream_t st) {
-    if (tile != 0)
-        return launch_pass19a_sweep<T, TW>(g, in, out, w, div, c, rk, s, tile, zchunk, frc, st);
     const dim3 grid((unsigned)((g.nx + 63) / 64), (unsigned)((g.ny + 3) / 4), (unsigned)g.nz);
     const ForceArgs<T> fa = frc ? *frc : ForceArgs<T>{nullptr, nullptr};
     auto go = [&](auto force) {
@@ -280,75 +273,27 @@ hipError_t launch_pass19a(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<
     return hipGetLastError();
 }
 
-// Pass 2 takes the column tile of the chosen shape (its register budget and
-// loader options do not apply to this one-field sweep).
 template <typename T, typename TW>
 hipError_t launch_pass19b(const Geom& g, const T* div, Fields4<T> out, Fields4<TW> w,
-                          const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile, int zchunk,
-                          double* partials, int part_cap, int* nparts, hipStream_t st) {
-    if (nparts) *nparts = 0;
-    const TW cgd = TW((double)rk.dt * c.nu3);
-    return with_tile(tile, hipErrorInvalidValue, [&](auto I) -> hipError_t {
-        constexpr TileCfg k = kTiles[decltype(I)::value];
-        if constexpr (k.tx == 0) {
-            const dim3 grid((unsigned)((g.nx + 63) / 64), (unsigned)((g.ny + 3) / 4),
-                            (unsigned)g.nz);
-            hipLaunchKernelGGL((pass19b_kernel<T, TW>), grid, dim3(256), 0, st, g, div, out, w, c,
-                               rk, cgd);
-        } else {
-            const int res =
-                resident_blocks<substep19_pass2<T, TW, k.tx, k.ty, 2, k.nt>>(k.tx * k.ty);
-            const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res);
-            const dim3 grid(sg.blocks), block(k.tx * k.ty);
-            // Fuse the diagnostics unless that leaves fewer than 2 waves per
-            // SIMD: this light one-field sweep loses little occupancy that
-            // matters, while the standalone pass re-reads the whole state
-            // (measured at 512^3: 4.7% of the FP32 19-point step).
-            static const bool fuse_ok = [] {
-                int a = 0, b = 0;
-                const int blk = k.tx * k.ty;
-                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                        &a, substep19_pass2<T, TW, k.tx, k.ty, 3, k.nt, true>, blk, 0) !=
-                        hipSuccess ||
-                    hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                        &b, substep19_pass2<T, TW, k.tx, k.ty, 3, k.nt>, blk, 0) != hipSuccess)
-                    return false;
-                return a > 0 && (a >= b || a * (blk / 64) >= 8);
-            }();
-            switch (s) {
-            case 1:
-                hipLaunchKernelGGL((substep19_pass2<T, TW, k.tx, k.ty, 1, k.nt>), grid, block, 0,
-                                   st, g, div, out, w, c, rk, cgd, sg, nullptr);
-                break;
-            case 2:
-                hipLaunchKernelGGL((substep19_pass2<T, TW, k.tx, k.ty, 2, k.nt>), grid, block, 0,
-                                   st, g, div, out, w, c, rk, cgd, sg, nullptr);
-                break;
-            default:
-                if (partials && nparts && fuse_ok && sg.blocks <= part_cap) {
-                    hipLaunchKernelGGL((substep19_pass2<T, TW, k.tx, k.ty, 3, k.nt, true>), grid,
-                                       block, 0, st, g, div, out, w, c, rk, cgd, sg, partials);
-                    *nparts = sg.blocks;
-                } else {
-                    hipLaunchKernelGGL((substep19_pass2<T, TW, k.tx, k.ty, 3, k.nt>), grid, block,
-                                       0, st, g, div, out, w, c, rk, cgd, sg, nullptr);
-                }
-                break;
-            }
-        }
-        return hipGetLastError();
-    });
+                          const Coef<T>& c, const RKCoef<TW>& rk, hipStream_t st) {
+    const dim3 grid((unsigned)((g.nx + 63) / 64), (unsigned)((g.ny + 3) / 4), (unsigned)g.nz);
+    hipLaunchKernelGGL((pass19b_kernel<T, TW>), grid, dim3(256), 0, st, g, div, out, w, c, rk,
+                       TW((double)rk.dt * c.nu3));
+    return hipGetLastError();
 }
 
 #define FD6_INST19(T, TW)                                                                       \
     template hipError_t launch_pass19a<T, TW>(const Geom&, Fields4<T>, Fields4<T>, Fields4<TW>, \
-                                              T*, const Coef<T>&, const RKCoef<TW>&, int, int, \
-                                              int, const ForceArgs<T>*, hipStream_t);          \
+                                              T*, const Coef<T>&, const RKCoef<TW>&, int,      \
+                                              const ForceArgs<T>*, hipStream_t);               \
     template hipError_t launch_pass19b<T, TW>(const Geom&, const T*, Fields4<T>, Fields4<TW>,   \
-                                              const Coef<T>&, const RKCoef<TW>&, int, int,     \
-                                              int, double*, int, int*, hipStream_t);
+                                              const Coef<T>&, const RKCoef<TW>&, hipStream_t);
 FD6_INST19(double, double)
 FD6_INST19(float, float)
 FD6_INST19(float, double)
+template hipError_t launch_div19<double>(const Geom&, Fields4<double>, double*,
+                                         const Coef<double>&, hipStream_t);
+template hipError_t launch_div19<float>(const Geom&, Fields4<float>, float*, const Coef<float>&,
+                                        hipStream_t);
 
 }  // namespace fd6

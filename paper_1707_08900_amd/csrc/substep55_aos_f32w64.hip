@@ -11,8 +11,7 @@ template hipError_t launch_substep55_aos<float, double>(const Geom&, Fields4<flo
                                                    int, int*, const ForceArgs<float>*,
                                                    hipStream_t);
 template hipError_t launch_batch55_aos<float, double>(const BatchBox<float, double>*,
-                                                 const BatchItem*, const int*, int, int, int, int,
-                                                 double, double, hipStream_t);
+                                                 const BatchItem*, const int*, int, int, int, int, hipStream_t);
 template int batch55_blocks_per_cu_aos<float, double>(int);
 
 }  // namespace fd6

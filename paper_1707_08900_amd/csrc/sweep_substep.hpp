@@ -29,7 +29,7 @@
 //    layout (one 16-byte access per cell and field set); NT streams the new
 //    state and the RK3 register past the caches; FRC adds the external
 //    force; RED accumulates the FP64 diagnostics; P19 turns the sweep into
-//    pass 1 of the 19-point method.
+//    that of the 19-point method, over the state and its divergence.
 #pragma once
 
 #include "sweep_common.hpp"
@@ -63,20 +63,49 @@ __device__ __forceinline__ void assemble_rhs(const T u[3], const T g[3], const T
     }
 }
 
-// 2N-RK3 update of one value (eq. 2N-RK_scheme, Algorithm 2):
-//   w <- alpha w + dt r  (alpha(1) = 0: substep 1 does not read w)
-//   out <- in + beta w   (substep 3 need not store w: the next step's
-//                         substep 1 ignores it)
-template <int S, typename T, typename TW>
-__device__ __forceinline__ T rk_update(T in, T r, TW& w, const RKCoef<TW>& rk) {
-    TW wn;
-    if constexpr (S == 1)
-        wn = rk.dt * TW(r);
-    else
-        wn = rk.alpha * w + rk.dt * TW(r);
-    w = wn;
-    return T(TW(in) + rk.beta * wn);
+// 2N-RK3 update of one value (eq. 2N-RK_scheme, Algorithm 2) with the register
+// formed from the states: w(s - 1) = (in - prev) / beta(s - 1), where prev is
+// the previous substep's input at this point.  Substeps 2 and 3 read prev from
+// the place they then write, so no register is stored or read: 128 instead of
+// 160 bytes per point and step in FP32 (512^3 array of structures, 10 steps
+// with diagnostics and a snapshot: 49.0 -> 45.5 ms; FP64, 4 steps: 50.7 -> 42.8
+// ms).  It also follows the rounding of the
+// stored states: of the errors e1, e2, e3 made when the three substeps round
+// their new states, e1 / 2 + 0.32 e2 + e3 remains after the step, against
+// e1 + e2 + e3 with the register kept apart.
+template <int S, typename T>
+__device__ __forceinline__ T rk_update(T in, T r, T prev, const RKCoef<T>& rk) {
+    T q = r;
+    if constexpr (S != 1) q = rk.c * (in - prev) + q;
+    return rk.b * q + in;
 }
+
+// The same with a register wider than the state (FP64 beside an FP32 state),
+// which stays in memory: w <- alpha w + dt r, out <- in + beta w.  The rounding
+// error e of the stored state is known here, and w takes up the multiple of it
+// (rk.c) whose later contributions to the state cancel most of it.  With z the
+// time step times the linear operator's eigenvalue and k e taken up, what is
+// left of e at the end of the step is
+//   substep 1:  (1 - k / 6) + (5/6) (1 - k / 3) z + z^2 / 2
+//   substep 2:  (1 - 51/80 k) + (8/15) z
+// times e.  Rounding errors are white in space, so z = i y with y^2 = 0.2 (a
+// velocity) to 0.6 (lnrho) in the mean at Courant number 0.4: k = 4 leaves 0.07
+// and 0.05 of e's variance in substep 1 (forming w from the states is k = 3:
+// 0.16 and 0.05), k = 80/51 the least in substep 2.
+template <int S, typename T, typename TW>
+__device__ __forceinline__ T rk_update_reg(T in, T r, TW& w, const RKCoef<TW>& rk) {
+    TW wn = rk.dt * TW(r);
+    if constexpr (S != 1) wn = rk.alpha * w + rk.dt * TW(r);
+    const TW v = rk.beta * wn + TW(in);
+    const T out = T(v);
+    if constexpr (S != 3) w = rk.c * (TW(out) - v) + wn;
+    return out;
+}
+
+// Whether the RK3 register is kept in memory (wider than the state) or formed
+// from the states.
+template <typename T, typename TW>
+constexpr bool kRegInMemory = !std::is_same_v<T, TW>;
 
 // ---------------------------------------------------------------------------
 // Direct kernel: one thread per point, every tap read from global memory.
@@ -149,9 +178,10 @@ __global__ __launch_bounds__(256) void substep55_direct(Geom g, Fields4<T> in, F
     const long long cw = (long long)k * g.wplane + (long long)j * g.wpx + i;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        TW wv = (S == 1) ? TW(0) : w.f[q][cw];
-        out.f[q][c] = rk_update<S>(in.f[q][c], r[q], wv, rk);
-        if (S != 3) w.f[q][cw] = wv;
+        TW wv = rk.dt * TW(r[q]);
+        if constexpr (S != 1) wv = rk.alpha * w.f[q][cw] + rk.dt * TW(r[q]);
+        out.f[q][c] = T(TW(in.f[q][c]) + rk.beta * wv);
+        if constexpr (S != 3) w.f[q][cw] = wv;
     }
 }
 
@@ -161,12 +191,16 @@ __global__ __launch_bounds__(256) void substep55_direct(Geom g, Fields4<T> in, F
 
 template <typename T, typename TW, int NH>
 struct SweepRegs {
+    using Reg = std::conditional_t<kRegInMemory<T, TW>, TW, T>;
     T q[4][8];       // raw column values of the 4 fields, ring over planes
     T L[3][8];       // pending linear viscous term of the 3 momentum components
     T dd[4][8];      // x/y first derivatives of the 4 fields, ring of 4 planes
     T pf[4][4];      // prefetched interior values of the next plane(s)
     T ph[4][NH][4];  // prefetched halo values of the next plane(s)
-    TW wq[2][4];     // RK3 register of the output point (PD = 2: loaded a step early)
+    // 19-point method: the same of the divergence field
+    T qd[8], pfd[4], phd[4][NH];
+    Reg wq[2][4];    // previous substep's input, or the RK3 register in memory, at the
+                     // output point (PD >= 2: loaded a step early)
     double red[4];   // fused diagnostics of the thread's column (RED): sum rho,
                      // sum rho u^2, sum lnrho, max u^2
     int bad;         // RED: points of the column with a non-finite value
@@ -182,11 +216,17 @@ struct SweepRegs {
 
 // Loads plane `corner` of the four fields (this thread's cells) into
 // register set RS; bytes = 0 loads nothing.
-template <int RS, int VS, typename T, typename TW, int TX, int TY, int NH>
+template <int RS, int VS, bool P19, typename T, typename TW, int TX, int TY, int NH>
 __device__ __forceinline__ void sweep_prefetch(SweepRegs<T, TW, NH>& R,
                                                const SweepCtx<T, TX, TY>& X,
-                                               const Fields4<T>& in, long long corner,
-                                               unsigned bytes) {
+                                               const Fields4<T>& in, const T* dv,
+                                               long long corner, unsigned bytes) {
+    if constexpr (P19) {
+        const __amdgpu_buffer_rsrc_t rs = plane_rsrc(dv + corner, bytes);
+        R.pfd[RS] = bload((T*)nullptr, rs, X.goff_int);
+#pragma unroll
+        for (int h = 0; h < NH; ++h) R.phd[RS][h] = bload((T*)nullptr, rs, X.goff_h[h]);
+    }
     if constexpr (VS == 4) {
         const __amdgpu_buffer_rsrc_t rs = plane_rsrc(in.f[0] + 4 * corner, bytes);
         bload_point(R.pf[RS], rs, X.goff_int);
@@ -203,35 +243,48 @@ __device__ __forceinline__ void sweep_prefetch(SweepRegs<T, TW, NH>& R,
     }
 }
 
-template <int RS, bool NT, int VS, typename T, typename TW, int NH>
-__device__ __forceinline__ void load_w(SweepRegs<T, TW, NH>& R, const Fields4<TW>& w,
-                                       const Geom& g, int o, unsigned wplane_bytes,
-                                       unsigned lane_w) {
+// What the update of output plane o needs beside the plane's input: the
+// previous substep's input, which the state set being written still holds
+// there, or the RK3 register.  on: the plane is an output plane of the chunk.
+template <int RS, bool NT, int VS, typename T, typename TW, typename Ctx, int NH>
+__device__ __forceinline__ void load_prev(SweepRegs<T, TW, NH>& R, const Ctx& X,
+                                          const Fields4<T>& out, const Fields4<TW>& w,
+                                          const Geom& g, int o, bool on) {
     constexpr int CP = NT ? kNonTemporal : 0;
+    constexpr bool REG = kRegInMemory<T, TW>;
+    using P = typename SweepRegs<T, TW, NH>::Reg;
+    const long long at = REG ? (long long)o * g.wplane
+                             : g.origin + (long long)o * g.plane - kR * g.px - kR;
+    const unsigned bytes = on ? (REG ? X.wplane_bytes : X.plane_bytes) : 0u;
+    const unsigned lane = REG ? X.lane_w : X.lane_o;
+    auto base = [&](int f) -> const P* {
+        if constexpr (REG)
+            return w.f[f];
+        else
+            return out.f[f];
+    };
     if constexpr (VS == 4) {
-        bload_point<CP>(R.wq[RS], plane_rsrc(w.f[0] + 4 * (long long)o * g.wplane, wplane_bytes),
-                        lane_w);
+        bload_point<CP>(R.wq[RS], plane_rsrc(base(0) + 4 * at, bytes), lane);
     } else {
 #pragma unroll
         for (int f = 0; f < 4; ++f)
-            R.wq[RS][f] = bload<CP>((TW*)nullptr,
-                                    plane_rsrc(w.f[f] + (long long)o * g.wplane, wplane_bytes),
-                                    lane_w);
+            R.wq[RS][f] = bload<CP>((P*)nullptr, plane_rsrc(base(f) + at, bytes), lane);
     }
 }
 
-// LD: copy plane `corner` of the four fields into one LDS buffer.  Chunk j
+// LD: copy plane `corner` of the four fields (19-point: and of the divergence)
+// into one LDS buffer.  Chunk j
 // (64 dwords) is issued by wave j % NW; its lanes fetch the dwords whose byte
 // offsets were precomputed in doff (periodic images included).
-template <typename T, int TX, int TY>
+template <bool P19, typename T, int TX, int TY>
 __device__ __forceinline__ void sweep_dma(const SweepCtx<T, TX, TY, true>& X,
-                                          const Fields4<T>& in, long long corner, lds_t<T> buf,
-                                          unsigned bytes) {
+                                          const Fields4<T>& in, const T* dv, long long corner,
+                                          lds_t<T> buf, unsigned bytes) {
     using Sh = SweepShape<T, TX, TY, true>;
     const int wv = threadIdx.x / 64;
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        const __amdgpu_buffer_rsrc_t rs = plane_rsrc(in.f[f] + corner, bytes);
+    for (int f = 0; f < (P19 ? 5 : 4); ++f) {
+        const __amdgpu_buffer_rsrc_t rs = plane_rsrc((f < 4 ? in.f[f & 3] : dv) + corner, bytes);
 #pragma unroll
         for (int js = 0; js < Sh::ND; ++js) {
             const int j = wv + js * Sh::NW;
@@ -247,16 +300,17 @@ __device__ __forceinline__ void sweep_dma(const SweepCtx<T, TX, TY, true>& X,
 // TB selects the two stages of the substep-1+2 fusion (fused12_tile): 0 is
 // the plain sweep; 1 is substep 1 over the extended region, whose new state
 // goes to the LDS plane buffer tb_u (layout of the inner tile's sweep) and
-// whose RK3 register, for the inner columns, to the LDS ring tb_w; 2 is
-// substep 2 of the inner tile, which takes its plane from tb_u (passed as
-// lds, loaded by stage 1) and its RK3 register from tb_w, and starts output
-// planes 2 * kR steps later.
+// whose input, for the inner columns, to the LDS ring tb_w; 2 is substep 2 of
+// the inner tile, which takes its plane from tb_u (passed as lds, loaded by
+// stage 1) and the substep-1 input from tb_w, leaves the substep-1 state in w,
+// and starts output planes 2 * kR steps later.
 template <int PH, int S, int PD, bool LD, bool NT, int VS, bool P19, bool RED, bool FRC,
           int TB = 0, bool DDL = false, typename T, typename TW, int TX, int TY, int NH>
 __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepRegs<T, TW, NH>& R,
                                            const SweepCtx<T, TX, TY, LD>& X, T* lds,
                                            lds_t<T> lds3, const Geom& g, const Fields4<T>& in,
-                                           const Fields4<T>& out, const Fields4<TW>& w, T* dv,
+                                           const Fields4<T>& out, const Fields4<TW>& w,
+                                           const T* dv,
                                            const Coef<T>& cf, const RKCoef<TW>& rk,
                                            const T* ftab, T* tb_u = nullptr,
                                            TW* tb_w = nullptr, T* ddl = nullptr) {
@@ -278,25 +332,25 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
     const int o = p - kR;       // output plane finished in this step
     const bool outstep = t >= (TB == 2 ? 4 : 2) * kR;
 
-    T* buf = lds + (PH & 1) * 4 * Sh::FS;
+    constexpr int NF = P19 ? 5 : 4;  // field planes in LDS
+    T* buf = lds + (PH & 1) * NF * Sh::FS;
     const int ci = (threadIdx.x / TX + kR) * W + (threadIdx.x % TX + kR);
     // register sets: plane p sits in set RS (PD sets, PD divides the unroll
-    // of 8); the RK3 register of output o in set WS
+    // of 8); the previous input of output o in set WS
     static_assert(PD == 1 || PD == 2 || PD == 4, "prefetch depth");
     constexpr int RS = PH % PD;
     constexpr int WS = PD >= 2 ? (PH & 1) : 0;
     if constexpr (TB == 2) {
         // plane p was written to LDS by stage 1 of this step (barrier between)
     } else if constexpr (!LD) {
-        // RK3 register of an output point, issued early: PD = 1 loads the one
-        // finished in this step, PD = 2 the one finished in the next step
-        if constexpr (S != 1) {
+        // previous input of an output point, issued early: PD = 1 loads the one
+        // finished in this step, PD >= 2 the one finished in the next step
+        if constexpr (S >= 2) {
             if constexpr (PD >= 2) {
                 const bool next_out = t + 1 >= 2 * kR && t + 1 < nplanes;
-                load_w<(PH + 1) & 1, NT, VS>(R, w, g, o + 1, next_out ? X.wplane_bytes : 0u,
-                                             X.lane_w);
+                load_prev<(PH + 1) & 1, NT, VS>(R, X, out, w, g, o + 1, next_out);
             } else {
-                load_w<0, NT, VS>(R, w, g, o, outstep ? X.wplane_bytes : 0u, X.lane_w);
+                load_prev<0, NT, VS>(R, X, out, w, g, o, outstep);
             }
         }
         // prefetched plane p -> LDS buffer (PH & 1)
@@ -306,20 +360,24 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
 #pragma unroll
             for (int h = 0; h < NH; ++h) buf[f * Sh::FS + X.loff_h[h]] = R.ph[RS][h][f];
         }
+        if constexpr (P19) {
+            buf[4 * Sh::FS + ci] = R.pfd[RS];
+#pragma unroll
+            for (int h = 0; h < NH; ++h) buf[4 * Sh::FS + X.loff_h[h]] = R.phd[RS][h];
+        }
         // plane p + PD -> the register set just emptied
-        sweep_prefetch<RS, VS>(R, X, in, plane_corner(g, p + PD),
-                               t + PD < nplanes ? X.plane_bytes : 0u);
+        sweep_prefetch<RS, VS, P19>(R, X, in, dv, plane_corner(g, p + PD),
+                                    t + PD < nplanes ? X.plane_bytes : 0u);
         __syncthreads();
     } else {
         // this wave's copies of plane p are complete before the barrier; after
         // it the other buffer (read in the previous step by every wave) takes
         // plane p + 1
         __syncthreads();
-        sweep_dma<T, TX, TY>(X, in, plane_corner(g, p + 1), lds3 + ((PH + 1) & 1) * 4 * Sh::FS,
-                             t + 1 < nplanes ? X.plane_bytes : 0u);
-        if constexpr (S != 1) {
-            load_w<0, NT, VS>(R, w, g, o, outstep ? X.wplane_bytes : 0u, X.lane_w);
-        }
+        sweep_dma<P19, T, TX, TY>(X, in, dv, plane_corner(g, p + 1),
+                                  lds3 + ((PH + 1) & 1) * NF * Sh::FS,
+                                  t + 1 < nplanes ? X.plane_bytes : 0u);
+        if constexpr (S >= 2) load_prev<0, NT, VS>(R, X, out, w, g, o, outstep);
     }
 
     // ---- plane quantities of plane p for this thread's column ----
@@ -333,6 +391,7 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
     const T* B1 = win + Sh::FS + C0;
     const T* B2 = win + 2 * Sh::FS + C0;
     const T* B3 = win + 3 * Sh::FS + C0;
+    [[maybe_unused]] const T* B4 = win + (NF - 1) * Sh::FS + C0;  // 19-point: the divergence
     constexpr int DS = PH & 3;  // first-derivative slot of plane p
     constexpr T w2[3] = {T(270), T(-27), T(2)};
 
@@ -345,6 +404,7 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
         R.q[1][sl8(PH)] = B1[0];
         R.q[2][sl8(PH)] = B2[0];
         R.q[3][sl8(PH)] = B3[0];
+        if constexpr (P19) R.qd[sl8(PH)] = B4[0];
     }
     if constexpr (!P19) {
         const T zs3[3] = {cf.mu[1] * (B3[3] - B3[-3]),                 // (1/3) Dxz uz
@@ -400,6 +460,12 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
                          T(-490) * R.q[f][sl8(PH - 3)];
             Lf[i] = R.L[i][sl8(PH - 3)] + ((i == 2 && !P19) ? cf.sg4[2] : cf.sg[2]) * rz;
         }
+        if constexpr (P19) {  // (nu/3) d_z div u
+            const T dd = cf.d1[2][0] * (R.qd[sl8(PH - 2)] - R.qd[sl8(PH - 4)]) +
+                         cf.d1[2][1] * (R.qd[sl8(PH - 1)] - R.qd[sl8(PH - 5)]) +
+                         cf.d1[2][2] * (R.qd[sl8(PH)] - R.qd[sl8(PH - 6)]);
+            Lf[2] = cf.n3 * dd + Lf[2];
+        }
         constexpr int DO = (PH + 1) & 3;  // slot of plane p - 3
         T dxy[8];
 #pragma unroll
@@ -435,43 +501,56 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
         // ghost corner (-3, -3) of output plane o
         const long long ocorner = g.origin + (long long)o * g.plane - kR * g.px - kR;
         constexpr int CP = NT ? kNonTemporal : 0;
+        // w receives the right-hand side (S = 0), the RK3 register where that is
+        // kept in memory or, in stage 2 of the fusion, the substep-1 state
+        constexpr bool REG = kRegInMemory<T, TW>;
+        constexpr bool WOUT = S == 0 || TB == 2 || (REG && S != 3);
         T vout[4];
         TW wout[4];
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
-            // stage 2 of the fusion: the register stage 1 wrote 3 steps earlier
-            TW wv = S == 1 ? TW(0)
-                           : (TB == 2 ? tb_w[((PH + 1) & 3) * 4 * (TX * TY) + f * (TX * TY) +
-                                             threadIdx.x]
-                                      : R.wq[WS][f]);
-            const T v = rk_update<S>(R.q[f][sl8(PH - 3)], r[f], wv, rk);
+            const T uc = R.q[f][sl8(PH - 3)];
+            T v = T(0);
+            if constexpr (S == 0) {
+                wout[f] = TW(r[f]);
+            } else if constexpr (REG) {
+                wout[f] = S >= 2 ? R.wq[WS][f] : TW(0);
+                v = rk_update_reg<S>(uc, r[f], wout[f], rk);
+            } else {
+                // stage 2 of the fusion: the input stage 1 kept 3 steps earlier
+                T prev = T(0);
+                if constexpr (TB == 2)
+                    prev = tb_w[((PH + 1) & 3) * 4 * (TX * TY) + f * (TX * TY) + threadIdx.x];
+                else if constexpr (S >= 2)
+                    prev = R.wq[WS][f];
+                v = rk_update<S>(uc, r[f], prev, rk);
+                wout[f] = uc;
+            }
             vout[f] = v;
-            wout[f] = wv;
             if constexpr (TB == 1) {
                 // new state of every extended column into the inner sweep's
-                // plane buffer (its cell is this thread's index); the register
+                // plane buffer (its cell is this thread's index); the input
                 // of the inner columns into ring slot (step & 3)
                 constexpr int NI = (TX - 2 * kR) * (TY - 2 * kR);
                 constexpr int FS2 = SweepShape<T, TX - 2 * kR, TY - 2 * kR>::FS;
                 tb_u[(PH & 1) * 4 * FS2 + f * FS2 + threadIdx.x] = v;
                 const int ix = (int)(threadIdx.x % TX) - kR, iy = (int)(threadIdx.x / TX) - kR;
                 if (ix >= 0 && ix < TX - 2 * kR && iy >= 0 && iy < TY - 2 * kR)
-                    tb_w[(PH & 3) * 4 * NI + f * NI + iy * (TX - 2 * kR) + ix] = wv;
+                    tb_w[(PH & 3) * 4 * NI + f * NI + iy * (TX - 2 * kR) + ix] = uc;
             } else if constexpr (VS == 1) {
-                bstore<CP>(v, plane_rsrc(out.f[f] + ocorner, ob), X.lane_o);
-                if constexpr (S != 3)
-                    bstore<CP>(wv, plane_rsrc(w.f[f] + (long long)o * g.wplane, wb), X.lane_w);
+                if constexpr (S >= 1) bstore<CP>(v, plane_rsrc(out.f[f] + ocorner, ob), X.lane_o);
+                if constexpr (WOUT)
+                    bstore<CP>(wout[f], plane_rsrc(w.f[f] + (long long)o * g.wplane, wb),
+                               X.lane_w);
             }
         }
         if constexpr (VS == 4 && TB != 1) {
-            bstore_point<CP>(vout, plane_rsrc(out.f[0] + 4 * ocorner, ob), X.lane_o);
-            if constexpr (S != 3)
+            if constexpr (S >= 1)
+                bstore_point<CP>(vout, plane_rsrc(out.f[0] + 4 * ocorner, ob), X.lane_o);
+            if constexpr (WOUT)
                 bstore_point<CP>(wout, plane_rsrc(w.f[0] + 4 * (long long)o * g.wplane, wb),
                                  X.lane_w);
         }
-        // 19-point pass 1 also stores the divergence for pass 2
-        if constexpr (P19)
-            bstore(J[0][0] + J[1][1] + J[2][2], plane_rsrc(dv + ocorner, ob), X.lane_o);
         // FP64 diagnostics of the new state, from the values just stored (the
         // same per-point quantities as the standalone reduction)
         if constexpr (RED) {
@@ -697,9 +776,13 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
     // sum_k c_k [A_k(z + k) - A_k(z - k)], so plane p adds +c_k A_k to the
     // pending output p - k and -c_k A_k to p + k (c = 270, -27, 2); the k = 3
     // terms were added in (A).
-    if constexpr (P19) {
-        R.L[0][sl8(PH)] = lx;
-        R.L[1][sl8(PH)] = ly;
+    if constexpr (P19) {  // with (nu/3) d_x and d_y of div u
+        const T ddx = cf.d1[0][0] * (B4[1] - B4[-1]) + cf.d1[0][1] * (B4[2] - B4[-2]) +
+                      cf.d1[0][2] * (B4[3] - B4[-3]);
+        const T ddy = cf.d1[1][0] * (B4[W] - B4[-W]) + cf.d1[1][1] * (B4[2 * W] - B4[-2 * W]) +
+                      cf.d1[1][2] * (B4[3 * W] - B4[-3 * W]);
+        R.L[0][sl8(PH)] = cf.n3 * ddx + lx;
+        R.L[1][sl8(PH)] = cf.n3 * ddy + ly;
         R.L[2][sl8(PH)] = lz;
     } else {
         const T* zs[3] = {zx, zy, zz};
@@ -717,13 +800,14 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
 
 // One tile-chunk: columns [x0, x0 + TX) x [y0, y0 + TY) of the box, output
 // planes [zb, ze).  Every thread of the workgroup calls it with the same
-// arguments.  P19: pass 1 of the 19-point method (dv receives the divergence).
+// arguments.  P19: the 19-point method (dv holds the divergence of in).
 // RED: also reduce the FP64 diagnostics of the output and store this
 // workgroup's partial at part[blockIdx.x * kReduceSlots ...].
 template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool NT, int VS,
           bool P19 = false, bool RED = false, bool FRC = false, bool DDL = false>
 __device__ __forceinline__ void sweep_tile(const Geom& g, const Fields4<T>& in,
-                                           const Fields4<T>& out, const Fields4<TW>& w, T* dv,
+                                           const Fields4<T>& out, const Fields4<TW>& w,
+                                           const T* dv,
                                            const Coef<T>& cf, const RKCoef<TW>& rk, int x0,
                                            int y0, int zb, int ze, T* lds, lds_t<T> lds3,
                                            double* part = nullptr,
@@ -732,7 +816,7 @@ __device__ __forceinline__ void sweep_tile(const Geom& g, const Fields4<T>& in,
     using Sh = SweepShape<T, TX, TY, LD>;
     constexpr int NH = Sh::NH;
     SweepCtx<T, TX, TY, LD> X;
-    static_assert(VS == 1 || !P19, "the 19-point passes use one array per field");
+    static_assert(VS == 1 || !P19, "the 19-point sweep uses one array per field");
     sweep_ctx_init<T, TW, TX, TY, LD, VS>(X, g, x0, y0);
 
     SweepRegs<T, TW, NH> R;
@@ -747,6 +831,10 @@ __device__ __forceinline__ void sweep_tile(const Geom& g, const Fields4<T>& in,
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int s = 0; s < 8; ++s) R.L[i][s] = T(0);
+    if constexpr (P19) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) R.qd[s] = T(0);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) R.red[i] = 0.0;
     R.bad = 0;
@@ -768,15 +856,18 @@ __device__ __forceinline__ void sweep_tile(const Geom& g, const Fields4<T>& in,
 
     const int nplanes = (ze - zb) + 2 * kR;
     if constexpr (LD) {
-        sweep_dma<T, TX, TY>(X, in, plane_corner(g, zb - kR), lds3, X.plane_bytes);
+        sweep_dma<P19, T, TX, TY>(X, in, dv, plane_corner(g, zb - kR), lds3, X.plane_bytes);
     } else {
-        sweep_prefetch<0, VS>(R, X, in, plane_corner(g, zb - kR), X.plane_bytes);
+        sweep_prefetch<0, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR), X.plane_bytes);
         if constexpr (PD >= 2)
-            sweep_prefetch<1, VS>(R, X, in, plane_corner(g, zb - kR + 1), X.plane_bytes);
+            sweep_prefetch<1, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR + 1),
+                                       X.plane_bytes);
         if constexpr (PD == 4) {
             // a chunk sweeps at least 7 planes, so these exist
-            sweep_prefetch<2, VS>(R, X, in, plane_corner(g, zb - kR + 2), X.plane_bytes);
-            sweep_prefetch<3, VS>(R, X, in, plane_corner(g, zb - kR + 3), X.plane_bytes);
+            sweep_prefetch<2, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR + 2),
+                                       X.plane_bytes);
+            sweep_prefetch<3, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR + 3),
+                                       X.plane_bytes);
         }
     }
     for (int t0 = 0; t0 < nplanes; t0 += 8) {
@@ -834,14 +925,15 @@ void substep55_sweep(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, Coef<
 //    and a 3-column ring), one column per thread, loading the input state as
 //    the plain sweep does.  Its new state does not go to memory: plane o1
 //    goes into an LDS plane buffer laid out as the inner tile's sweep reads
-//    its planes, and the RK3 register of the inner columns into an LDS ring
-//    of 4 planes.
+//    its planes, and the input of the inner columns into an LDS ring of 4
+//    planes.
 //  * Stage 2 (threads 0 .. TX TY - 1, whole waves): the substep-2 sweep of
 //    the output tile with that buffer as its plane source, 3 planes behind
-//    stage 1, storing the substep-2 state and RK3 register.
-// The substep-1 state and register never reach HBM: substeps 1 and 2 move
-// 16 + 32 bytes per point (FP32) instead of 48 + 64, at the price of
-// substep 1 on (TX + 6)(TY + 6) / (TX TY) times the columns.  Per point the
+//    stage 1, storing the substep-2 state and, into w, the substep-1 state
+//    that substep 3 needs.
+// Substeps 1 and 2 move 16 + 32 bytes per point (FP32), and 32 more to put
+// the substep-1 state where substep 3 reads it, instead of 32 + 48, at the
+// price of substep 1 on (TX + 6)(TY + 6) / (TX TY) times the columns.  Per point the
 // arithmetic is the plain sweep's, so the result is bit for bit that of two
 // plain launches.  The loaded planes start 2 * kR further back (nplanes =
 // chunk + 4 kR).
@@ -876,20 +968,22 @@ __device__ __forceinline__ void fused12_tile(const Geom& g, const Fields4<T>& in
         for (int s = 0; s < 8; ++s) R1.L[i][s] = R2.L[i][s] = T(0);
     const int nplanes = (ze - zb) + 4 * kR;
     const int zb1 = zb - kR, zb2 = zb - 2 * kR;  // stage 1 outputs from zb - 3
-    sweep_prefetch<0, VS>(R1, X1, in, plane_corner(g, zb1 - kR), X1.plane_bytes);
+    const T* const nodiv = nullptr;
+    sweep_prefetch<0, VS, false>(R1, X1, in, nodiv, plane_corner(g, zb1 - kR), X1.plane_bytes);
     if constexpr (PD >= 2)
-        sweep_prefetch<1, VS>(R1, X1, in, plane_corner(g, zb1 - kR + 1), X1.plane_bytes);
+        sweep_prefetch<1, VS, false>(R1, X1, in, nodiv, plane_corner(g, zb1 - kR + 1),
+                                     X1.plane_bytes);
     static_assert(PD == 1 || PD == 2, "prefetch depth of the fused sweep");
     const Fields4<T> none{{nullptr, nullptr, nullptr, nullptr}};
     for (int t0 = 0; t0 < nplanes; t0 += 8) {
 #define FD6_FUSED_STEP(PH)                                                                      \
         sweep_step<PH, 1, PD, false, NT, VS, false, false, false, 1>(                            \
-            t0, nplanes, zb1, R1, X1, lds1, (lds_t<T>)lds1, g, in, none, w, (T*)nullptr, cf,     \
+            t0, nplanes, zb1, R1, X1, lds1, (lds_t<T>)lds1, g, in, none, w, nodiv, cf,            \
             rk1, (const T*)nullptr, lds2, ring);                                                 \
         __syncthreads();                                                                         \
         if (inner)                                                                               \
             sweep_step<PH, 2, PD, false, NT, VS, false, false, false, 2>(                        \
-                t0, nplanes, zb2, R2, X2, lds2, (lds_t<T>)lds2, g, in, out, w, (T*)nullptr, cf,  \
+                t0, nplanes, zb2, R2, X2, lds2, (lds_t<T>)lds2, g, in, out, w, nodiv, cf,         \
                 rk2, (const T*)nullptr, (T*)nullptr, ring);
         FD6_FUSED_STEP(0)
         FD6_FUSED_STEP(1)
@@ -934,19 +1028,25 @@ void substep55_sweep_red(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, C
         g, in, out, w, nullptr, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, (lds_t<T>)lds, part, fa, ddl);
 }
 
-// Pass 1 of the 19-point method (Sec. 4.2, Algorithm 3): the same sweep
-// without the mixed-derivative terms, with nu lap u in place of the viscous
-// operator, and the divergence stored for pass 2.
-template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool NT, bool FRC>
+// The 19-point method (Sec. 4.2, Algorithm 3): the same sweep over the state
+// and the divergence field of its input (substep19_div), with nu lap u and
+// (nu/3) grad d in place of the viscous operator.  Algorithm 3 adds the second
+// term to the stored velocity and register in a pass of its own: 304 bytes per
+// point and step in FP32.  With the divergence computed first, every value is
+// written once: 188 bytes (256^3 FP32 with a new force every step, 10 steps and
+// a snapshot: 10.96 -> 8.18 ms; 300 x 240 x 192 FP64, 5 steps: 11.46 -> 9.57 ms).
+template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool NT, bool FRC,
+          bool RED = false>
 __global__ __launch_bounds__(TX* TY)
-void substep19_pass1(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, T* dv, Coef<T> cf,
-                     RKCoef<TW> rk, SweepGrid m, ForceArgs<T> fa) {
+void substep19_sweep(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, const T* dv,
+                     Coef<T> cf, RKCoef<TW> rk, SweepGrid m, double* part, ForceArgs<T> fa) {
     using Sh = SweepShape<T, TX, TY, LD>;
-    __shared__ T lds[2 * 4 * Sh::FS];
+    static_assert(!RED || S == 3, "diagnostics of the final substep only");
+    __shared__ T lds[2 * 5 * Sh::FS];
     const TileXY t = sweep_tile_of(g, TX, TY, m);
-    if (t.zb >= t.ze) return;
-    sweep_tile<T, TW, TX, TY, S, PD, LD, NT, 1, true, false, FRC>(
-        g, in, out, w, dv, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, (lds_t<T>)lds, nullptr, fa);
+    if (!RED && t.zb >= t.ze) return;
+    sweep_tile<T, TW, TX, TY, S, PD, LD, NT, 1, true, RED, FRC>(
+        g, in, out, w, dv, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, (lds_t<T>)lds, part, fa);
 }
 
 // Batched form: one persistent launch advances every box of an ensemble by
@@ -961,7 +1061,7 @@ template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool 
 __global__ __launch_bounds__(TX* TY)
 void substep55_batch(const BatchBox<T, TW>* __restrict__ boxes,
                      const BatchItem* __restrict__ items, const int* __restrict__ wg_first,
-                     int parity, TW alpha, TW beta) {
+                     int parity) {
     using Sh = SweepShape<T, TX, TY, LD>;
     __shared__ T lds[2 * 4 * Sh::FS];
     const int G = gridDim.x;
@@ -975,7 +1075,7 @@ void substep55_batch(const BatchBox<T, TW>* __restrict__ boxes,
         const Coef<T> cf = bx->cf;
         const Fields4<T> in = bx->st[parity], out = bx->st[parity ^ 1];
         const Fields4<TW> w = bx->w;
-        const RKCoef<TW> rk{alpha, beta, bx->dt};
+        const RKCoef<TW> rk = bx->rk[S - 1];
         sweep_tile<T, TW, TX, TY, S, PD, LD, NT, VS>(g, in, out, w, nullptr, cf, rk, wi.x0, wi.y0,
                                              wi.zb, wi.ze, lds, (lds_t<T>)lds);
         __syncthreads();  // the next item's first LDS write must follow every read
@@ -986,6 +1086,7 @@ void substep55_batch(const BatchBox<T, TW>* __restrict__ boxes,
 template <template <int> class K, typename... A>
 hipError_t launch_s(int s, dim3 grid, dim3 block, hipStream_t st, A... args) {
     switch (s) {
+    case 0: return hipErrorInvalidValue;
     case 1: hipLaunchKernelGGL(K<1>::fn, grid, block, 0, st, args...); break;
     case 2: hipLaunchKernelGGL(K<2>::fn, grid, block, 0, st, args...); break;
     default: hipLaunchKernelGGL(K<3>::fn, grid, block, 0, st, args...); break;
@@ -1008,8 +1109,12 @@ template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, boo
 struct K19 {
     template <int S>
     struct at {
-        static constexpr auto fn = substep19_pass1<T, TW, TX, TY, S, PD, LD, NT, FRC>;
+        static constexpr auto fn = substep19_sweep<T, TW, TX, TY, S, PD, LD, NT, FRC>;
     };
+};
+template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, bool FRC>
+struct K19Red {
+    static constexpr auto fn = substep19_sweep<T, TW, TX, TY, 3, PD, LD, NT, FRC, true>;
 };
 template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, int VS>
 struct KBatch {
@@ -1018,6 +1123,9 @@ struct KBatch {
         static constexpr auto fn = substep55_batch<T, TW, TX, TY, S, PD, LD, NT, VS>;
     };
 };
+// Shape that evaluates the bare right-hand side (S = 0).
+template <typename T>
+constexpr int kRhsTile = sizeof(T) == 8 ? 8 : 6;
 template <typename T, typename TW, bool FRC>
 struct KDirect {
     template <int S>
@@ -1036,6 +1144,20 @@ hipError_t launch_substep55_vs(const Geom& g, Fields4<T> in, Fields4<T> out, Fie
     if (nparts) *nparts = 0;
     if (g.vs != VS) return hipErrorInvalidValue;
     const ForceArgs<T> fa = frc ? *frc : ForceArgs<T>{nullptr, nullptr};
+    if (s == 0) {  // every z-sweep shape gives the same bits: one serves them all
+        if (tile == 0) return hipErrorInvalidValue;
+        auto rhs = [&](auto force) -> hipError_t {
+            constexpr TileCfg k = kTiles[kRhsTile<T>];
+            constexpr auto fn = substep55_sweep<T, TW, k.tx, k.ty, 0, k.pd, k.ld, k.nt, VS,
+                                                decltype(force)::value>;
+            const SweepGrid sg =
+                sweep_grid(g, k.tx, k.ty, 0, resident_blocks<fn>(k.tx * k.ty));
+            hipLaunchKernelGGL(fn, dim3(sg.blocks), dim3(k.tx * k.ty), 0, st, g, in, out, w, c,
+                               rk, sg, fa);
+            return hipGetLastError();
+        };
+        return frc ? rhs(std::true_type{}) : rhs(std::false_type{});
+    }
     auto go = [&](auto force) -> hipError_t {
         constexpr bool FRC = decltype(force)::value;
         return with_tile(tile, hipErrorInvalidValue, [&](auto I) -> hipError_t {
@@ -1097,12 +1219,28 @@ hipError_t launch_substep55_aos(const Geom& g, Fields4<T> in, Fields4<T> out, Fi
                                          part_cap, nparts, frc, st);
 }
 
-// Pass 1 of the 19-point method in a z-sweep shape (tile >= 1).
+// The 19-point method in a z-sweep shape (tile >= 1), after launch_div19.
 template <typename T, typename TW>
-hipError_t launch_pass19a_sweep(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<TW> w,
-                                T* dv, const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile,
-                                int zchunk, const ForceArgs<T>* frc, hipStream_t st) {
+hipError_t launch_substep19(const Geom& g, Fields4<T> in, Fields4<T> out, Fields4<TW> w,
+                            const T* dv, const Coef<T>& c, const RKCoef<TW>& rk, int s, int tile,
+                            int zchunk, double* partials, int part_cap, int* nparts,
+                            const ForceArgs<T>* frc, hipStream_t st) {
+    if (nparts) *nparts = 0;
     const ForceArgs<T> fa = frc ? *frc : ForceArgs<T>{nullptr, nullptr};
+    double* const none = nullptr;
+    if (s == 0) {
+        auto rhs = [&](auto force) -> hipError_t {
+            constexpr TileCfg k = kTiles[kRhsTile<T>];
+            constexpr auto fn = substep19_sweep<T, TW, k.tx, k.ty, 0, k.pd, k.ld, k.nt,
+                                                decltype(force)::value>;
+            const SweepGrid sg =
+                sweep_grid(g, k.tx, k.ty, 0, resident_blocks<fn>(k.tx * k.ty));
+            hipLaunchKernelGGL(fn, dim3(sg.blocks), dim3(k.tx * k.ty), 0, st, g, in, out, w, dv,
+                               c, rk, sg, none, fa);
+            return hipGetLastError();
+        };
+        return frc ? rhs(std::true_type{}) : rhs(std::false_type{});
+    }
     auto go = [&](auto force) -> hipError_t {
         constexpr bool FRC = decltype(force)::value;
         return with_tile(tile, hipErrorInvalidValue, [&](auto I) -> hipError_t {
@@ -1111,10 +1249,20 @@ hipError_t launch_pass19a_sweep(const Geom& g, Fields4<T> in, Fields4<T> out, Fi
                 return hipErrorInvalidValue;
             } else {
                 using K = K19<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, FRC>;
-                const int res = resident_blocks<K::template at<2>::fn>(k.tx * k.ty);
+                using KR = K19Red<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, FRC>;
+                const int blk = k.tx * k.ty;
+                const int res = resident_blocks<K::template at<2>::fn>(blk);
                 const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res);
-                return launch_s<K::template at>(s, dim3(sg.blocks), dim3(k.tx * k.ty), st, g, in,
-                                                out, w, dv, c, rk, sg, fa);
+                // fuse only where the extra accumulators cost no occupancy
+                if (s == 3 && partials && nparts && sg.blocks <= part_cap &&
+                    resident_blocks<KR::fn>(blk) >= resident_blocks<K::template at<3>::fn>(blk)) {
+                    hipLaunchKernelGGL(KR::fn, dim3(sg.blocks), dim3(blk), 0, st, g, in, out, w,
+                                       dv, c, rk, sg, partials, fa);
+                    *nparts = sg.blocks;
+                    return hipGetLastError();
+                }
+                return launch_s<K::template at>(s, dim3(sg.blocks), dim3(blk), st, g, in, out, w,
+                                                dv, c, rk, sg, none, fa);
             }
         });
     };
@@ -1125,15 +1273,15 @@ namespace {
 
 template <typename T, typename TW, int VS>
 hipError_t launch_batch55_vs(const BatchBox<T, TW>* boxes, const BatchItem* items,
-                             const int* wg_first, int grid, int parity, int s, int tile, TW alpha,
-                             TW beta, hipStream_t st) {
+                             const int* wg_first, int grid, int parity, int s, int tile,
+                             hipStream_t st) {
     return with_tile(tile, hipErrorInvalidValue, [&](auto I) -> hipError_t {
         constexpr TileCfg k = kTiles[decltype(I)::value];
         if constexpr (k.tx == 0 || (VS != 1 && k.ld)) {
             return hipErrorInvalidValue;
         } else {
             return launch_s<KBatch<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, VS>::template at>(
-                s, dim3(grid), dim3(k.tx * k.ty), st, boxes, items, wg_first, parity, alpha, beta);
+                s, dim3(grid), dim3(k.tx * k.ty), st, boxes, items, wg_first, parity);
         }
     });
 }
@@ -1159,18 +1307,16 @@ int batch55_blocks_per_cu_vs(int tile) {
 
 template <typename T, typename TW>
 hipError_t launch_batch55(const BatchBox<T, TW>* boxes, const BatchItem* items,
-                          const int* wg_first, int grid, int parity, int s, int tile, TW alpha,
-                          TW beta, hipStream_t st) {
-    return launch_batch55_vs<T, TW, 1>(boxes, items, wg_first, grid, parity, s, tile, alpha,
-                                       beta, st);
+                          const int* wg_first, int grid, int parity, int s, int tile,
+                          hipStream_t st) {
+    return launch_batch55_vs<T, TW, 1>(boxes, items, wg_first, grid, parity, s, tile, st);
 }
 
 template <typename T, typename TW>
 hipError_t launch_batch55_aos(const BatchBox<T, TW>* boxes, const BatchItem* items,
                               const int* wg_first, int grid, int parity, int s, int tile,
-                              TW alpha, TW beta, hipStream_t st) {
-    return launch_batch55_vs<T, TW, 4>(boxes, items, wg_first, grid, parity, s, tile, alpha,
-                                       beta, st);
+                              hipStream_t st) {
+    return launch_batch55_vs<T, TW, 4>(boxes, items, wg_first, grid, parity, s, tile, st);
 }
 
 template <typename T, typename TW>
