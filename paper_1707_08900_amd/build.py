@@ -33,18 +33,6 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-ffp
           "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option"]
 
 
-# Per-unit options.  The FP64 sweep kernels run at one wave per SIMD (they need
-# about 430 registers), so latency is hidden only by instruction-level
-# parallelism inside the wave: the scheduler's max-ILP strategy orders them for
-# that (512^3 AoS: 3640 -> 3525 us per launch; 32 x 8 with one array per field
-# 4268 -> 3742 us).  It slows the two-wave FP32 kernels (1462 -> 1583 us), so it
-# is applied to the FP64 units only.  Scheduling does not change results.
-UNIT_FLAGS = {
-    "substep55_f64.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-    "substep55_aos_f64.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-}
-
-
 # Host-side sanitizers only: each flag applies to the host compilation.
 HOST_SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
                  "-Xarch_host", "-fno-omit-frame-pointer"]
@@ -69,7 +57,7 @@ def _compile(src: str, resource_usage: bool, incremental: bool = False, build_di
     obj = os.path.join(build_dir, os.path.splitext(src)[0] + ".o")
     if incremental and not resource_usage and _up_to_date(src, obj):
         return obj
-    cmd = [HIPCC, *COMMON, *UNIT_FLAGS.get(src, []), *extra, "-x", "hip", "-c",
+    cmd = [HIPCC, *COMMON, *extra, "-x", "hip", "-c",
            os.path.join(CSRC, src), "-o", obj]
     if resource_usage:
         cmd.insert(1, "-Rpass-analysis=kernel-resource-usage")

@@ -20,8 +20,9 @@ namespace fd6 {
 
 // The arithmetic, with the fused multiply-add supplied by the caller (the
 // device form below, or a host fma for checking it on the CPU).
-template <typename Fma>
-__host__ __device__ inline double exp_fp64_with(double x, Fma fma) {
+// fmak: the same with a constant addend.
+template <typename Fma, typename FmaK>
+__host__ __device__ inline double exp_fp64_with(double x, Fma fma, FmaK fmak) {
     constexpr double kInvLn2 = 0x1.71547652b82fep+0;  // 1 / ln2
     constexpr double kLn2Hi = 0x1.62e42fee00000p-1;   // ln2, 32 significant bits
     constexpr double kLn2Lo = 0x1.a39ef35793c76p-33;  // ln2 - kLn2Hi
@@ -31,20 +32,25 @@ __host__ __device__ inline double exp_fp64_with(double x, Fma fma) {
     r = fma(-k, kLn2Lo, r);
     // sum_{n=0}^{13} r^n / n!, innermost term first
     double p = 1.0 / 6227020800.0;  // 1/13!
-    p = fma(p, r, 1.0 / 479001600.0);
-    p = fma(p, r, 1.0 / 39916800.0);
-    p = fma(p, r, 1.0 / 3628800.0);
-    p = fma(p, r, 1.0 / 362880.0);
-    p = fma(p, r, 1.0 / 40320.0);
-    p = fma(p, r, 1.0 / 5040.0);
-    p = fma(p, r, 1.0 / 720.0);
-    p = fma(p, r, 1.0 / 120.0);
-    p = fma(p, r, 1.0 / 24.0);
-    p = fma(p, r, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
+    p = fmak(p, r, 1.0 / 479001600.0);
+    p = fmak(p, r, 1.0 / 39916800.0);
+    p = fmak(p, r, 1.0 / 3628800.0);
+    p = fmak(p, r, 1.0 / 362880.0);
+    p = fmak(p, r, 1.0 / 40320.0);
+    p = fmak(p, r, 1.0 / 5040.0);
+    p = fmak(p, r, 1.0 / 720.0);
+    p = fmak(p, r, 1.0 / 120.0);
+    p = fmak(p, r, 1.0 / 24.0);
+    p = fmak(p, r, 1.0 / 6.0);
+    p = fmak(p, r, 0.5);
+    p = fmak(p, r, 1.0);
+    p = fmak(p, r, 1.0);
     return __builtin_ldexp(p, (int)k);
+}
+
+template <typename Fma>
+__host__ __device__ inline double exp_fp64_with(double x, Fma fma) {
+    return exp_fp64_with(x, fma, fma);
 }
 
 // a * b + c as one three-operand instruction.  With the plain builtin the
@@ -59,6 +65,23 @@ struct FmaVop3 {
     }
 };
 
-__device__ __forceinline__ double exp_fp64(double x) { return exp_fp64_with(x, FmaVop3{}); }
+// The same with the addend in scalar registers, where a constant costs two scalar
+// moves per use; in vector registers the 13 constants of the chain would stay
+// resident (26 registers of kernels that have none to spare).
+struct FmaVop3K {
+    __device__ __forceinline__ double operator()(double a, double b, double c) const {
+        double d;
+        asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+        return d;
+    }
+};
+
+template <bool ScalarK = false>
+__device__ __forceinline__ double exp_fp64(double x) {
+    if constexpr (ScalarK)
+        return exp_fp64_with(x, FmaVop3{}, FmaVop3K{});
+    else
+        return exp_fp64_with(x, FmaVop3{});
+}
 
 }  // namespace fd6

@@ -210,8 +210,8 @@ int make_plan(const fd6_desc* d, Plan* p) {
     g.wfelems = (long long)round_up((size_t)(g.wplane * d->nz) * p->wsize, kAlign) /
                 (long long)p->wsize;
     if (g.felems > kMaxFieldElems || g.wfelems > kMaxFieldElems) return FD6_EUNSUPPORTED;
-    // array of structures: one array of 4 values per point, field q starting
-    // q elements in (the same bytes as four separate fields)
+    // array of structures: one array of 4 values per point (the same bytes as
+    // four separate fields)
     const bool aos = d->flags == FD6_LAYOUT_AOS;
     g.vs = aos ? 4 : 1;
     size_t off = 0;
@@ -220,9 +220,9 @@ int make_plan(const fd6_desc* d, Plan* p) {
     for (int s = 0; s < 2; ++s)
         for (int q = 0; q < 4; ++q)
             p->off_state[s][q] =
-                aos ? off + 4 * s * fbytes + q * p->tsize : off + (4 * s + q) * fbytes;
+                aos ? off + 4 * s * fbytes + (q + 3) % 4 * p->tsize : off + (4 * s + q) * fbytes;
     off += 8 * fbytes;
-    for (int q = 0; q < 4; ++q) p->off_w[q] = aos ? off + q * p->wsize : off + q * wbytes;
+    for (int q = 0; q < 4; ++q) p->off_w[q] = aos ? off + (q + 3) % 4 * p->wsize : off + q * wbytes;
     off += 4 * wbytes;
     p->off_div = off;
     if (d->variant == FD6_19P) off += fbytes;
@@ -287,18 +287,53 @@ int timed(fd6_box* b, std::vector<std::pair<hipEvent_t, hipEvent_t>>& log, F&& f
 constexpr double kAlpha[3] = {0.0, -5.0 / 9.0, -153.0 / 128.0};
 constexpr double kBeta[3] = {1.0 / 3.0, 15.0 / 16.0, 8.0 / 15.0};
 
-// Constants of substep s (1, 2, 3) for time step dt, in the precision of the
-// update.  b and c derive from dt as that precision holds it.  A dt so small
-// that 1 / dt overflows makes no increment that a state could hold: c stays
-// finite and multiplies in - prev = 0.
+// Constants of the three substeps for time step dt, in the precision of the
+// update (b and c derive from dt as that precision holds it).  A dt so small that
+// 1 / dt overflows makes no increment that a state could hold: c stays finite and
+// multiplies in - prev = 0.
+//
+// In FP32 the five rounded factors leave the step's first- and second-order
+// terms off by up to 1.2e-7 (relative), more than alpha, beta and dt rounded by
+// themselves (5e-8), and that error is the same in every step.  So each is taken
+// one unit in the last place up or down where the set then meets dt, dt^2 / 2 and
+// dt^3 / 6 best (1.5e-8 and better).
 template <typename T, typename TW>
-RKCoef<TW> make_rk(int s, double dt) {
+std::array<RKCoef<TW>, 3> make_rk(double dt) {
     const double h = (double)TW(dt), big = (double)std::numeric_limits<TW>::max();
-    RKCoef<TW> r{TW(kAlpha[s - 1]), TW(kBeta[s - 1]), TW(dt), TW(kBeta[s - 1] * h), TW(0)};
-    if (!std::is_same<T, TW>::value)
-        r.c = s == 1 ? TW(4.0) : s == 2 ? TW(80.0 / 51.0) : TW(0);
-    else if (s > 1)
-        r.c = TW(std::max(kAlpha[s - 1] / (kBeta[s - 2] * h), -big));
+    std::array<RKCoef<TW>, 3> r;
+    for (int s = 0; s < 3; ++s) {
+        r[s] = RKCoef<TW>{TW(kAlpha[s]), TW(kBeta[s]), TW(dt), TW(kBeta[s] * h), TW(0)};
+        if (!std::is_same<T, TW>::value)
+            r[s].c = s == 0 ? TW(4.0) : s == 1 ? TW(80.0 / 51.0) : TW(0);
+        else if (s > 0)
+            r[s].c = TW(std::max(kAlpha[s] / (kBeta[s - 1] * h), -big));
+    }
+    // (outside this range of dt the factors or their squares leave FP32's)
+    if (std::is_same<TW, float>::value && h > 1e-15 && h < 1e15) {
+        TW* const f[5] = {&r[0].b, &r[1].b, &r[2].b, &r[1].c, &r[2].c};
+        TW near[5][3], best[5] = {};
+        for (int i = 0; i < 5; ++i) {
+            near[i][0] = *f[i];
+            near[i][1] = std::nextafter(*f[i], TW(-big));
+            near[i][2] = std::nextafter(*f[i], TW(big));
+        }
+        double least = -1.0;
+        for (int k = 0; k < 243; ++k) {
+            TW v[5];
+            for (int i = 0, d = k; i < 5; ++i, d /= 3) v[i] = near[i][d % 3];
+            const double b1 = v[0], b2 = v[1], b3 = v[2], c2 = v[3], c3 = v[4];
+            const double g = 1.0 + c2 * b1, s = b1 + b2 * g;
+            const double e1 = (s + b3 * (1.0 + c3 * b2 * g)) / h - 1.0;
+            const double e2 = 2.0 * (b2 * b1 + b3 * (s + c3 * b2 * b1)) / (h * h) - 1.0;
+            const double e3 = 6.0 * b3 * b2 * b1 / (h * h * h) - 1.0;
+            const double e = std::max({std::fabs(e1), std::fabs(e2), 0.3 * std::fabs(e3)});
+            if (least < 0.0 || e < least) {
+                least = e;
+                std::copy(v, v + 5, best);
+            }
+        }
+        for (int i = 0; i < 5; ++i) *f[i] = best[i];
+    }
     return r;
 }
 
@@ -307,7 +342,7 @@ Coef<T> make_coef(const fd6_params& p) {
     const double h[3] = {p.dx, p.dy, p.dz};
     const double w1[3] = {45.0, -9.0, 1.0};
     const double w2[4] = {-490.0, 270.0, -27.0, 2.0};
-    const double wm[3] = {270.0, -27.0, 2.0};
+    const double wm[4] = {270.0, -27.0, 2.0, 1.0};
     Coef<T> c{};
     double d2[3][4];
     for (int a = 0; a < 3; ++a) {
@@ -333,19 +368,41 @@ Coef<T> make_coef(const fd6_params& p) {
     c.cs2 = T(p.cs * p.cs);
     c.nu3 = p.nu / 3.0;
     c.n3 = T(c.nu3);
-    double sg[3], sg4[3];
+    double sg[3];
     for (int a = 0; a < 3; ++a) {
         sg[a] = p.nu / (180.0 * h[a] * h[a]);
-        sg4[a] = (4.0 / 3.0) * sg[a];
-        c.sg[a] = T(sg[a]);
-        c.sg4[a] = T(sg4[a]);
+        for (int k = 0; k < 4; ++k) {
+            c.s[a][k] = T(wm[k] * sg[a]);
+            c.s4[a][k] = T(wm[k] * (4.0 / 3.0) * sg[a]);
+        }
     }
-    for (int i = 0; i < 3; ++i) {
-        const double sx = i == 0 ? sg4[0] : sg[0], sy = i == 1 ? sg4[1] : sg[1];
-        c.kxy[i] = T(-490.0 * (sx + sy));
-    }
-    for (int q = 0; q < 3; ++q) c.mu[q] = T(p.nu / (3.0 * 720.0 * h[pa[q]] * h[pb[q]]));
-    c.kp = T(-490.0 * (sg[0] + sg[1]));
+    // The second derivatives of a component must cancel on a constant: what the
+    // rounded weights leave over damps or drives every mode alike, step after step
+    // (512^3 FP32, 10 steps: the sums of the diagnostics off by 4.5e-7 instead of
+    // 4e-8, the fields by 9.7e-8 instead of 5.8e-8, both relative).  The centre weight therefore matches the rounded weights, and what its own
+    // rounding leaves goes into the last axis' weights, largest first, none by
+    // more than about a unit in its last place.
+    // (FP64 sweeps use exact integers times entry 3 instead.)
+    auto centre = [](const T* x, const T* y, T* z) {
+        if (sizeof(T) == 8) return T(-490.0 * ((double)x[3] + (double)y[3] + (double)z[3]));
+        auto left = [&](double k) {
+            double s = k;
+            for (const T* w : {x, y, static_cast<const T*>(z)})
+                for (int i = 0; i < 3; ++i) s += 2.0 * (double)w[i];
+            return s;
+        };
+        const T k = T(-left(0.0));
+        for (int i = 0; i < 3; ++i) z[i] = T((double)z[i] - 0.5 * left((double)k));
+        return k;
+    };
+    c.kc19 = centre(c.s[0], c.s[1], c.s[2]);
+    c.kc[0] = centre(c.s[1], c.s[2], c.s4[0]);
+    c.kc[1] = centre(c.s[0], c.s[2], c.s4[1]);
+    c.kc[2] = centre(c.s[0], c.s[1], c.s4[2]);
+    for (int q = 0; q < 3; ++q)
+        for (int k = 0; k < 4; ++k)
+            c.m[q][k] = T(wm[k] * p.nu / (3.0 * 720.0 * h[pa[q]] * h[pb[q]]));
+    c.tn = T(2.0 * p.nu / 3.0);
     return c;
 }
 
@@ -468,13 +525,12 @@ int fused12_substeps(fd6_box* b) {
         b->err = "fused substeps: FP32 state and register only";
         return FD6_EUNSUPPORTED;
     } else {
-        const double dt = b->params.dt;
-        const RKCoef<TW> rk1 = make_rk<T, TW>(1, dt), rk2 = make_rk<T, TW>(2, dt);
+        const std::array<RKCoef<TW>, 3> rk = make_rk<T, TW>(b->params.dt);
         const Coef<T> c = make_coef<T>(b->params);
         int rc = timed(b, b->ev_kernel, [&]() -> int {
             HIPCHK(b, (launch_fused12<T, TW>(b->geom, fields_of<T>(b->state[b->cur]),
                                              fields_of<T>(b->state[b->cur ^ 1]),
-                                             fields_of<TW>(b->w), c, rk1, rk2, b->zchunk,
+                                             fields_of<TW>(b->w), c, rk[0], rk[1], b->zchunk,
                                              b->stream)));
             HIPCHK(b, launch_unpack_w<T>(b->geom, fields_of<TW>(b->w),
                                          fields_of<T>(b->state[b->cur]), b->stream));
@@ -491,7 +547,7 @@ int fused12_substeps(fd6_box* b) {
 // produces the diagnostics of the new state.
 template <typename T, typename TW>
 int one_step(fd6_box* b, double* red_out) {
-    const double dt = b->params.dt;
+    const std::array<RKCoef<TW>, 3> rk = make_rk<T, TW>(b->params.dt);
     int s0 = 0;
     if (fused_step(b)) {
         int rc = fused12_substeps<T, TW>(b);
@@ -499,7 +555,7 @@ int one_step(fd6_box* b, double* red_out) {
         s0 = 2;
     }
     for (int s = s0; s < 3; ++s) {
-        int rc = do_substep<T, TW>(b, s + 1, make_rk<T, TW>(s + 1, dt), red_out);
+        int rc = do_substep<T, TW>(b, s + 1, rk[s], red_out);
         if (rc) return rc;
     }
     return FD6_OK;
@@ -789,7 +845,8 @@ int upload_boxes(fd6_batch* b) {
         h[i].st[1] = fields_of<T>(b->st[1][i].data());
         h[i].w = fields_of<TW>(b->w[i].data());
         h[i].cf = make_coef<T>(b->params[i]);
-        for (int s = 1; s <= 3; ++s) h[i].rk[s - 1] = make_rk<T, TW>(s, b->params[i].dt);
+        const std::array<RKCoef<TW>, 3> rk = make_rk<T, TW>(b->params[i].dt);
+        for (int s = 0; s < 3; ++s) h[i].rk[s] = rk[s];
     }
     HIPCHK(b, hipMemcpyAsync(b->boxes_dev, h.data(), sizeof(BatchBox<T, TW>) * b->n,
                              hipMemcpyHostToDevice, b->stream));

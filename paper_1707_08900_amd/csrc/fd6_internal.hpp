@@ -31,10 +31,11 @@ struct Geom {
     int wpx;               // elements per w row
     long long wplane;      // wpx * ny
     long long wfelems;     // elements per w field (multiple of 256 B)
-    // Values per grid point in memory: 1 = one array per field; 4 = the four
-    // fields of a point adjacent (array of structures).  Element indices above
-    // count points; field q of point e is at f[q][e * vs], with f[q] = f[0] + q
-    // when vs = 4 (the same holds for w).
+    // Values per grid point in memory: 1 = one array per field, felems apart; 4 =
+    // the four fields of a point adjacent (array of structures), in the order
+    // ux, uy, uz, lnrho: the pairs the sweeps read together are then aligned in
+    // the registers a point is loaded to.  Element indices above count points;
+    // field q of point e is at f[q][e * vs] (the same holds for w).
     int vs = 1;
 };
 
@@ -84,13 +85,13 @@ struct Coef {
     T lp[3][4];
     double nu3;
     T n3;
-    // Scale factors for stencils written with their integer weights
-    // (second derivative 2, -27, 270, -490; mixed 270, -27, 2):
-    //   sg[a]  = nu / (180 h_a^2),  sg4[a] = (4/3) sg[a]
-    //   kxy[i] = -490 (s_ix + s_iy), s_ia = (a == i ? sg4 : sg)[a]
-    //   mu[p]  = nu / (3 * 720 h_a h_b), p = xy, xz, yz
-    //   kp     = -490 (sg[x] + sg[y])  (centre weight of nu (D2x + D2y))
-    T sg[3], sg4[3], kxy[3], mu[3], kp;
+    // Weights of the sweeps (w = 270, -27, 2 for k = 1, 2, 3):
+    //   s[a][k-1]  = nu w / (180 h_a^2),  s4 = (4/3) s   second derivatives
+    //                (entry 3 of s, s4 and m: the factor of w)
+    //   kc[i]      = their centre weight in L_i, all three axes; kc19 in nu lap u
+    //   m[p][k-1]  = nu w / (3 * 720 h_a h_b), p = xy, xz, yz
+    //   tn         = (2/3) nu
+    T s[3][4], s4[3][4], kc[3], kc19, m[3][4], tn;
 };
 
 // External force of the momentum equation, one Fourier mode of eq. (forcing)

@@ -15,7 +15,7 @@ template hipError_t launch_batch55_aos<float, float>(const BatchBox<float, float
 template int batch55_blocks_per_cu_aos<float, float>(int);
 
 bool substep55_aos_tile_ok(int tile) {
-    return tile > 0 && tile < kNumTiles && !kTiles[tile].ld;
+    return tile > 0 && tile < kNumTiles && !kTiles[tile].soa;
 }
 
 }  // namespace fd6

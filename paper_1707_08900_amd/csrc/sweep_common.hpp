@@ -87,24 +87,19 @@ __device__ __forceinline__ void bstore_point(const double (&v)[4], __amdgpu_buff
     __builtin_amdgcn_raw_buffer_store_b128(u32x4{p2[0], p2[1], p3[0], p3[1]}, r, off + 16u, 0, CP);
 }
 
-// LD = false: the next plane is loaded into registers and written to LDS by
-// the threads; LD = true: it is copied by the buffer unit straight into LDS
-// (64 consecutive dwords per wave instruction), with no staging registers.
-template <typename T, int TX, int TY, bool LD = false>
+// A TX x TY column tile, its halo and its LDS planes.
+template <typename T, int TX, int TY>
 struct SweepShape {
     static constexpr int NT = TX * TY;
     static constexpr int NW = NT / 64;              // wavefronts per workgroup
     static constexpr int W = TX + 2 * kR;           // LDS row length
     static constexpr int H = TY + 2 * kR;           // LDS rows
-    static constexpr int PLANE = W * H;             // LDS elements per field plane
+    static constexpr int PLANE = W * H;             // cells per plane
     static constexpr int HALO = 2 * kR * W + 2 * kR * TY;  // halo cells per plane
-    static constexpr int NH = (HALO + NT - 1) / NT; // halo loads per thread (LD = false)
-    static constexpr int DPE = (int)sizeof(T) / 4;  // dwords per element
-    static constexpr int NCH = (PLANE * DPE + 63) / 64;  // 64-dword chunks per plane (LD)
-    static constexpr int ND = (NCH + NW - 1) / NW;  // chunk copies per wave and field (LD)
-    // field stride in LDS elements: LD pads to whole chunks; otherwise cell
-    // PLANE is a dummy target for unused halo slots
-    static constexpr int FS = LD ? NCH * 64 / DPE : PLANE + 1;
+    static constexpr int NH = (HALO + NT - 1) / NT; // halo loads per thread
+    // cell stride of a field in LDS: cell PLANE is a dummy target for unused
+    // halo slots; even, so that pairs stay aligned beside an odd number of planes
+    static constexpr int FS = (PLANE + 2) / 2 * 2;
 };
 
 // Element index of the ghost corner (-3, -3) of interior plane p mod nz.
@@ -112,10 +107,6 @@ __device__ __forceinline__ long long plane_corner(const Geom& g, int p) {
     const int pz = p < 0 ? p + g.nz : (p >= g.nz ? p - g.nz : p);
     return g.origin + (long long)pz * g.plane - kR * g.px - kR;
 }
-
-// LDS pointer in the local address space (required by the LDS copy).
-template <typename T>
-using lds_t = __attribute__((address_space(3))) T*;
 
 // Workgroup-to-XCD remapping of tiles (FD6_XCD_REMAP=0 disables it).
 inline int xcd_remap() {
@@ -130,10 +121,9 @@ inline int xcd_remap() {
 // corner (-3, -3) of a plane, of the cells this thread loads (beyond the
 // plane's range the load returns 0; such cells are only read by threads whose
 // outputs are dropped), LDS slots of its halo loads, and its output offsets.
-template <typename T, int TX, int TY, bool LD = false>
+template <typename T, int TX, int TY>
 struct SweepCtx {
-    using Sh = SweepShape<T, TX, TY, LD>;
-    unsigned doff[Sh::ND];  // LD: byte offset of each lane's dword of the plane tile
+    using Sh = SweepShape<T, TX, TY>;
     unsigned goff_int;
     unsigned goff_h[Sh::NH];
     int loff_h[Sh::NH];   // LDS slot of each halo load (dummy cell if unused)
@@ -152,11 +142,10 @@ struct SweepCtx {
 // cell at any offset takes its periodic image and none is dropped (the
 // extended tile of the substep-1+2 fusion, whose cells may lie a whole tile
 // beyond the box).
-template <typename T, typename TW, int TX, int TY, bool LD, int VS = 1, bool WRAP_ALL = false>
-__device__ __forceinline__ void sweep_ctx_init(SweepCtx<T, TX, TY, LD>& X, const Geom& g, int x0,
+template <typename T, typename TW, int TX, int TY, int VS = 1, bool WRAP_ALL = false>
+__device__ __forceinline__ void sweep_ctx_init(SweepCtx<T, TX, TY>& X, const Geom& g, int x0,
                                                int y0) {
-    using Sh = SweepShape<T, TX, TY, LD>;
-    static_assert(VS == 1 || !LD, "the LDS-copy loader reads one array per field");
+    using Sh = SweepShape<T, TX, TY>;
     constexpr int PT = VS * (int)sizeof(T), PW = VS * (int)sizeof(TW);  // bytes per point
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
     X.plane_bytes = (unsigned)(g.plane * (long long)PT);
@@ -171,18 +160,6 @@ __device__ __forceinline__ void sweep_ctx_init(SweepCtx<T, TX, TY, LD>& X, const
         const int iy = gy < 0 ? gy + g.ny : (gy >= g.ny ? gy - g.ny : gy);
         return (unsigned)(((iy + kR) * g.px + (ix + kR)) * PT);
     };
-    if constexpr (LD) {
-        // dword d = 64 j + lane of the padded plane tile, j = wave + js NW
-        const int lane = threadIdx.x & 63, wv = threadIdx.x / 64;
-#pragma unroll
-        for (int js = 0; js < Sh::ND; ++js) {
-            const int d = 64 * (wv + js * Sh::NW) + lane;
-            const int e = d / Sh::DPE, half = d % Sh::DPE;
-            const int r = e / Sh::W, c = e - (e / Sh::W) * Sh::W;
-            const unsigned o = e < Sh::PLANE ? wrapped_off(x0 - kR + c, y0 - kR + r) : kDropOffset;
-            X.doff[js] = o == kDropOffset ? kDropOffset : o + 4u * (unsigned)half;
-        }
-    }
     X.goff_int = wrapped_off(x0 + tx, y0 + ty);
 #pragma unroll
     for (int h = 0; h < Sh::NH; ++h) {
@@ -315,8 +292,7 @@ __device__ __forceinline__ TileXY sweep_tile_of(const Geom& g, int TX, int TY,
 // FP64 diagnostics of one point of the new state (the quantities of the
 // standalone reduction): per thread, red = {sum rho, sum rho |u|^2, sum
 // lnrho, max |u|^2} and bad = points holding a non-finite value.  The caller
-// skips points that are not outputs (branches, not selects, so the skipped
-// steps and lanes cost no FP64 instructions).  The kinetic energy's factor
+// leaves out points that are not outputs.  The kinetic energy's factor
 // 1/2 is applied once per workgroup (exact).  Non-finite values are found by
 // class checks of the stored values; the mass and kinetic-energy terms of
 // such a point are meaningless and the final combination reports them as
@@ -327,7 +303,7 @@ __device__ __forceinline__ void red_point(double red[4], int& bad, T lr, T ux, T
                         __builtin_isfinite(uy) && __builtin_isfinite(uz);
     bad += finite ? 0 : 1;
     const double l = (double)lr, a = (double)ux, b = (double)uy, c = (double)uz;
-    const double rho = exp_fp64(l);
+    const double rho = exp_fp64<sizeof(T) == 8>(l);  // FP64 sweeps: no vector registers to spare
     const double u2 = a * a + b * b + c * c;
     red[0] += rho;
     red[1] += rho * u2;
@@ -373,13 +349,15 @@ __device__ __forceinline__ void red_store_n(const double red[4], int bad, double
 
 // Kernel shapes of the z-sweep substeps.  Index 0 is the direct kernel (one
 // thread per point, taps from the ghost zone); the others are (TX, TY) column
-// tiles.  pd: how many planes ahead the register loader fetches (1, 2 or 4;
-// 2 and 4 also load the RK3 register one step early); ld: the LDS-copy loader
-// instead.
+// tiles.  pd: how many planes ahead the loader fetches (1, 2 or 4; 2 and 4 also
+// load the update's other operand one step early).  FP64 states always fetch one:
+// a second set of planes fills the registers (512^3, ms per step: 7.33 with one
+// plane, 7.30 with two; with diagnostics 7.50 and 7.96, which spills).  Shape 9 is
+// shape 2 for boxes with one array per field.
 struct TileCfg {
     int tx, ty, pd;
-    bool ld;
-    bool nt;  // new state and RK register streamed past the caches
+    bool soa;  // one array per field only
+    bool nt;   // new state and RK register streamed past the caches
 };
 constexpr TileCfg kTiles[] = {
     {0, 0, 1, false, false},  {64, 4, 1, false, true},  {64, 8, 1, false, true},
@@ -387,6 +365,8 @@ constexpr TileCfg kTiles[] = {
     {64, 8, 2, false, true},  {128, 4, 2, false, true}, {32, 8, 2, false, true},
     {64, 8, 1, true, true},   {64, 8, 4, false, true},  {64, 8, 1, false, false},
     {64, 8, 2, false, false}, {32, 8, 2, false, false}};
+template <typename T, int PD>
+constexpr int kPd = sizeof(T) == 8 ? 1 : PD;
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 // Calls f(std::integral_constant<int, tile>) so that f can use kTiles[tile]

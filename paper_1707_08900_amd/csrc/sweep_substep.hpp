@@ -9,22 +9,29 @@
 //  * One workgroup owns a TX x TY column tile of the xy-plane and sweeps a
 //    chunk of z.  Each step loads one new xy-plane (tile + 3-cell halo) of the
 //    four fields from HBM into LDS (coalesced x-rows, double buffered, one
-//    barrier per plane), prefetching the next plane into registers.
-//  * From that plane every thread forms, for its own column, the x and y
-//    first derivatives of all fields and the xy part of the linear viscous
-//    term (second derivatives along x and y, xy mixed derivative).
+//    barrier per plane), prefetching the next plane into registers.  LDS holds
+//    the fields in pairs (PlaneBuf).
+//  * From that plane every thread forms, for its own column, the x and y first
+//    derivatives of all fields and all of the right-hand side that needs no z
+//    derivative, into the pending sum of that plane's output.
 //  * z derivatives come from a register queue holding the thread's column
 //    over 7 planes.
 //  * The xz and yz mixed derivatives are built by scatter: the bidiagonal
 //    stencil at output plane z is sum_k c_k [A_k(z+k) - A_k(z-k)], where
 //    A_k(p) = f(x+k, p) - f(x-k, p) is the same x (or y) difference the plane
-//    step already forms, so each plane adds +-c_k A_k into pending
-//    accumulators of the output planes p -+ k (a register ring of 8 planes).
-//  * Output plane z is finished 3 planes behind the load front: the right-hand
-//    side is assembled in registers and the RK3 update is written out.
+//    step already forms, so each plane adds +-c_k A_k into pending sums of the
+//    output planes p -+ k (a register ring of 8 planes).
+//  * Output plane z is finished 3 planes behind the load front: the terms with z
+//    derivatives join, and the RK3 update is written out.
 //  * The z loop is unrolled by 8 so every ring index is a compile-time
 //    register; the workgroup-to-tile map gives each XCD a near-square block
 //    of neighbouring tiles, so most halo cells are served from its L2.
+//  * What bounds it, at 512^3 in the array-of-structures layout (64 x 8 tiles, two
+//    waves per SIMD): FP32 HBM, 4.7 TB/s of its actual traffic where a 1 GiB copy
+//    runs at 5.1 (S1 1.20-1.27 ms, S2 and S3 1.31-1.38, S3 with diagnostics
+//    1.48-1.55; VALU busy 67-70%, 227 vector instructions per point against 255
+//    before, LDS 51%).  FP64 the same since two waves fit a SIMD: 7.33 ms per step
+//    against 10.2 with one wave (5.0 TB/s).
 //  * Template switches: VS = 4 reads and writes the array-of-structures
 //    layout (one 16-byte access per cell and field set); NT streams the new
 //    state and the RK3 register past the caches; FRC adds the external
@@ -189,16 +196,70 @@ __global__ __launch_bounds__(256) void substep55_direct(Geom g, Fields4<T> in, F
 // z-sweep kernel
 // ---------------------------------------------------------------------------
 
+// Values of a plane that wait for its output, 3 planes later: of the right-hand
+// side everything that holds no z derivative is formed with the plane itself and
+// added to the pending L; the terms with one need nu d_x lnrho, nu d_y lnrho,
+// d_x uz, d_y uz, d_x ux + d_y uy, and lnrho's in-plane advection.
+constexpr int kInPlane = 6;
+// They wait in per-thread LDS slots (a ring of 3 planes) in FP64, where that
+// keeps a thread within 256 registers and so two waves on a SIMD; in registers
+// in FP32, and where the slots do not fit beside NF field planes.
+constexpr int kLdsBytes = 160 * 1024;
+template <typename T, int TX, int TY, int NF>
+constexpr bool kInPlaneLds =
+    sizeof(T) == 8 && sizeof(T) * (2 * NF * SweepShape<T, TX, TY>::FS + 3 * kInPlane * TX * TY) <=
+                          kLdsBytes - 1024;
+// LDS elements of a workgroup's in-plane values
+template <typename T, int TX, int TY, int NF>
+constexpr int kInPlaneElems = kInPlaneLds<T, TX, TY, NF> ? 3 * kInPlane * TX * TY : 2;
+// LDS elements of the diagnostics' per-thread accumulators, which join the
+// in-plane values there.
+template <typename T, int TX, int TY, int NF>
+constexpr int kRedElems =
+    kInPlaneLds<T, TX, TY, NF> &&
+            sizeof(T) * (2 * NF * SweepShape<T, TX, TY>::FS + (3 * kInPlane + 4) * TX * TY) <=
+                kLdsBytes - 1024
+        ? 4 * TX * TY
+        : 0;
+// Waves per SIMD the register budget is set for.
+constexpr int kMinWaves = 2;
+
+// Terms w[k-1] s of a stencil whose weights w are 270, -27 and 2 times w[3]
+// (second and mixed derivatives), k = 1, 2, 3 in turn, added to acc.  FP32 takes
+// the three weights from scalar registers.  In FP64 all weights of the sweep
+// would fill 88 of the 102 (and spilled 80 into vector lanes: 51 lane moves per
+// point and plane), so the integers are factored out there: the terms gather in
+// part, and end() adds it with the factor, for one instruction more.
+template <typename T>
+struct Weighted {
+    T part;
+    template <int K>
+    __device__ __forceinline__ void add(const T* w, T s, T& acc) {
+        if constexpr (sizeof(T) == 8) {
+            constexpr T c = K == 1 ? T(270) : (K == 2 ? T(-27) : T(2));
+            part = K == 1 ? c * s : c * s + part;
+        } else {
+            acc = w[K - 1] * s + acc;
+        }
+    }
+    __device__ __forceinline__ void end(const T* w, T& acc) {
+        if constexpr (sizeof(T) == 8) acc = w[3] * part + acc;
+    }
+};
+
 template <typename T, typename TW, int NH>
 struct SweepRegs {
     using Reg = std::conditional_t<kRegInMemory<T, TW>, TW, T>;
+    // fields in the order ux, uy, uz, lnrho, that of a point's values in the array
+    // of structures
     T q[4][8];       // raw column values of the 4 fields, ring over planes
-    T L[3][8];       // pending linear viscous term of the 3 momentum components
-    T dd[4][8];      // x/y first derivatives of the 4 fields, ring of 4 planes
+    T L[3][8];       // pending momentum right-hand sides, ring over output planes
+    T dd[4][kInPlane];  // what an output still needs from its own plane, ring of 4 planes
     T pf[4][4];      // prefetched interior values of the next plane(s)
     T ph[4][NH][4];  // prefetched halo values of the next plane(s)
     // 19-point method: the same of the divergence field
     T qd[8], pfd[4], phd[4][NH];
+    int slot;        // in-plane values in LDS: the plane's slot
     Reg wq[2][4];    // previous substep's input, or the RK3 register in memory, at the
                      // output point (PD >= 2: loaded a step early)
     double red[4];   // fused diagnostics of the thread's column (RED): sum rho,
@@ -215,12 +276,15 @@ struct SweepRegs {
 // pipeline (stores share the load counter on this architecture).
 
 // Loads plane `corner` of the four fields (this thread's cells) into
-// register set RS; bytes = 0 loads nothing.
+// register set RS; bytes = 0 loads nothing.  One array per field: the arrays of a
+// state set follow one another, felems apart, so one pointer serves all (four
+// would cost scalar registers the weights need).
 template <int RS, int VS, bool P19, typename T, typename TW, int TX, int TY, int NH>
 __device__ __forceinline__ void sweep_prefetch(SweepRegs<T, TW, NH>& R,
                                                const SweepCtx<T, TX, TY>& X,
-                                               const Fields4<T>& in, const T* dv,
-                                               long long corner, unsigned bytes) {
+                                               const Fields4<T>& in, long long felems,
+                                               const T* dv, long long corner,
+                                               unsigned bytes) {
     if constexpr (P19) {
         const __amdgpu_buffer_rsrc_t rs = plane_rsrc(dv + corner, bytes);
         R.pfd[RS] = bload((T*)nullptr, rs, X.goff_int);
@@ -228,14 +292,14 @@ __device__ __forceinline__ void sweep_prefetch(SweepRegs<T, TW, NH>& R,
         for (int h = 0; h < NH; ++h) R.phd[RS][h] = bload((T*)nullptr, rs, X.goff_h[h]);
     }
     if constexpr (VS == 4) {
-        const __amdgpu_buffer_rsrc_t rs = plane_rsrc(in.f[0] + 4 * corner, bytes);
+        const __amdgpu_buffer_rsrc_t rs = plane_rsrc(in.f[1] + 4 * corner, bytes);
         bload_point(R.pf[RS], rs, X.goff_int);
 #pragma unroll
         for (int h = 0; h < NH; ++h) bload_point(R.ph[RS][h], rs, X.goff_h[h]);
     } else {
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
-            const __amdgpu_buffer_rsrc_t rs = plane_rsrc(in.f[f] + corner, bytes);
+            const __amdgpu_buffer_rsrc_t rs = plane_rsrc(in.f[0] + (corner + ((f + 1) & 3) * felems), bytes);
             R.pf[RS][f] = bload((T*)nullptr, rs, X.goff_int);
 #pragma unroll
             for (int h = 0; h < NH; ++h) R.ph[RS][h][f] = bload((T*)nullptr, rs, X.goff_h[h]);
@@ -259,9 +323,9 @@ __device__ __forceinline__ void load_prev(SweepRegs<T, TW, NH>& R, const Ctx& X,
     const unsigned lane = REG ? X.lane_w : X.lane_o;
     auto base = [&](int f) -> const P* {
         if constexpr (REG)
-            return w.f[f];
+            return VS == 4 ? w.f[1] : w.f[0] + ((f + 1) & 3) * g.wfelems;
         else
-            return out.f[f];
+            return VS == 4 ? out.f[1] : out.f[0] + ((f + 1) & 3) * g.felems;
     };
     if constexpr (VS == 4) {
         bload_point<CP>(R.wq[RS], plane_rsrc(base(0) + 4 * at, bytes), lane);
@@ -272,178 +336,261 @@ __device__ __forceinline__ void load_prev(SweepRegs<T, TW, NH>& R, const Ctx& X,
     }
 }
 
-// LD: copy plane `corner` of the four fields (19-point: and of the divergence)
-// into one LDS buffer.  Chunk j
-// (64 dwords) is issued by wave j % NW; its lanes fetch the dwords whose byte
-// offsets were precomputed in doff (periodic images included).
-template <bool P19, typename T, int TX, int TY>
-__device__ __forceinline__ void sweep_dma(const SweepCtx<T, TX, TY, true>& X,
-                                          const Fields4<T>& in, const T* dv, long long corner,
-                                          lds_t<T> buf, unsigned bytes) {
-    using Sh = SweepShape<T, TX, TY, true>;
-    const int wv = threadIdx.x / 64;
-#pragma unroll
-    for (int f = 0; f < (P19 ? 5 : 4); ++f) {
-        const __amdgpu_buffer_rsrc_t rs = plane_rsrc((f < 4 ? in.f[f & 3] : dv) + corner, bytes);
-#pragma unroll
-        for (int js = 0; js < Sh::ND; ++js) {
-            const int j = wv + js * Sh::NW;
-            if (j < Sh::NCH) {
-                lds_t<T> dst = buf + f * Sh::FS + j * (64 / Sh::DPE);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rs, (__attribute__((address_space(3))) void*)dst, 4, X.doff[js], 0, 0, 0);
-            }
-        }
-    }
+// Makes the compiler form a value where it stands (no instruction).
+template <typename T>
+__device__ __forceinline__ void keep_here(T& x) {
+    asm volatile("" : "+v"(x));
 }
 
+// A plane buffer in LDS holds the cells of the tile and its halo as pairs, first
+// (ux, uy), then (uz, lnrho), then, for the 19-point method, the divergence.  A
+// tap brings both fields of a pair in one access, and every tap of a thread is
+// at a constant offset from one address.  (One plane per field needed a register
+// for nearly every row and field: two-address reads reach only 255 elements.)
+template <typename T, int FS>
+struct PlaneBuf {
+    using T2 = T __attribute__((ext_vector_type(2)));
+    T* b;
+    __device__ __forceinline__ T2* u() const { return reinterpret_cast<T2*>(b); }
+    __device__ __forceinline__ T2* v() const { return reinterpret_cast<T2*>(b) + FS; }
+    __device__ __forceinline__ T* d() const { return b + 4 * FS; }
+    __device__ __forceinline__ void put(int cell, const T (&x)[4]) const {
+        u()[cell] = T2{x[0], x[1]};
+        v()[cell] = T2{x[2], x[3]};
+    }
+};
+
+// One step of the sweep: plane p = zb - 3 + t comes in, output plane p - 3 is
+// finished.  PH = t mod 8 (ring positions), ST: the step's number where it is one
+// of the first 6 of a chunk, which fill the rings and have no output; 6 later.
+// A plane below the chunk (ST < 3) only fills the z queues and contributes the
+// xz / yz terms of the outputs it reaches, and planes 0 .. 2 (ST 3 .. 5) lack
+// the output: of the 6 steps' arithmetic 2.3 are left, which matters where
+// chunks are short (small boxes, ensembles).
+//
 // TB selects the two stages of the substep-1+2 fusion (fused12_tile): 0 is
 // the plain sweep; 1 is substep 1 over the extended region, whose new state
 // goes to the LDS plane buffer tb_u (layout of the inner tile's sweep) and
 // whose input, for the inner columns, to the LDS ring tb_w; 2 is substep 2 of
 // the inner tile, which takes its plane from tb_u (passed as lds, loaded by
 // stage 1) and the substep-1 input from tb_w, leaves the substep-1 state in w,
-// and starts output planes 2 * kR steps later.
-template <int PH, int S, int PD, bool LD, bool NT, int VS, bool P19, bool RED, bool FRC,
-          int TB = 0, bool DDL = false, typename T, typename TW, int TX, int TY, int NH>
-__device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepRegs<T, TW, NH>& R,
-                                           const SweepCtx<T, TX, TY, LD>& X, T* lds,
-                                           lds_t<T> lds3, const Geom& g, const Fields4<T>& in,
-                                           const Fields4<T>& out, const Fields4<TW>& w,
-                                           const T* dv,
-                                           const Coef<T>& cf, const RKCoef<TW>& rk,
-                                           const T* ftab, T* tb_u = nullptr,
-                                           TW* tb_w = nullptr, T* ddl = nullptr) {
-    using Sh = SweepShape<T, TX, TY, LD>;
-    constexpr int W = Sh::W;
-    static_assert(TB == 0 || (!LD && !P19 && !RED && !FRC), "fusion: plain register sweep only");
-    static_assert(!DDL || TB == 0, "LDS derivative slots: plain sweep only");
-    // DDL: the x / y first derivatives of a plane wait for their output in
-    // this thread's LDS slots instead of registers (slot, field pair, thread)
-    using T2 = T __attribute__((ext_vector_type(2)));
-    T2* const dd2 = reinterpret_cast<T2*>(ddl);
-    // PIPE: the pinned order of phase (C) below; it pays where one wave runs per
-    // SIMD and the LDS slots left registers for the copies (FP64, the same
-    // kernels as DDL)
-    constexpr bool PIPE = DDL;
-    const int t = t0 + PH;
+// and starts output planes 2 * kR steps later.  Both run every step in full.
+template <int PH, int ST, int S, int PD, bool NT, int VS, bool P19, bool RED, bool FRC,
+          int TB = 0, typename T, typename TW, int TX, int TY, int NH>
+__device__ __forceinline__ void sweep_step(int t, int nplanes, int zb, SweepRegs<T, TW, NH>& R,
+                                           const SweepCtx<T, TX, TY>& X, T* lds, const Geom& g,
+                                           const Fields4<T>& in, const Fields4<T>& out,
+                                           const Fields4<TW>& w, const T* dv, const Coef<T>& cf,
+                                           const RKCoef<TW>& rk, const T* ftab, T* ipl,
+                                           T* tb_u = nullptr, TW* tb_w = nullptr) {
+    using Sh = SweepShape<T, TX, TY>;
+    constexpr int W = Sh::W, NF = P19 ? 5 : 4;
+    constexpr bool IPL = TB == 0 && kInPlaneLds<T, TX, TY, NF>;
+    static_assert(TB == 0 || (!P19 && !RED && !FRC && ST == 6), "fusion: plain sweep only");
     if (t >= nplanes) return;
     const int p = zb - kR + t;  // plane loaded in this step
     const int o = p - kR;       // output plane finished in this step
-    const bool outstep = t >= (TB == 2 ? 4 : 2) * kR;
+    const bool outstep = TB == 0 || t >= (TB == 2 ? 4 : 2) * kR;
 
-    constexpr int NF = P19 ? 5 : 4;  // field planes in LDS
-    T* buf = lds + (PH & 1) * NF * Sh::FS;
+    const PlaneBuf<T, Sh::FS> buf{lds + (PH & 1) * NF * Sh::FS};
     const int ci = (threadIdx.x / TX + kR) * W + (threadIdx.x % TX + kR);
     // register sets: plane p sits in set RS (PD sets, PD divides the unroll
     // of 8); the previous input of output o in set WS
     static_assert(PD == 1 || PD == 2 || PD == 4, "prefetch depth");
     constexpr int RS = PH % PD;
     constexpr int WS = PD >= 2 ? (PH & 1) : 0;
-    if constexpr (TB == 2) {
-        // plane p was written to LDS by stage 1 of this step (barrier between)
-    } else if constexpr (!LD) {
+    if constexpr (TB != 2) {  // (stage 2: plane p was written to LDS by stage 1)
         // previous input of an output point, issued early: PD = 1 loads the one
         // finished in this step, PD >= 2 the one finished in the next step
         if constexpr (S >= 2) {
-            if constexpr (PD >= 2) {
-                const bool next_out = t + 1 >= 2 * kR && t + 1 < nplanes;
-                load_prev<(PH + 1) & 1, NT, VS>(R, X, out, w, g, o + 1, next_out);
-            } else {
+            if constexpr (PD >= 2 && ST >= 5)
+                load_prev<(PH + 1) & 1, NT, VS>(R, X, out, w, g, o + 1, t + 1 < nplanes);
+            else if constexpr (PD < 2 && ST == 6)
                 load_prev<0, NT, VS>(R, X, out, w, g, o, outstep);
-            }
         }
-        // prefetched plane p -> LDS buffer (PH & 1)
+        // prefetched plane p -> LDS buffer (PH & 1), and the top of the z queues
+        buf.put(ci, R.pf[RS]);
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-            buf[f * Sh::FS + ci] = R.pf[RS][f];
-#pragma unroll
-            for (int h = 0; h < NH; ++h) buf[f * Sh::FS + X.loff_h[h]] = R.ph[RS][h][f];
-        }
+        for (int h = 0; h < NH; ++h) buf.put(X.loff_h[h], R.ph[RS][h]);
         if constexpr (P19) {
-            buf[4 * Sh::FS + ci] = R.pfd[RS];
+            buf.d()[ci] = R.pfd[RS];
 #pragma unroll
-            for (int h = 0; h < NH; ++h) buf[4 * Sh::FS + X.loff_h[h]] = R.phd[RS][h];
+            for (int h = 0; h < NH; ++h) buf.d()[X.loff_h[h]] = R.phd[RS][h];
+            R.qd[sl8(PH)] = R.pfd[RS];
         }
         // plane p + PD -> the register set just emptied
-        sweep_prefetch<RS, VS, P19>(R, X, in, dv, plane_corner(g, p + PD),
+        sweep_prefetch<RS, VS, P19>(R, X, in, g.felems, dv, plane_corner(g, p + PD),
                                     t + PD < nplanes ? X.plane_bytes : 0u);
         __syncthreads();
-    } else {
-        // this wave's copies of plane p are complete before the barrier; after
-        // it the other buffer (read in the previous step by every wave) takes
-        // plane p + 1
-        __syncthreads();
-        sweep_dma<P19, T, TX, TY>(X, in, dv, plane_corner(g, p + 1),
-                                  lds3 + ((PH + 1) & 1) * NF * Sh::FS,
-                                  t + 1 < nplanes ? X.plane_bytes : 0u);
-        if constexpr (S >= 2) load_prev<0, NT, VS>(R, X, out, w, g, o, outstep);
     }
-
-    // ---- plane quantities of plane p for this thread's column ----
-    // Stencils use their integer weights; grid spacing and viscosity enter
-    // through per-axis scale factors (see Coef), which keeps the runtime
-    // constants few enough to stay in scalar registers.
-    // all taps as non-negative constant offsets from one window base
-    const T* win = buf + (ci - kR * W - kR);
-    constexpr int C0 = kR * W + kR;  // centre of the window
-    const T* B0 = win + C0;
-    const T* B1 = win + Sh::FS + C0;
-    const T* B2 = win + 2 * Sh::FS + C0;
-    const T* B3 = win + 3 * Sh::FS + C0;
-    [[maybe_unused]] const T* B4 = win + (NF - 1) * Sh::FS + C0;  // 19-point: the divergence
-    constexpr int DS = PH & 3;  // first-derivative slot of plane p
-    constexpr T w2[3] = {T(270), T(-27), T(2)};
-
-    // (A) what output p - 3 still needs from plane p: the centre values (top
-    // of the z queues) and the k = 3 terms of its xz / yz stencils.  The
-    // first contribution to output p + 3 (from the same differences) assigns.
-    // The 19-point form has no mixed terms.
+    using T2 = typename PlaneBuf<T, Sh::FS>::T2;
+    const T2* const U = buf.u() + ci;
+    const T2* const V = buf.v() + ci;
     {
-        R.q[0][sl8(PH)] = B0[0];
-        R.q[1][sl8(PH)] = B1[0];
-        R.q[2][sl8(PH)] = B2[0];
-        R.q[3][sl8(PH)] = B3[0];
-        if constexpr (P19) R.qd[sl8(PH)] = B4[0];
+        R.q[0][sl8(PH)] = U[0].x;
+        R.q[1][sl8(PH)] = U[0].y;
+        R.q[2][sl8(PH)] = V[0].x;
+        R.q[3][sl8(PH)] = V[0].y;
     }
-    if constexpr (!P19) {
-        const T zs3[3] = {cf.mu[1] * (B3[3] - B3[-3]),                 // (1/3) Dxz uz
-                          cf.mu[2] * (B3[3 * W] - B3[-3 * W]),         // (1/3) Dyz uz
-                          cf.mu[1] * (B1[3] - B1[-3]) +                // (1/3) Dxz ux
-                              cf.mu[2] * (B2[3 * W] - B2[-3 * W])};    // + (1/3) Dyz uy
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            R.L[i][sl8(PH - 3)] += T(2) * zs3[i];
-            R.L[i][sl8(PH + 3)] = T(-2) * zs3[i];
+    constexpr int P = sl8(PH);
+    constexpr int DS = PH & 3;  // in-plane slot of plane p
+    T ip[kInPlane];             // in-plane values of plane p
+    // in-plane values in LDS: this thread's pairs of slot t mod 3
+    [[maybe_unused]] T2* const ip2 =
+        reinterpret_cast<T2*>(ipl) + R.slot * (kInPlane / 2 * Sh::NT) + threadIdx.x;
+
+    // (C) what plane p contributes: the x / y first derivatives of the four
+    // fields, the in-plane part of the right-hand side of output p, and the xz /
+    // yz terms of outputs p -+ k.  The bidiagonal xz / yz stencil at output z is
+    // sum_k c_k [A_k(z + k) - A_k(z - k)], with A_k the x or y difference at
+    // distance k, so plane p adds +c_k A_k to the pending output p - k and
+    // -c_k A_k to p + k; the first contribution to output p + 3 assigns.  (The
+    // 19-point form has no mixed terms.)
+    auto scatter = [&](auto k, int i, const T* m, T a, bool first) {
+        constexpr int K = decltype(k)::value;
+        constexpr int N = sl8(PH + K), Q = sl8(PH - K);
+        if constexpr (ST + K >= 3) {
+            if (K == 3 && first)
+                R.L[i][N] = -m[K - 1] * a;
+            else
+                R.L[i][N] = -m[K - 1] * a + R.L[i][N];
         }
-    }
-
-    // PIPE: register copies of the fields' x / y windows (the cross and the
-    // diagonals through the column), each filled from LDS one field ahead of
-    // its arithmetic, with the order pinned, so that the LDS latency overlaps
-    // the arithmetic before it (the output plane's for ln rho).  The
-    // operations and their operands are those of the plain order.
-    [[maybe_unused]] T wv[PIPE ? 4 : 1][PIPE ? 7 * W : 1];
-    [[maybe_unused]] auto fill = [&](T* wf, const T* Bf) {
-#pragma unroll
-        for (int dy = -kR; dy <= kR; ++dy)
-#pragma unroll
-            for (int dx = -kR; dx <= kR; ++dx)
-                if (dy == 0 || dx == 0 || dy == dx || dy == -dx)
-                    wf[C0 + dy * W + dx] = Bf[dy * W + dx];
+        if constexpr (ST - K >= 3) R.L[i][Q] = m[K - 1] * a + R.L[i][Q];
     };
-    if constexpr (PIPE) {
-        fill(wv[0], B0);
-        __builtin_amdgcn_sched_barrier(0);
+    if constexpr (ST >= 3) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            R.L[i][P] = P19 ? cf.kc19 * R.q[i][P] : cf.kc[i] * R.q[i][P] + R.L[i][P];
+        const T u0 = R.q[0][P], u1 = R.q[1][P];
+        T g0, g1, J20, J21;
+        {  // lnrho and uz
+            Weighted<T> zx, zy;
+            auto tap = [&](auto k) {
+                constexpr int K = decltype(k)::value;
+                const T2 xp = V[K], xm = V[-K], yp = V[K * W], ym = V[-K * W];
+                const T ax = xp.x - xm.x, ay = yp.x - ym.x;
+                const T bx = xp.y - xm.y, by = yp.y - ym.y;
+                g0 = K == 1 ? cf.d1[0][0] * bx : cf.d1[0][K - 1] * bx + g0;
+                g1 = K == 1 ? cf.d1[1][0] * by : cf.d1[1][K - 1] * by + g1;
+                J20 = K == 1 ? cf.d1[0][0] * ax : cf.d1[0][K - 1] * ax + J20;
+                J21 = K == 1 ? cf.d1[1][0] * ay : cf.d1[1][K - 1] * ay + J21;
+                zx.template add<K>(cf.s[0], xp.x + xm.x, R.L[2][P]);
+                zy.template add<K>(cf.s[1], yp.x + ym.x, R.L[2][P]);
+                if constexpr (!P19) {
+                    scatter(k, 0, cf.m[1], ax, true);  // (1/3) Dxz uz
+                    scatter(k, 1, cf.m[2], ay, true);  // (1/3) Dyz uz
+                }
+            };
+            tap(std::integral_constant<int, 1>{});
+            tap(std::integral_constant<int, 2>{});
+            tap(std::integral_constant<int, 3>{});
+            zx.end(cf.s[0], R.L[2][P]);
+            zy.end(cf.s[1], R.L[2][P]);
+        }
+        const T h0 = cf.nu * g0, h1 = cf.nu * g1;
+        const T v0 = cf.nu * g0 - u0, v1 = cf.nu * g1 - u1;
+        R.L[2][P] = J20 * v0 + R.L[2][P];
+        R.L[2][P] = J21 * v1 + R.L[2][P];
+        T J00, J01, J10, J11;
+        {  // ux and uy
+            Weighted<T> x0, y0, x1, y1, m0, m1;
+            constexpr bool F = !P19;
+            const T* sx0 = F ? cf.s4[0] : cf.s[0];
+            const T* sy1 = F ? cf.s4[1] : cf.s[1];
+            auto tap = [&](auto k) {
+                constexpr int K = decltype(k)::value;
+                const T2 xp = U[K], xm = U[-K], yp = U[K * W], ym = U[-K * W];
+                const T ax = xp.x - xm.x, ay = yp.x - ym.x;
+                const T bx = xp.y - xm.y, by = yp.y - ym.y;
+                J00 = K == 1 ? cf.d1[0][0] * ax : cf.d1[0][K - 1] * ax + J00;
+                J01 = K == 1 ? cf.d1[1][0] * ay : cf.d1[1][K - 1] * ay + J01;
+                J10 = K == 1 ? cf.d1[0][0] * bx : cf.d1[0][K - 1] * bx + J10;
+                J11 = K == 1 ? cf.d1[1][0] * by : cf.d1[1][K - 1] * by + J11;
+                x0.template add<K>(sx0, xp.x + xm.x, R.L[0][P]);
+                y0.template add<K>(cf.s[1], yp.x + ym.x, R.L[0][P]);
+                x1.template add<K>(cf.s[0], xp.y + xm.y, R.L[1][P]);
+                y1.template add<K>(sy1, yp.y + ym.y, R.L[1][P]);
+                if constexpr (!P19) {
+                    const T2 pp = U[K * W + K], pm = U[K * W - K];
+                    const T2 mp = U[-K * W + K], mm = U[-K * W - K];
+                    // (1/3) Dxy ux into uy's equation and the other way round
+                    m1.template add<K>(cf.m[0], (pp.x - pm.x) + (mm.x - mp.x), R.L[1][P]);
+                    m0.template add<K>(cf.m[0], (pp.y - pm.y) + (mm.y - mp.y), R.L[0][P]);
+                    scatter(k, 2, cf.m[1], ax, true);   // (1/3) Dxz ux
+                    scatter(k, 2, cf.m[2], by, false);  // (1/3) Dyz uy
+                }
+            };
+            tap(std::integral_constant<int, 1>{});
+            tap(std::integral_constant<int, 2>{});
+            tap(std::integral_constant<int, 3>{});
+            x0.end(sx0, R.L[0][P]);
+            y0.end(cf.s[1], R.L[0][P]);
+            x1.end(cf.s[0], R.L[1][P]);
+            y1.end(sy1, R.L[1][P]);
+            if constexpr (!P19) {
+                m1.end(cf.m[0], R.L[1][P]);
+                m0.end(cf.m[0], R.L[0][P]);
+            }
+        }
+        // the in-plane terms of the x and y momentum and of lnrho
+        const T D = J00 + J11;
+        const T e = -cf.tn * D - cf.cs2;
+        T l = R.L[0][P];
+        l = J00 * (v0 + h0) + l;
+        l = J01 * v1 + l;
+        l = J10 * h1 + l;
+        l = e * g0 + l;
+        R.L[0][P] = l;
+        l = R.L[1][P];
+        l = J11 * (v1 + h1) + l;
+        l = J10 * v0 + l;
+        l = J01 * h0 + l;
+        l = e * g1 + l;
+        R.L[1][P] = l;
+        ip[0] = h0, ip[1] = h1, ip[2] = J20, ip[3] = J21, ip[4] = D;
+        ip[5] = u0 * g0 + u1 * g1;
+        if constexpr (P19) {  // (nu/3) d_x and d_y of div u
+            const T* const F = buf.d() + ci;
+            const T dx = cf.d1[0][0] * (F[1] - F[-1]) + cf.d1[0][1] * (F[2] - F[-2]) +
+                         cf.d1[0][2] * (F[3] - F[-3]);
+            const T dy = cf.d1[1][0] * (F[W] - F[-W]) + cf.d1[1][1] * (F[2 * W] - F[-2 * W]) +
+                         cf.d1[1][2] * (F[3 * W] - F[-3 * W]);
+            R.L[0][P] = cf.n3 * dx + R.L[0][P];
+            R.L[1][P] = cf.n3 * dy + R.L[1][P];
+        }
+    } else if constexpr (!P19) {
+        auto tap = [&](auto k) {
+                constexpr int K = decltype(k)::value;
+            if constexpr (ST + K >= 3) {
+                scatter(k, 0, cf.m[1], V[K].x - V[-K].x, true);
+                scatter(k, 1, cf.m[2], V[K * W].x - V[-K * W].x, true);
+                scatter(k, 2, cf.m[1], U[K].x - U[-K].x, true);
+                scatter(k, 2, cf.m[2], U[K * W].y - U[-K * W].y, false);
+            }
+        };
+        tap(std::integral_constant<int, 1>{});
+        tap(std::integral_constant<int, 2>{});
+        tap(std::integral_constant<int, 3>{});
     }
 
-    // (B) finish output plane o = p - 3 before the rest of plane p is formed,
-    // so the two working sets do not overlap in registers.  In the first 6
-    // steps of a chunk there is no output plane yet: the arithmetic runs on
-    // the zero-initialised rings and the stores are dropped.
-    {
+    // (B) finish output plane o = p - 3: the terms with z derivatives, from the
+    // queues (plane p is their top) and the in-plane values of plane o, which
+    // plane p's then replace.
+    if constexpr (ST == 6) {
         const unsigned ob = outstep ? X.plane_bytes : 0u;
         const unsigned wb = outstep ? X.wplane_bytes : 0u;
+        constexpr int Q = sl8(PH - 3);
+        T io[kInPlane];  // of plane o
+#pragma unroll
+        for (int i = 0; i < kInPlane; i += 2) {
+            T2 v;
+            if constexpr (IPL)
+                v = ip2[(i / 2) * Sh::NT];
+            else
+                v = T2{R.dd[(PH + 1) & 3][i], R.dd[(PH + 1) & 3][i + 1]};
+            io[i] = v.x;
+            io[i + 1] = v.y;
+        }
         T dz[4];
 #pragma unroll
         for (int f = 0; f < 4; ++f)
@@ -453,12 +600,14 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
         T Lf[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const int f = 1 + i;
-            const T rz = T(270) * (R.q[f][sl8(PH - 2)] + R.q[f][sl8(PH - 4)]) +
-                         T(-27) * (R.q[f][sl8(PH - 1)] + R.q[f][sl8(PH - 5)]) +
-                         T(2) * (R.q[f][sl8(PH)] + R.q[f][sl8(PH - 6)]) +
-                         T(-490) * R.q[f][sl8(PH - 3)];
-            Lf[i] = R.L[i][sl8(PH - 3)] + ((i == 2 && !P19) ? cf.sg4[2] : cf.sg[2]) * rz;
+            const T* sz = (i == 2 && !P19) ? cf.s4[2] : cf.s[2];
+            const T* c = R.q[i];
+            Weighted<T> z;
+            Lf[i] = R.L[i][Q];
+            z.template add<1>(sz, c[sl8(PH - 2)] + c[sl8(PH - 4)], Lf[i]);
+            z.template add<2>(sz, c[sl8(PH - 1)] + c[sl8(PH - 5)], Lf[i]);
+            z.template add<3>(sz, c[sl8(PH)] + c[sl8(PH - 6)], Lf[i]);
+            z.end(sz, Lf[i]);
         }
         if constexpr (P19) {  // (nu/3) d_z div u
             const T dd = cf.d1[2][0] * (R.qd[sl8(PH - 2)] - R.qd[sl8(PH - 4)]) +
@@ -466,37 +615,37 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
                          cf.d1[2][2] * (R.qd[sl8(PH)] - R.qd[sl8(PH - 6)]);
             Lf[2] = cf.n3 * dd + Lf[2];
         }
-        constexpr int DO = (PH + 1) & 3;  // slot of plane p - 3
-        T dxy[8];
-#pragma unroll
-        for (int f = 0; f < 4; ++f) {
-            if constexpr (DDL) {
-                const T2 v = dd2[(DO * 4 + f) * Sh::NT + threadIdx.x];
-                dxy[2 * f] = v.x;
-                dxy[2 * f + 1] = v.y;
-            } else {
-                dxy[2 * f] = R.dd[DO][2 * f];
-                dxy[2 * f + 1] = R.dd[DO][2 * f + 1];
-            }
-        }
-        const T gr[3] = {dxy[0], dxy[1], dz[0]};
-        const T J[3][3] = {{dxy[2], dxy[3], dz[1]}, {dxy[4], dxy[5], dz[2]}, {dxy[6], dxy[7], dz[3]}};
-        const T u[3] = {R.q[1][sl8(PH - 3)], R.q[2][sl8(PH - 3)], R.q[3][sl8(PH - 3)]};
+        // dz: d_z of ux, uy, uz (J22) and lnrho (g2)
+        const T u2 = R.q[2][Q], g2 = dz[3], J22 = dz[2];
+        const T h2 = cf.nu * g2, v2 = cf.nu * g2 - u2;
+        const T x = T(-2.0 / 3.0) * J22;
+        const T div = io[4] + J22;
+        const T e2 = -cf.tn * div - cf.cs2;
         T r[4];
-        assemble_rhs(u, gr, J, Lf, cf.nu, cf.cs2, r);
+        r[0] = x * io[0] + Lf[0];
+        r[0] = dz[0] * v2 + r[0];
+        r[0] = io[2] * h2 + r[0];
+        r[1] = x * io[1] + Lf[1];
+        r[1] = dz[1] * v2 + r[1];
+        r[1] = io[3] * h2 + r[1];
+        r[2] = dz[0] * io[0] + Lf[2];
+        r[2] = dz[1] * io[1] + r[2];
+        r[2] = J22 * (v2 + h2) + r[2];
+        r[2] = e2 * g2 + r[2];
+        // the small advection terms are summed before the divergence joins them:
+        // rounded together with it they bias the mean of lnrho
+        r[3] = -(u2 * g2 + io[5]) - div;
         if constexpr (FRC) {
-            // f = a cos(k.x + phase) at the output point (eq. forcing); the
-            // plane index wraps for the steps without an output plane
-            // the table is read-only during the kernel: reading it through the
+            // f = a cos(k.x + phase) at the output point (eq. forcing).  The
+            // table is read-only during the kernel: reading it through the
             // constant address space makes these scalar loads, which keep out
             // of the vector-memory counter the sweep's pipeline depends on
-            const int ow = o < 0 ? o + g.nz : o;
             const __attribute__((address_space(4))) T* ct =
                 (const __attribute__((address_space(4))) T*)ftab;
-            const T cz = ct[2 * ow], sz = ct[2 * ow + 1];
+            const T cz = ct[2 * o], sz = ct[2 * o + 1];
             const T ph = R.fc * cz - R.fs * sz;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) r[1 + i] += R.fa[i] * ph;
+            for (int i = 0; i < 3; ++i) r[i] += R.fa[i] * ph;
         }
         // ghost corner (-3, -3) of output plane o
         const long long ocorner = g.origin + (long long)o * g.plane - kR * g.px - kR;
@@ -528,274 +677,81 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
             }
             vout[f] = v;
             if constexpr (TB == 1) {
-                // new state of every extended column into the inner sweep's
-                // plane buffer (its cell is this thread's index); the input
-                // of the inner columns into ring slot (step & 3)
+                // the input of the inner columns into ring slot (step & 3)
                 constexpr int NI = (TX - 2 * kR) * (TY - 2 * kR);
-                constexpr int FS2 = SweepShape<T, TX - 2 * kR, TY - 2 * kR>::FS;
-                tb_u[(PH & 1) * 4 * FS2 + f * FS2 + threadIdx.x] = v;
                 const int ix = (int)(threadIdx.x % TX) - kR, iy = (int)(threadIdx.x / TX) - kR;
                 if (ix >= 0 && ix < TX - 2 * kR && iy >= 0 && iy < TY - 2 * kR)
                     tb_w[(PH & 3) * 4 * NI + f * NI + iy * (TX - 2 * kR) + ix] = uc;
             } else if constexpr (VS == 1) {
-                if constexpr (S >= 1) bstore<CP>(v, plane_rsrc(out.f[f] + ocorner, ob), X.lane_o);
+                if constexpr (S >= 1)
+                    bstore<CP>(v, plane_rsrc(out.f[0] + (ocorner + ((f + 1) & 3) * g.felems), ob),
+                               X.lane_o);
                 if constexpr (WOUT)
-                    bstore<CP>(wout[f], plane_rsrc(w.f[f] + (long long)o * g.wplane, wb),
+                    bstore<CP>(wout[f],
+                               plane_rsrc(w.f[0] + ((long long)o * g.wplane +
+                                                    ((f + 1) & 3) * g.wfelems), wb),
                                X.lane_w);
             }
         }
+        if constexpr (TB == 1) {
+            // new state of every extended column into the inner sweep's plane
+            // buffer (its cell is this thread's index)
+            constexpr int FS2 = SweepShape<T, TX - 2 * kR, TY - 2 * kR>::FS;
+            PlaneBuf<T, FS2>{tb_u + (PH & 1) * 4 * FS2}.put(threadIdx.x, vout);
+        }
         if constexpr (VS == 4 && TB != 1) {
             if constexpr (S >= 1)
-                bstore_point<CP>(vout, plane_rsrc(out.f[0] + 4 * ocorner, ob), X.lane_o);
+                bstore_point<CP>(vout, plane_rsrc(out.f[1] + 4 * ocorner, ob), X.lane_o);
             if constexpr (WOUT)
-                bstore_point<CP>(wout, plane_rsrc(w.f[0] + 4 * (long long)o * g.wplane, wb),
+                bstore_point<CP>(wout, plane_rsrc(w.f[1] + 4 * (long long)o * g.wplane, wb),
                                  X.lane_w);
         }
         // FP64 diagnostics of the new state, from the values just stored (the
-        // same per-point quantities as the standalone reduction)
+        // same per-point quantities as the standalone reduction); without a
+        // branch: sweep_tile drops the sums of columns outside the box
         if constexpr (RED) {
-            if (outstep && X.lane_o != kDropOffset)
-                red_point(R.red, R.bad, vout[0], vout[1], vout[2], vout[3]);
-        }
-    }
-
-    // (C) the rest of plane p for this column: x / y first derivatives of the
-    // four fields (kept 3 planes), the xy part of the linear viscous term, and
-    // the k = 1, 2 terms of the xz / yz stencils of outputs p -+ k.
-    auto dd_put = [&](int f, T dx, T dy) {
-        if constexpr (DDL) {
-            dd2[(DS * 4 + f) * Sh::NT + threadIdx.x] = T2{dx, dy};
-        } else {
-            R.dd[DS][2 * f] = dx;
-            R.dd[DS][2 * f + 1] = dy;
-        }
-    };
-    T lx, ly, lz;  // xy parts of nu (lap u_i + (1/3) d_i div u) at plane p (19-point:
-                   // of nu lap u_i)
-    T zx[2], zy[2], zz[2];  // scaled k = 1, 2 differences feeding the xz / yz terms
-    if constexpr (PIPE) {
-        // lnrho
-        auto c_lnrho = [&](const T* F) {
-            dd_put(0,
-                   cf.d1[0][0] * (F[1] - F[-1]) + cf.d1[0][1] * (F[2] - F[-2]) +
-                       cf.d1[0][2] * (F[3] - F[-3]),
-                   cf.d1[1][0] * (F[W] - F[-W]) + cf.d1[1][1] * (F[2 * W] - F[-2 * W]) +
-                       cf.d1[1][2] * (F[3 * W] - F[-3 * W]));
-        };
-        // ux
-        auto c_ux = [&](const T* F) {
-            const T c = F[0];
-            T a[3], b[3];
-            T rx = T(0), ry = T(0), m = T(0);
-    #pragma unroll
-            for (int k = 1; k <= 3; ++k) {
-                const T xp = F[k], xm = F[-k], yp = F[k * W], ym = F[-k * W];
-                a[k - 1] = xp - xm;
-                b[k - 1] = yp - ym;
-                rx += w2[k - 1] * (xp + xm);
-                ry += w2[k - 1] * (yp + ym);
-                if constexpr (!P19) {
-                    const T t = (F[k * W + k] - F[k * W - k]) + (F[-k * W - k] - F[-k * W + k]);
-                    m += w2[k - 1] * t;
-                }
-            }
-            dd_put(1, cf.d1[0][0] * a[0] + cf.d1[0][1] * a[1] + cf.d1[0][2] * a[2],
-                   cf.d1[1][0] * b[0] + cf.d1[1][1] * b[1] + cf.d1[1][2] * b[2]);
-            if constexpr (P19) {
-                lx = cf.kp * c + cf.sg[0] * rx + cf.sg[1] * ry;  // D2x + D2y
-                ly = T(0);
+            if constexpr (kRedElems<T, TX, TY, NF> > 0) {
+                double2* const a =
+                    reinterpret_cast<double2*>(ipl + kInPlaneElems<T, TX, TY, NF>) + threadIdx.x;
+                const double2 p0 = a[0], p1 = a[Sh::NT];
+                double s[4] = {p0.x, p0.y, p1.x, p1.y};
+                red_point(s, R.bad, vout[3], vout[0], vout[1], vout[2]);
+                a[0] = make_double2(s[0], s[1]);
+                a[Sh::NT] = make_double2(s[2], s[3]);
             } else {
-                lx = cf.kxy[0] * c + cf.sg4[0] * rx + cf.sg[1] * ry;  // (4/3) D2x + D2y
-                ly = cf.mu[0] * m;                                     // (1/3) Dxy ux
-            }
-            if constexpr (!P19) {
-    #pragma unroll
-                for (int k = 0; k < 2; ++k) zz[k] = cf.mu[1] * a[k];  // (1/3) Dxz ux
-            }
-        };
-        // uy
-        auto c_uy = [&](const T* F) {
-            const T c = F[0];
-            T a[3], b[3];
-            T rx = T(0), ry = T(0), m = T(0);
-    #pragma unroll
-            for (int k = 1; k <= 3; ++k) {
-                const T xp = F[k], xm = F[-k], yp = F[k * W], ym = F[-k * W];
-                a[k - 1] = xp - xm;
-                b[k - 1] = yp - ym;
-                rx += w2[k - 1] * (xp + xm);
-                ry += w2[k - 1] * (yp + ym);
-                if constexpr (!P19) {
-                    const T t = (F[k * W + k] - F[k * W - k]) + (F[-k * W - k] - F[-k * W + k]);
-                    m += w2[k - 1] * t;
-                }
-            }
-            dd_put(2, cf.d1[0][0] * a[0] + cf.d1[0][1] * a[1] + cf.d1[0][2] * a[2],
-                   cf.d1[1][0] * b[0] + cf.d1[1][1] * b[1] + cf.d1[1][2] * b[2]);
-            if constexpr (P19) {
-                ly = cf.kp * c + cf.sg[0] * rx + cf.sg[1] * ry;  // D2x + D2y
-            } else {
-                ly += cf.kxy[1] * c + cf.sg[0] * rx + cf.sg4[1] * ry;  // D2x + (4/3) D2y
-                lx += cf.mu[0] * m;                                     // (1/3) Dxy uy
-            }
-            if constexpr (!P19) {
-    #pragma unroll
-                for (int k = 0; k < 2; ++k) zz[k] += cf.mu[2] * b[k];  // (1/3) Dyz uy
-            }
-        };
-        // uz
-        auto c_uz = [&](const T* F) {
-            const T c = F[0];
-            T a[3], b[3];
-            T rx = T(0), ry = T(0);
-    #pragma unroll
-            for (int k = 1; k <= 3; ++k) {
-                const T xp = F[k], xm = F[-k], yp = F[k * W], ym = F[-k * W];
-                a[k - 1] = xp - xm;
-                b[k - 1] = yp - ym;
-                rx += w2[k - 1] * (xp + xm);
-                ry += w2[k - 1] * (yp + ym);
-            }
-            dd_put(3, cf.d1[0][0] * a[0] + cf.d1[0][1] * a[1] + cf.d1[0][2] * a[2],
-                   cf.d1[1][0] * b[0] + cf.d1[1][1] * b[1] + cf.d1[1][2] * b[2]);
-            lz = cf.kp * c + cf.sg[0] * rx + cf.sg[1] * ry;  // D2x + D2y
-            if constexpr (!P19) {
-    #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    zx[k] = cf.mu[1] * a[k];  // (1/3) Dxz uz
-                    zy[k] = cf.mu[2] * b[k];  // (1/3) Dyz uy
-                }
-            }
-        };
-        // stages: [next window, this field's arithmetic], pinned apart
-        __builtin_amdgcn_sched_barrier(0);
-        fill(wv[1], B1);
-        c_lnrho(wv[0] + C0);
-        __builtin_amdgcn_sched_barrier(0);
-        fill(wv[2], B2);
-        c_ux(wv[1] + C0);
-        __builtin_amdgcn_sched_barrier(0);
-        fill(wv[3], B3);
-        c_uy(wv[2] + C0);
-        __builtin_amdgcn_sched_barrier(0);
-        c_uz(wv[3] + C0);
-    } else {
-        dd_put(0,
-               cf.d1[0][0] * (B0[1] - B0[-1]) + cf.d1[0][1] * (B0[2] - B0[-2]) +
-                   cf.d1[0][2] * (B0[3] - B0[-3]),
-               cf.d1[1][0] * (B0[W] - B0[-W]) + cf.d1[1][1] * (B0[2 * W] - B0[-2 * W]) +
-                   cf.d1[1][2] * (B0[3 * W] - B0[-3 * W]));
-        // ux
-        {
-            const T c = B1[0];
-            T a[3], b[3];
-            T rx = T(0), ry = T(0), m = T(0);
-    #pragma unroll
-            for (int k = 1; k <= 3; ++k) {
-                const T xp = B1[k], xm = B1[-k], yp = B1[k * W], ym = B1[-k * W];
-                a[k - 1] = xp - xm;
-                b[k - 1] = yp - ym;
-                rx += w2[k - 1] * (xp + xm);
-                ry += w2[k - 1] * (yp + ym);
-                if constexpr (!P19) {
-                    const T t = (B1[k * W + k] - B1[k * W - k]) + (B1[-k * W - k] - B1[-k * W + k]);
-                    m += w2[k - 1] * t;
-                }
-            }
-            dd_put(1, cf.d1[0][0] * a[0] + cf.d1[0][1] * a[1] + cf.d1[0][2] * a[2],
-                   cf.d1[1][0] * b[0] + cf.d1[1][1] * b[1] + cf.d1[1][2] * b[2]);
-            if constexpr (P19) {
-                lx = cf.kp * c + cf.sg[0] * rx + cf.sg[1] * ry;  // D2x + D2y
-                ly = T(0);
-            } else {
-                lx = cf.kxy[0] * c + cf.sg4[0] * rx + cf.sg[1] * ry;  // (4/3) D2x + D2y
-                ly = cf.mu[0] * m;                                     // (1/3) Dxy ux
-            }
-            if constexpr (!P19) {
-    #pragma unroll
-                for (int k = 0; k < 2; ++k) zz[k] = cf.mu[1] * a[k];  // (1/3) Dxz ux
-            }
-        }
-        // uy
-        {
-            const T c = B2[0];
-            T a[3], b[3];
-            T rx = T(0), ry = T(0), m = T(0);
-    #pragma unroll
-            for (int k = 1; k <= 3; ++k) {
-                const T xp = B2[k], xm = B2[-k], yp = B2[k * W], ym = B2[-k * W];
-                a[k - 1] = xp - xm;
-                b[k - 1] = yp - ym;
-                rx += w2[k - 1] * (xp + xm);
-                ry += w2[k - 1] * (yp + ym);
-                if constexpr (!P19) {
-                    const T t = (B2[k * W + k] - B2[k * W - k]) + (B2[-k * W - k] - B2[-k * W + k]);
-                    m += w2[k - 1] * t;
-                }
-            }
-            dd_put(2, cf.d1[0][0] * a[0] + cf.d1[0][1] * a[1] + cf.d1[0][2] * a[2],
-                   cf.d1[1][0] * b[0] + cf.d1[1][1] * b[1] + cf.d1[1][2] * b[2]);
-            if constexpr (P19) {
-                ly = cf.kp * c + cf.sg[0] * rx + cf.sg[1] * ry;  // D2x + D2y
-            } else {
-                ly += cf.kxy[1] * c + cf.sg[0] * rx + cf.sg4[1] * ry;  // D2x + (4/3) D2y
-                lx += cf.mu[0] * m;                                     // (1/3) Dxy uy
-            }
-            if constexpr (!P19) {
-    #pragma unroll
-                for (int k = 0; k < 2; ++k) zz[k] += cf.mu[2] * b[k];  // (1/3) Dyz uy
-            }
-        }
-        // uz
-        {
-            const T c = B3[0];
-            T a[3], b[3];
-            T rx = T(0), ry = T(0);
-    #pragma unroll
-            for (int k = 1; k <= 3; ++k) {
-                const T xp = B3[k], xm = B3[-k], yp = B3[k * W], ym = B3[-k * W];
-                a[k - 1] = xp - xm;
-                b[k - 1] = yp - ym;
-                rx += w2[k - 1] * (xp + xm);
-                ry += w2[k - 1] * (yp + ym);
-            }
-            dd_put(3, cf.d1[0][0] * a[0] + cf.d1[0][1] * a[1] + cf.d1[0][2] * a[2],
-                   cf.d1[1][0] * b[0] + cf.d1[1][1] * b[1] + cf.d1[1][2] * b[2]);
-            lz = cf.kp * c + cf.sg[0] * rx + cf.sg[1] * ry;  // D2x + D2y
-            if constexpr (!P19) {
-    #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    zx[k] = cf.mu[1] * a[k];  // (1/3) Dxz uz
-                    zy[k] = cf.mu[2] * b[k];  // (1/3) Dyz uy
-                }
+                red_point(R.red, R.bad, vout[3], vout[0], vout[1], vout[2]);
             }
         }
     }
-
-    // Scatter: the bidiagonal xz / yz stencil at output z is
-    // sum_k c_k [A_k(z + k) - A_k(z - k)], so plane p adds +c_k A_k to the
-    // pending output p - k and -c_k A_k to p + k (c = 270, -27, 2); the k = 3
-    // terms were added in (A).
-    if constexpr (P19) {  // with (nu/3) d_x and d_y of div u
-        const T ddx = cf.d1[0][0] * (B4[1] - B4[-1]) + cf.d1[0][1] * (B4[2] - B4[-2]) +
-                      cf.d1[0][2] * (B4[3] - B4[-3]);
-        const T ddy = cf.d1[1][0] * (B4[W] - B4[-W]) + cf.d1[1][1] * (B4[2 * W] - B4[-2 * W]) +
-                      cf.d1[1][2] * (B4[3 * W] - B4[-3 * W]);
-        R.L[0][sl8(PH)] = cf.n3 * ddx + lx;
-        R.L[1][sl8(PH)] = cf.n3 * ddy + ly;
-        R.L[2][sl8(PH)] = lz;
-    } else {
-        const T* zs[3] = {zx, zy, zz};
-        const T lc[3] = {lx, ly, lz};
+    // Pin what this step formed: left alone, the compiler moves the arithmetic of
+    // a value to the step that uses it, and keeps its many operands alive instead
+    // (19-point FP64: 122 registers spilled).
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            R.L[i][sl8(PH + 2)] += T(27) * zs[i][1];
-            R.L[i][sl8(PH + 1)] += T(-270) * zs[i][0];
-            R.L[i][sl8(PH)] += lc[i];
-            R.L[i][sl8(PH - 1)] += T(270) * zs[i][0];
-            R.L[i][sl8(PH - 2)] += T(-27) * zs[i][1];
+    for (int i = 0; i < 3; ++i) {
+        if constexpr (ST >= 3) keep_here(R.L[i][P]);
+        if constexpr (!P19) {
+            if constexpr (ST + 1 >= 3) keep_here(R.L[i][sl8(PH + 1)]);
+            if constexpr (ST + 2 >= 3) keep_here(R.L[i][sl8(PH + 2)]);
+            keep_here(R.L[i][sl8(PH + 3)]);
+            if constexpr (ST >= 4) keep_here(R.L[i][sl8(PH - 1)]);
+            if constexpr (ST >= 5) keep_here(R.L[i][sl8(PH - 2)]);
         }
     }
+    // the in-plane values of plane p
+    if constexpr (ST >= 3) {
+#pragma unroll
+        for (int i = 0; i < kInPlane; i += 2) {
+            if constexpr (IPL) {
+                ip2[(i / 2) * Sh::NT] = T2{ip[i], ip[i + 1]};
+            } else {
+                keep_here(ip[i]);
+                keep_here(ip[i + 1]);
+                R.dd[DS][i] = ip[i];
+                R.dd[DS][i + 1] = ip[i + 1];
+            }
+        }
+    }
+    if constexpr (IPL) R.slot = R.slot == 2 ? 0 : R.slot + 1;
 }
 
 // One tile-chunk: columns [x0, x0 + TX) x [y0, y0 + TY) of the box, output
@@ -803,45 +759,24 @@ __device__ __forceinline__ void sweep_step(int t0, int nplanes, int zb, SweepReg
 // arguments.  P19: the 19-point method (dv holds the divergence of in).
 // RED: also reduce the FP64 diagnostics of the output and store this
 // workgroup's partial at part[blockIdx.x * kReduceSlots ...].
-template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool NT, int VS,
-          bool P19 = false, bool RED = false, bool FRC = false, bool DDL = false>
+template <typename T, typename TW, int TX, int TY, int S, int PD, bool NT, int VS,
+          bool P19 = false, bool RED = false, bool FRC = false>
 __device__ __forceinline__ void sweep_tile(const Geom& g, const Fields4<T>& in,
                                            const Fields4<T>& out, const Fields4<TW>& w,
-                                           const T* dv,
-                                           const Coef<T>& cf, const RKCoef<TW>& rk, int x0,
-                                           int y0, int zb, int ze, T* lds, lds_t<T> lds3,
-                                           double* part = nullptr,
-                                           ForceArgs<T> fa = ForceArgs<T>{nullptr, nullptr},
-                                           T* ddl = nullptr) {
-    using Sh = SweepShape<T, TX, TY, LD>;
+                                           const T* dv, const Coef<T>& cf,
+                                           const RKCoef<TW>& rk, int x0, int y0, int zb, int ze,
+                                           T* lds, double* part, ForceArgs<T> fa, T* ipl) {
+    using Sh = SweepShape<T, TX, TY>;
     constexpr int NH = Sh::NH;
-    SweepCtx<T, TX, TY, LD> X;
+    SweepCtx<T, TX, TY> X;
     static_assert(VS == 1 || !P19, "the 19-point sweep uses one array per field");
-    sweep_ctx_init<T, TW, TX, TY, LD, VS>(X, g, x0, y0);
+    sweep_ctx_init<T, TW, TX, TY, VS>(X, g, x0, y0);
 
     SweepRegs<T, TW, NH> R;
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            R.q[f][s] = T(0);
-            R.dd[s >> 1][(2 * f + (s & 1))] = T(0);
-        }
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int s = 0; s < 8; ++s) R.L[i][s] = T(0);
-    if constexpr (P19) {
-#pragma unroll
-        for (int s = 0; s < 8; ++s) R.qd[s] = T(0);
-    }
-#pragma unroll
     for (int i = 0; i < 4; ++i) R.red[i] = 0.0;
     R.bad = 0;
-    if constexpr (DDL) {
-#pragma unroll
-        for (int s = 0; s < 32; ++s) ddl[s * Sh::NT + threadIdx.x] = T(0);
-    }
+    R.slot = 0;
     if constexpr (FRC) {
         const ForceDev<T>* fd = fa.dev;
         const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
@@ -854,68 +789,78 @@ __device__ __forceinline__ void sweep_tile(const Geom& g, const Fields4<T>& in,
         for (int i = 0; i < 3; ++i) R.fa[i] = fd->a[i];
     }
 
-    const int nplanes = (ze - zb) + 2 * kR;
-    if constexpr (LD) {
-        sweep_dma<P19, T, TX, TY>(X, in, dv, plane_corner(g, zb - kR), lds3, X.plane_bytes);
-    } else {
-        sweep_prefetch<0, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR), X.plane_bytes);
-        if constexpr (PD >= 2)
-            sweep_prefetch<1, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR + 1),
-                                       X.plane_bytes);
-        if constexpr (PD == 4) {
-            // a chunk sweeps at least 7 planes, so these exist
-            sweep_prefetch<2, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR + 2),
-                                       X.plane_bytes);
-            sweep_prefetch<3, VS, P19>(R, X, in, dv, plane_corner(g, zb - kR + 3),
-                                       X.plane_bytes);
+    constexpr int NF = P19 ? 5 : 4;
+    constexpr bool RL = RED && kRedElems<T, TX, TY, NF> > 0;
+    T* const redl = ipl + kInPlaneElems<T, TX, TY, NF>;
+    if constexpr (RL) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) redl[s * Sh::NT + threadIdx.x] = T(0);
+    }
+    const int nplanes = (ze - zb) + 2 * kR;  // at least 7
+    sweep_prefetch<0, VS, P19>(R, X, in, g.felems, dv, plane_corner(g, zb - kR), X.plane_bytes);
+    if constexpr (PD >= 2)
+        sweep_prefetch<1, VS, P19>(R, X, in, g.felems, dv, plane_corner(g, zb - kR + 1),
+                                   X.plane_bytes);
+    if constexpr (PD == 4) {
+        sweep_prefetch<2, VS, P19>(R, X, in, g.felems, dv, plane_corner(g, zb - kR + 2),
+                                   X.plane_bytes);
+        sweep_prefetch<3, VS, P19>(R, X, in, g.felems, dv, plane_corner(g, zb - kR + 3),
+                                   X.plane_bytes);
+    }
+    auto step = [&](auto ph, auto st, int t) {
+        sweep_step<decltype(ph)::value, decltype(st)::value, S, PD, NT, VS, P19, RED, FRC>(
+            t, nplanes, zb, R, X, lds, g, in, out, w, dv, cf, rk, fa.tab, ipl);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    using I4 = std::integral_constant<int, 4>;
+    using I5 = std::integral_constant<int, 5>;
+    using I6 = std::integral_constant<int, 6>;
+    using I7 = std::integral_constant<int, 7>;
+    step(I0{}, I0{}, 0);
+    step(I1{}, I1{}, 1);
+    step(I2{}, I2{}, 2);
+    step(I3{}, I3{}, 3);
+    step(I4{}, I4{}, 4);
+    step(I5{}, I5{}, 5);
+    for (int t = 2 * kR; t < nplanes; t += 8) {
+        step(I6{}, I6{}, t);
+        step(I7{}, I6{}, t + 1);
+        step(I0{}, I6{}, t + 2);
+        step(I1{}, I6{}, t + 3);
+        step(I2{}, I6{}, t + 4);
+        step(I3{}, I6{}, t + 5);
+        step(I4{}, I6{}, t + 6);
+        step(I5{}, I6{}, t + 7);
+    }
+    if constexpr (RED) {
+        if constexpr (RL) {
+            const double* a = reinterpret_cast<const double*>(redl) + 2 * threadIdx.x;
+            R.red[0] = a[0], R.red[1] = a[1];
+            R.red[2] = a[2 * Sh::NT], R.red[3] = a[2 * Sh::NT + 1];
         }
+        if (X.lane_o == kDropOffset) {  // not a point of the box
+            R.red[0] = R.red[1] = R.red[2] = R.red[3] = 0.0;
+            R.bad = 0;
+        }
+        red_store_n<Sh::NW>(R.red, R.bad, part);
     }
-    for (int t0 = 0; t0 < nplanes; t0 += 8) {
-        sweep_step<0, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-        sweep_step<1, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-        sweep_step<2, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-        sweep_step<3, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-        sweep_step<4, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-        sweep_step<5, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-        sweep_step<6, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-        sweep_step<7, S, PD, LD, NT, VS, P19, RED, FRC, 0, DDL>(
-            t0, nplanes, zb, R, X, lds, lds3, g, in, out, w, dv, cf, rk, fa.tab, (T*)nullptr, (TW*)nullptr, ddl);
-    }
-    if constexpr (RED) red_store_n<SweepShape<T, TX, TY, LD>::NW>(R.red, R.bad, part);
 }
 
-// Where the x / y first derivatives wait for their output plane: LDS slots
-// for the FP64 array-of-structures register sweeps of at most 256 threads,
-// registers otherwise.  Those kernels need more than 256 registers and run
-// one wave per SIMD; the slots take about 110 registers off the part kept in
-// AGPRs and the copies between the two files.
-#ifndef FD6_DD_LDS
-#define FD6_DD_LDS 1
-#endif
-template <typename T, int TX, int TY, bool LD, int VS>
-constexpr bool kDdInLds = FD6_DD_LDS && sizeof(T) == 8 && TX * TY <= 256 && !LD && VS == 4;
-
-template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool NT, int VS,
+template <typename T, typename TW, int TX, int TY, int S, int PD, bool NT, int VS,
           bool FRC>
-__global__ __launch_bounds__(TX* TY)
+__global__ __launch_bounds__(TX* TY, kMinWaves)
 void substep55_sweep(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, Coef<T> cf,
                      RKCoef<TW> rk, SweepGrid m, ForceArgs<T> fa) {
-    using Sh = SweepShape<T, TX, TY, LD>;
-    constexpr bool DDL = kDdInLds<T, TX, TY, LD, VS>;
-    __shared__ T lds[2 * 4 * Sh::FS];
-    __shared__ __attribute__((aligned(16))) T ddl[DDL ? 32 * TX * TY : 2];
+    using Sh = SweepShape<T, TX, TY>;
+    __shared__ __attribute__((aligned(16))) T lds[2 * 4 * Sh::FS];
+    __shared__ __attribute__((aligned(16))) T ipl[kInPlaneElems<T, TX, TY, 4>];
     const TileXY t = sweep_tile_of(g, TX, TY, m);
     if (t.zb >= t.ze) return;
-    sweep_tile<T, TW, TX, TY, S, PD, LD, NT, VS, false, false, FRC, DDL>(
-        g, in, out, w, nullptr, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, (lds_t<T>)lds, nullptr, fa,
-        ddl);
+    sweep_tile<T, TW, TX, TY, S, PD, NT, VS, false, false, FRC>(
+        g, in, out, w, nullptr, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, nullptr, fa, ipl);
 }
 
 // Substeps 1 and 2 of one step in one launch: the temporal blocking the
@@ -949,19 +894,20 @@ __device__ __forceinline__ void fused12_tile(const Geom& g, const Fields4<T>& in
     static_assert(Sh2::W == EX && Sh2::H == EY, "stage-2 planes are the stage-1 tile");
     static_assert((TX * TY) % 64 == 0, "stage 2 runs on whole waves");
     SweepCtx<T, EX, EY> X1;
-    sweep_ctx_init<T, TW, EX, EY, false, VS, true>(X1, g, x0 - kR, y0 - kR);
+    sweep_ctx_init<T, TW, EX, EY, VS, true>(X1, g, x0 - kR, y0 - kR);
     SweepCtx<T, TX, TY> X2;
     const bool inner = threadIdx.x < TX * TY;
-    if (inner) sweep_ctx_init<T, TW, TX, TY, false, VS>(X2, g, x0, y0);
+    if (inner) sweep_ctx_init<T, TW, TX, TY, VS>(X2, g, x0, y0);
     SweepRegs<T, TW, Sh1::NH> R1;
     SweepRegs<T, TW, Sh2::NH> R2;
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            R1.q[f][s] = R2.q[f][s] = T(0);
-            R1.dd[s >> 1][(2 * f + (s & 1))] = R2.dd[s >> 1][(2 * f + (s & 1))] = T(0);
-        }
+        for (int s = 0; s < 8; ++s) R1.q[f][s] = R2.q[f][s] = T(0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < kInPlane; ++i) R1.dd[s][i] = R2.dd[s][i] = T(0);
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
@@ -969,22 +915,22 @@ __device__ __forceinline__ void fused12_tile(const Geom& g, const Fields4<T>& in
     const int nplanes = (ze - zb) + 4 * kR;
     const int zb1 = zb - kR, zb2 = zb - 2 * kR;  // stage 1 outputs from zb - 3
     const T* const nodiv = nullptr;
-    sweep_prefetch<0, VS, false>(R1, X1, in, nodiv, plane_corner(g, zb1 - kR), X1.plane_bytes);
+    sweep_prefetch<0, VS, false>(R1, X1, in, g.felems, nodiv, plane_corner(g, zb1 - kR), X1.plane_bytes);
     if constexpr (PD >= 2)
-        sweep_prefetch<1, VS, false>(R1, X1, in, nodiv, plane_corner(g, zb1 - kR + 1),
+        sweep_prefetch<1, VS, false>(R1, X1, in, g.felems, nodiv, plane_corner(g, zb1 - kR + 1),
                                      X1.plane_bytes);
     static_assert(PD == 1 || PD == 2, "prefetch depth of the fused sweep");
     const Fields4<T> none{{nullptr, nullptr, nullptr, nullptr}};
     for (int t0 = 0; t0 < nplanes; t0 += 8) {
 #define FD6_FUSED_STEP(PH)                                                                      \
-        sweep_step<PH, 1, PD, false, NT, VS, false, false, false, 1>(                            \
-            t0, nplanes, zb1, R1, X1, lds1, (lds_t<T>)lds1, g, in, none, w, nodiv, cf,            \
-            rk1, (const T*)nullptr, lds2, ring);                                                 \
+        sweep_step<PH, 6, 1, PD, NT, VS, false, false, false, 1>(                                \
+            t0 + PH, nplanes, zb1, R1, X1, lds1, g, in, none, w, nodiv, cf,            \
+            rk1, (const T*)nullptr, (T*)nullptr, lds2, ring);                                                 \
         __syncthreads();                                                                         \
         if (inner)                                                                               \
-            sweep_step<PH, 2, PD, false, NT, VS, false, false, false, 2>(                        \
-                t0, nplanes, zb2, R2, X2, lds2, (lds_t<T>)lds2, g, in, out, w, nodiv, cf,         \
-                rk2, (const T*)nullptr, (T*)nullptr, ring);
+            sweep_step<PH, 6, 2, PD, NT, VS, false, false, false, 2>(                            \
+                t0 + PH, nplanes, zb2, R2, X2, lds2, g, in, out, w, nodiv, cf,         \
+                rk2, (const T*)nullptr, (T*)nullptr, (T*)nullptr, ring);
         FD6_FUSED_STEP(0)
         FD6_FUSED_STEP(1)
         FD6_FUSED_STEP(2)
@@ -1003,8 +949,8 @@ void substep55_fused12(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, Coe
                        RKCoef<TW> rk1, RKCoef<TW> rk2, SweepGrid m) {
     using Sh1 = SweepShape<T, TX + 2 * kR, TY + 2 * kR>;
     using Sh2 = SweepShape<T, TX, TY>;
-    __shared__ T lds1[2 * 4 * Sh1::FS];
-    __shared__ T lds2[2 * 4 * Sh2::FS];
+    __shared__ __attribute__((aligned(16))) T lds1[2 * 4 * Sh1::FS];
+    __shared__ __attribute__((aligned(16))) T lds2[2 * 4 * Sh2::FS];
     __shared__ TW ring[4 * 4 * TX * TY];
     const TileXY t = sweep_tile_of(g, TX, TY, m);
     if (t.zb >= t.ze) return;
@@ -1014,18 +960,18 @@ void substep55_fused12(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, Coe
 
 // Substep 3 with the FP64 diagnostics of the new state fused in: one partial
 // per workgroup (every workgroup of the grid has a non-empty chunk).
-template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, int VS, bool FRC>
-__global__ __launch_bounds__(TX* TY)
+template <typename T, typename TW, int TX, int TY, int PD, bool NT, int VS, bool FRC>
+__global__ __launch_bounds__(TX* TY, kMinWaves)
 void substep55_sweep_red(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, Coef<T> cf,
                          RKCoef<TW> rk, SweepGrid m, double* part,
                          ForceArgs<T> fa) {
-    using Sh = SweepShape<T, TX, TY, LD>;
-    constexpr bool DDL = kDdInLds<T, TX, TY, LD, VS>;
-    __shared__ T lds[2 * 4 * Sh::FS];
-    __shared__ __attribute__((aligned(16))) T ddl[DDL ? 32 * TX * TY : 2];
+    using Sh = SweepShape<T, TX, TY>;
+    __shared__ __attribute__((aligned(16))) T lds[2 * 4 * Sh::FS];
+    __shared__ __attribute__((aligned(16))) T ipl[kInPlaneElems<T, TX, TY, 4> +
+                                                  kRedElems<T, TX, TY, 4>];
     const TileXY t = sweep_tile_of(g, TX, TY, m);
-    sweep_tile<T, TW, TX, TY, 3, PD, LD, NT, VS, false, true, FRC, DDL>(
-        g, in, out, w, nullptr, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, (lds_t<T>)lds, part, fa, ddl);
+    sweep_tile<T, TW, TX, TY, 3, PD, NT, VS, false, true, FRC>(
+        g, in, out, w, nullptr, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, part, fa, ipl);
 }
 
 // The 19-point method (Sec. 4.2, Algorithm 3): the same sweep over the state
@@ -1035,18 +981,20 @@ void substep55_sweep_red(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, C
 // point and step in FP32.  With the divergence computed first, every value is
 // written once: 188 bytes (256^3 FP32 with a new force every step, 10 steps and
 // a snapshot: 10.96 -> 8.18 ms; 300 x 240 x 192 FP64, 5 steps: 11.46 -> 9.57 ms).
-template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool NT, bool FRC,
+template <typename T, typename TW, int TX, int TY, int S, int PD, bool NT, bool FRC,
           bool RED = false>
-__global__ __launch_bounds__(TX* TY)
+__global__ __launch_bounds__(TX* TY, kMinWaves)
 void substep19_sweep(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, const T* dv,
                      Coef<T> cf, RKCoef<TW> rk, SweepGrid m, double* part, ForceArgs<T> fa) {
-    using Sh = SweepShape<T, TX, TY, LD>;
+    using Sh = SweepShape<T, TX, TY>;
     static_assert(!RED || S == 3, "diagnostics of the final substep only");
-    __shared__ T lds[2 * 5 * Sh::FS];
+    __shared__ __attribute__((aligned(16))) T lds[2 * 5 * Sh::FS];
+    __shared__ __attribute__((aligned(16))) T ipl[kInPlaneElems<T, TX, TY, 5> +
+                                                  (RED ? kRedElems<T, TX, TY, 5> : 0)];
     const TileXY t = sweep_tile_of(g, TX, TY, m);
     if (!RED && t.zb >= t.ze) return;
-    sweep_tile<T, TW, TX, TY, S, PD, LD, NT, 1, true, RED, FRC>(
-        g, in, out, w, dv, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, (lds_t<T>)lds, part, fa);
+    sweep_tile<T, TW, TX, TY, S, PD, NT, 1, true, RED, FRC>(
+        g, in, out, w, dv, cf, rk, t.tx, t.ty, t.zb, t.ze, lds, part, fa, ipl);
 }
 
 // Batched form: one persistent launch advances every box of an ensemble by
@@ -1057,13 +1005,14 @@ void substep19_sweep(Geom g, Fields4<T> in, Fields4<T> out, Fields4<TW> w, const
 // geometry, pointers, coefficients and time step come from device memory, so
 // a captured graph never needs re-capture when they change.  Per point the
 // arithmetic is the single-box kernel's.
-template <typename T, typename TW, int TX, int TY, int S, int PD, bool LD, bool NT, int VS>
-__global__ __launch_bounds__(TX* TY)
+template <typename T, typename TW, int TX, int TY, int S, int PD, bool NT, int VS>
+__global__ __launch_bounds__(TX* TY, kMinWaves)
 void substep55_batch(const BatchBox<T, TW>* __restrict__ boxes,
                      const BatchItem* __restrict__ items, const int* __restrict__ wg_first,
                      int parity) {
-    using Sh = SweepShape<T, TX, TY, LD>;
-    __shared__ T lds[2 * 4 * Sh::FS];
+    using Sh = SweepShape<T, TX, TY>;
+    __shared__ __attribute__((aligned(16))) T lds[2 * 4 * Sh::FS];
+    __shared__ __attribute__((aligned(16))) T ipl[kInPlaneElems<T, TX, TY, 4>];
     const int G = gridDim.x;
     int b = blockIdx.x;
     if ((G & 7) == 0) b = (b & 7) * (G >> 3) + (b >> 3);
@@ -1076,8 +1025,9 @@ void substep55_batch(const BatchBox<T, TW>* __restrict__ boxes,
         const Fields4<T> in = bx->st[parity], out = bx->st[parity ^ 1];
         const Fields4<TW> w = bx->w;
         const RKCoef<TW> rk = bx->rk[S - 1];
-        sweep_tile<T, TW, TX, TY, S, PD, LD, NT, VS>(g, in, out, w, nullptr, cf, rk, wi.x0, wi.y0,
-                                             wi.zb, wi.ze, lds, (lds_t<T>)lds);
+        sweep_tile<T, TW, TX, TY, S, PD, NT, VS>(g, in, out, w, nullptr, cf, rk, wi.x0, wi.y0,
+                                                   wi.zb, wi.ze, lds, nullptr,
+                                                   ForceArgs<T>{nullptr, nullptr}, ipl);
         __syncthreads();  // the next item's first LDS write must follow every read
     }
 }
@@ -1094,33 +1044,33 @@ hipError_t launch_s(int s, dim3 grid, dim3 block, hipStream_t st, A... args) {
     return hipGetLastError();
 }
 
-template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, int VS, bool FRC>
+template <typename T, typename TW, int TX, int TY, int PD, bool NT, int VS, bool FRC>
 struct K55 {
     template <int S>
     struct at {
-        static constexpr auto fn = substep55_sweep<T, TW, TX, TY, S, PD, LD, NT, VS, FRC>;
+        static constexpr auto fn = substep55_sweep<T, TW, TX, TY, S, PD, NT, VS, FRC>;
     };
 };
-template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, int VS, bool FRC>
+template <typename T, typename TW, int TX, int TY, int PD, bool NT, int VS, bool FRC>
 struct KRed {
-    static constexpr auto fn = substep55_sweep_red<T, TW, TX, TY, PD, LD, NT, VS, FRC>;
+    static constexpr auto fn = substep55_sweep_red<T, TW, TX, TY, PD, NT, VS, FRC>;
 };
-template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, bool FRC>
+template <typename T, typename TW, int TX, int TY, int PD, bool NT, bool FRC>
 struct K19 {
     template <int S>
     struct at {
-        static constexpr auto fn = substep19_sweep<T, TW, TX, TY, S, PD, LD, NT, FRC>;
+        static constexpr auto fn = substep19_sweep<T, TW, TX, TY, S, PD, NT, FRC>;
     };
 };
-template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, bool FRC>
+template <typename T, typename TW, int TX, int TY, int PD, bool NT, bool FRC>
 struct K19Red {
-    static constexpr auto fn = substep19_sweep<T, TW, TX, TY, 3, PD, LD, NT, FRC, true>;
+    static constexpr auto fn = substep19_sweep<T, TW, TX, TY, 3, PD, NT, FRC, true>;
 };
-template <typename T, typename TW, int TX, int TY, int PD, bool LD, bool NT, int VS>
+template <typename T, typename TW, int TX, int TY, int PD, bool NT, int VS>
 struct KBatch {
     template <int S>
     struct at {
-        static constexpr auto fn = substep55_batch<T, TW, TX, TY, S, PD, LD, NT, VS>;
+        static constexpr auto fn = substep55_batch<T, TW, TX, TY, S, PD, NT, VS>;
     };
 };
 // Shape that evaluates the bare right-hand side (S = 0).
@@ -1148,7 +1098,7 @@ hipError_t launch_substep55_vs(const Geom& g, Fields4<T> in, Fields4<T> out, Fie
         if (tile == 0) return hipErrorInvalidValue;
         auto rhs = [&](auto force) -> hipError_t {
             constexpr TileCfg k = kTiles[kRhsTile<T>];
-            constexpr auto fn = substep55_sweep<T, TW, k.tx, k.ty, 0, k.pd, k.ld, k.nt, VS,
+            constexpr auto fn = substep55_sweep<T, TW, k.tx, k.ty, 0, kPd<T, k.pd>, k.nt, VS,
                                                 decltype(force)::value>;
             const SweepGrid sg =
                 sweep_grid(g, k.tx, k.ty, 0, resident_blocks<fn>(k.tx * k.ty));
@@ -1162,7 +1112,7 @@ hipError_t launch_substep55_vs(const Geom& g, Fields4<T> in, Fields4<T> out, Fie
         constexpr bool FRC = decltype(force)::value;
         return with_tile(tile, hipErrorInvalidValue, [&](auto I) -> hipError_t {
             constexpr TileCfg k = kTiles[decltype(I)::value];
-            if constexpr (VS != 1 && (k.tx == 0 || k.ld)) {
+            if constexpr (VS != 1 && (k.tx == 0 || k.soa)) {
                 return hipErrorInvalidValue;
             } else if constexpr (k.tx == 0) {
                 const dim3 grid((unsigned)((g.nx + 63) / 64), (unsigned)((g.ny + 3) / 4),
@@ -1170,8 +1120,8 @@ hipError_t launch_substep55_vs(const Geom& g, Fields4<T> in, Fields4<T> out, Fie
                 return launch_s<KDirect<T, TW, FRC>::template at>(s, grid, dim3(256), st, g, in,
                                                                   out, w, c, rk, fa);
             } else {
-                using K = K55<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, VS, FRC>;
-                using KR = KRed<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, VS, FRC>;
+                using K = K55<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, VS, FRC>;
+                using KR = KRed<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, VS, FRC>;
                 const int res = resident_blocks<K::template at<2>::fn>(k.tx * k.ty);
                 const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res);
                 // fuse only where the extra accumulators cost no occupancy
@@ -1231,7 +1181,7 @@ hipError_t launch_substep19(const Geom& g, Fields4<T> in, Fields4<T> out, Fields
     if (s == 0) {
         auto rhs = [&](auto force) -> hipError_t {
             constexpr TileCfg k = kTiles[kRhsTile<T>];
-            constexpr auto fn = substep19_sweep<T, TW, k.tx, k.ty, 0, k.pd, k.ld, k.nt,
+            constexpr auto fn = substep19_sweep<T, TW, k.tx, k.ty, 0, kPd<T, k.pd>, k.nt,
                                                 decltype(force)::value>;
             const SweepGrid sg =
                 sweep_grid(g, k.tx, k.ty, 0, resident_blocks<fn>(k.tx * k.ty));
@@ -1248,8 +1198,8 @@ hipError_t launch_substep19(const Geom& g, Fields4<T> in, Fields4<T> out, Fields
             if constexpr (k.tx == 0) {
                 return hipErrorInvalidValue;
             } else {
-                using K = K19<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, FRC>;
-                using KR = K19Red<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, FRC>;
+                using K = K19<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, FRC>;
+                using KR = K19Red<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, FRC>;
                 const int blk = k.tx * k.ty;
                 const int res = resident_blocks<K::template at<2>::fn>(blk);
                 const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res);
@@ -1277,10 +1227,10 @@ hipError_t launch_batch55_vs(const BatchBox<T, TW>* boxes, const BatchItem* item
                              hipStream_t st) {
     return with_tile(tile, hipErrorInvalidValue, [&](auto I) -> hipError_t {
         constexpr TileCfg k = kTiles[decltype(I)::value];
-        if constexpr (k.tx == 0 || (VS != 1 && k.ld)) {
+        if constexpr (k.tx == 0 || (VS != 1 && k.soa)) {
             return hipErrorInvalidValue;
         } else {
-            return launch_s<KBatch<T, TW, k.tx, k.ty, k.pd, k.ld, k.nt, VS>::template at>(
+            return launch_s<KBatch<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, VS>::template at>(
                 s, dim3(grid), dim3(k.tx * k.ty), st, boxes, items, wg_first, parity);
         }
     });
@@ -1290,12 +1240,12 @@ template <typename T, typename TW, int VS>
 int batch55_blocks_per_cu_vs(int tile) {
     return with_tile(tile, 1, [&](auto I) -> int {
         constexpr TileCfg k = kTiles[decltype(I)::value];
-        if constexpr (k.tx == 0 || (VS != 1 && k.ld)) {
+        if constexpr (k.tx == 0 || (VS != 1 && k.soa)) {
             return 1;
         } else {
             int n = 0;
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                    &n, substep55_batch<T, TW, k.tx, k.ty, 2, k.pd, k.ld, k.nt, VS>, k.tx * k.ty,
+                    &n, substep55_batch<T, TW, k.tx, k.ty, 2, kPd<T, k.pd>, k.nt, VS>, k.tx * k.ty,
                     0) != hipSuccess)
                 return 1;
             return n > 0 ? n : 1;
