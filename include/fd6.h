@@ -183,8 +183,9 @@ int fd6_rhs(fd6_box *box, double *r_lnrho, double *r_ux, double *r_uy, double *r
  * last-level cache).  Results agree up to rounding order (the z-sweep shapes
  * bit for bit with each other); the choice only changes speed (see the
  * autotuner).  FD6_EINVAL for an index out of range; FD6_EUNSUPPORTED for a
- * shape the box's layout does not take (FD6_LAYOUT_AOS).  Default: 6 (64 x 8,
- * two planes ahead) for FP32 state, 8 (32 x 8, two planes ahead) for FP64. */
+ * shape the box's layout does not take (FD6_LAYOUT_AOS).  Until a shape is set or
+ * tuned the library picks one by the box's size, precision, method and layout
+ * (fd6_get_schedule then reports 6 for FP32 state, 8 for FP64). */
 int fd6_tile_count(void);
 int fd6_set_tile(fd6_box *box, int32_t tile);
 
@@ -351,7 +352,7 @@ int fd6_batch_init_fields(fd6_batch *batch, int32_t box, const double *lnrho, co
  * FD6_EUNSUPPORTED for a shape the ensemble's layout does not take.  A
  * refused call leaves the schedule in force (and fd6_batch_get_schedule's
  * answer) unchanged.  Default: shape 8 (32 x 8, two planes ahead), chunks of
- * at most 64 planes. */
+ * at most 64 planes, of a length fitted to the boxes. */
 #define FD6_BATCH_BALANCED (-1)
 #define FD6_BATCH_PACKED (-2)
 int fd6_batch_set_schedule(fd6_batch *batch, int32_t tile, int32_t zchunk);

@@ -47,8 +47,10 @@ struct fd6_box {
     double* staging = nullptr;
     long long staging_elems = 0;
     int cur = 0;
-    int tile = 6;  // z-sweep shape; fd6_create picks it by precision
+    int tile = 6;  // z-sweep shape set or tuned (before: what fd6_get_schedule reports)
     int zchunk = 0;  // z-sweep chunk length, 0: automatic
+    bool shape_set = false;  // otherwise the launchers pick the shape by size
+    int run_tile() const { return shape_set ? tile : kAutoTile; }
     // candidates timed by the last fd6_tune call: (tile, zchunk, ms per step)
     struct TuneTrial {
         int tile, zchunk;
@@ -99,7 +101,8 @@ struct fd6_batch {
     int n = 0;
     int precision = 0;
     int tile = 8;     // 32 x 8 z-sweep, two planes ahead
-    int zchunk = 64;  // planes per work item (0: whole box)
+    int zchunk = 64;  // planes per work item at most (0: whole box)
+    bool schedule_set = false;  // otherwise the chunk length is fitted to the boxes
     bool aos = false;  // every box in the array-of-structures layout
     bool use_graph = true;
     hipStream_t stream = nullptr;   // caller's stream (graph launches, transfers)
@@ -424,7 +427,7 @@ int do_substep(fd6_box* b, int s, const RKCoef<TW>& rk, double* red_out = nullpt
     Fields4<T> out = fields_of<T>(b->state[b->cur ^ 1]);
     Fields4<TW> w = fields_of<TW>(b->w);
     const Coef<T> c = make_coef<T>(b->params);
-    const bool needs_ghosts = substep55_reads_ghosts(b->tile);
+    const bool needs_ghosts = substep55_reads_ghosts(b->run_tile());
     int rc = FD6_OK;
     if (needs_ghosts && !b->ghosts_ok[b->cur]) {
         rc = timed(b, b->ev_ghost, [&]() -> int {
@@ -442,7 +445,7 @@ int do_substep(fd6_box* b, int s, const RKCoef<TW>& rk, double* red_out = nullpt
         double* parts = (red_out && s == 3) ? b->partials : nullptr;
         auto launch = g.vs == 4 ? launch_substep55_aos<T, TW> : launch_substep55<T, TW>;
         rc = timed(b, b->ev_kernel, [&]() -> int {
-            HIPCHK(b, launch(g, in, out, w, c, rk, s, b->tile, b->zchunk, parts, kFusedPartials,
+            HIPCHK(b, launch(g, in, out, w, c, rk, s, b->run_tile(), b->zchunk, parts, kFusedPartials,
                              &nparts, frc, b->stream));
             return FD6_OK;
         });
@@ -470,7 +473,7 @@ int do_substep(fd6_box* b, int s, const RKCoef<TW>& rk, double* red_out = nullpt
             if (needs_ghosts)
                 HIPCHK(b, (launch_pass19b<T, TW>(g, dv, out, w, c, rk, b->stream)));
             else
-                HIPCHK(b, (launch_substep19<T, TW>(g, in, out, w, dv, c, rk, s, b->tile,
+                HIPCHK(b, (launch_substep19<T, TW>(g, in, out, w, dv, c, rk, s, b->run_tile(),
                                                    b->zchunk, parts, kFusedPartials, &nparts,
                                                    frc, b->stream)));
             return FD6_OK;
@@ -630,7 +633,7 @@ int do_rhs(fd6_box* b, double* const out[4]) {
     RKCoef<TW> rk{TW(0), TW(0), TW(1), TW(0), TW(0)};
     int rc = force_sync<T>(b);
     if (rc) return rc;
-    rc = do_substep<T, TW>(b, substep55_reads_ghosts(b->tile) ? 1 : 0, rk);
+    rc = do_substep<T, TW>(b, substep55_reads_ghosts(b->run_tile()) ? 1 : 0, rk);
     if (rc) return rc;  // a failed substep returns before its in/out swap
     b->cur ^= 1;        // keep the original state current
     b->ghosts_ok[b->cur ^ 1] = false;
@@ -1020,6 +1023,46 @@ int build_items(fd6_batch* b, int tile, int zchunk) {
     return FD6_OK;
 }
 
+// Chunk length of an ensemble that has no schedule set: the one of at most 64
+// planes whose deal in turn leaves the most loaded workgroup the least plane steps
+// (5 more per chunk: the refill's six run less than the full arithmetic), the
+// longest among equals.  Long chunks suit ensembles that fill the device several
+// times over; a few boxes in 64-plane chunks leave most workgroups without work
+// (12 boxes with edges 32-96 on 512 workgroups: 69 plane steps at 64, 37 at 32).
+template <typename T, typename TW>
+int fitted_chunk(fd6_batch* b) {
+    int tx = 0, ty = 0;
+    if (substep55_tile_dims(b->tile, &tx, &ty)) return b->zchunk;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return b->zchunk;
+    const long long G = std::max<long long>(
+        1, (long long)cus * (b->aos ? batch55_blocks_per_cu_aos<T, TW>(b->tile)
+                                    : batch55_blocks_per_cu<T, TW>(b->tile)));
+    int best = b->zchunk;
+    long long least = -1;
+    for (int zc : {64, 56, 48, 40, 32, 28, 24, 20, 16, 12, 8}) {
+        std::array<long long, 65> count{};  // chunks by length
+        for (const Geom& g : b->geom) {
+            const int cap = std::min(zc, g.nz), nch = (g.nz + cap - 1) / cap;
+            const int zl = (g.nz + nch - 1) / nch, last = g.nz - (g.nz - 1) / zl * zl;
+            const long long cols = (long long)((g.nx + tx - 1) / tx) * ((g.ny + ty - 1) / ty);
+            count[zl] += cols * ((g.nz - 1) / zl);
+            count[last] += cols;
+        }
+        // the most loaded workgroup takes the first entry of each round
+        long long load = 0, dealt = 0;
+        for (int len = 64; len >= 1; --len) {
+            const long long first = (dealt + G - 1) / G, next = (dealt + count[len] + G - 1) / G;
+            load += (next - first) * (len + 5);
+            dealt += count[len];
+        }
+        if (least < 0 || load < least) least = load, best = zc;
+    }
+    return best;
+}
+
 template <typename T, typename TW>
 int batch_substeps(fd6_batch* b, hipStream_t st, int parity) {
     auto launch = b->aos ? launch_batch55_aos<T, TW> : launch_batch55<T, TW>;
@@ -1056,7 +1099,10 @@ int build_graphs(fd6_batch* b) {
 template <typename T, typename TW>
 int batch_steps(fd6_batch* b, int nsteps) {
     if (b->nitems == 0) {
-        int rc = build_items<T, TW>(b, b->tile, b->zchunk);
+        const int reported = b->zchunk;
+        int rc = build_items<T, TW>(
+            b, b->tile, b->schedule_set ? b->zchunk : fitted_chunk<T, TW>(b));
+        b->zchunk = reported;
         if (rc) return rc;
     }
     if (b->use_graph && !b->graph_ok) {
@@ -1273,8 +1319,7 @@ int fd6_create(const fd6_desc* desc, void* d_ws, size_t bytes, void* stream, fd6
     return guarded((fd6_box*)nullptr, [&]() -> int {
         fd6_box* b = new fd6_box();
         b->desc = *desc;
-        // the fastest shapes at 512^3: 64 x 8 for FP32 state, 32 x 8 for FP64
-        // (whose 512-thread shapes spill), both two planes ahead
+        // reported until a shape is set or tuned; until then the launchers choose
         b->tile = desc->precision == FD6_FP64 ? 8 : 6;
         b->geom = p.g;
         b->stream = static_cast<hipStream_t>(stream);
@@ -1506,8 +1551,9 @@ const char* fd6_last_error(const fd6_box* b) { return b ? b->err.c_str() : ""; }
 int fd6_set_tile(fd6_box* b, int32_t tile) {
     if (!b || tile < 0 || tile >= substep55_tile_count()) return FD6_EINVAL;
     if (b->geom.vs == 4 && !substep55_aos_tile_ok(tile)) return FD6_EUNSUPPORTED;
-    if (tile != b->tile) b->drop_graphs();
+    if (tile != b->run_tile()) b->drop_graphs();
     b->tile = tile;
+    b->shape_set = true;
     return FD6_OK;
 }
 
@@ -1562,8 +1608,9 @@ int fd6_tune(fd6_box* b, const char* cache_path) {
             b->timing = false;
             // ms per reducing step of one schedule (one warm-up step first)
             auto trial = [&](int cand, int zc, float* ms) -> int {
-                if (cand != b->tile || zc != b->zchunk) b->drop_graphs();
+                if (cand != b->run_tile() || zc != b->zchunk) b->drop_graphs();
                 b->tile = cand;
+                b->shape_set = true;
                 b->zchunk = zc;
                 int rc = do_steps<T, TW>(b, 1, b->result);
                 if (rc) return rc;
@@ -1725,7 +1772,9 @@ int fd6_batch_set_schedule(fd6_batch* b, int32_t tile, int32_t zchunk) {
         return batch_dispatch(b, [&](auto* t, auto* tw) -> int {
             using T = std::remove_pointer_t<decltype(t)>;
             using TW = std::remove_pointer_t<decltype(tw)>;
-            return build_items<T, TW>(b, tile, zchunk);
+            const int rc = build_items<T, TW>(b, tile, zchunk);
+            if (rc == FD6_OK) b->schedule_set = true;
+            return rc;
         });
     });
 }
@@ -1809,10 +1858,13 @@ int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
                     best_ms = fastest[k], best_tile = cands[k].first, best_zc = cands[k].second;
             if (rc != FD6_OK) {
                 // a failed trial leaves the schedule that was in force before
+                // (none set: it is fitted again by the next step)
                 (void)build_items<T, TW>(b, old_tile, old_zc);
+                if (!b->schedule_set) b->nitems = 0;
                 return rc;
             }
             rc = build_items<T, TW>(b, best_tile, best_zc);
+            if (rc == FD6_OK) b->schedule_set = true;
             if (rc == FD6_OK && cache_path) write_tune_cache(cache_path, key, best_tile, best_zc);
             return rc;
         });

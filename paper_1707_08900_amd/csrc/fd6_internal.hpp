@@ -133,6 +133,8 @@ hipError_t launch_export_w(const Geom& g, const TW* src, double* dst, int z0, in
 template <typename TW>
 hipError_t launch_zero_w(const Geom& g, Fields4<TW> w, hipStream_t s);
 
+// Kernel shape left to the launcher (auto_shape, by the box's size).
+constexpr int kAutoTile = -1;
 // 55-point fused right-hand side + RK3 update for substep s (1, 2, 3) with
 // kernel shape `tile` and z-chunk length `zchunk` (0: chosen by the launcher).
 // s = 0 (z-sweep shapes): the right-hand side alone, written to w; the state

@@ -249,6 +249,15 @@ inline SweepGrid sweep_grid(const Geom& g, int tx, int ty, int zchunk, int resid
     return s;
 }
 
+inline int device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        cus = 256;
+    return cus;
+}
+
 // Workgroups of Kernel (block threads) the current device holds at once
 // (the per-CU occupancy is queried once per kernel).
 template <auto Kernel>
@@ -259,12 +268,7 @@ int resident_blocks(int block) {
             n = 1;
         return n > 0 ? n : 1;
     }();
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-        cus = 256;
-    return per_cu * cus;
+    return per_cu * device_cus();
 }
 
 struct TileXY {
@@ -368,6 +372,46 @@ constexpr TileCfg kTiles[] = {
 template <typename T, int PD>
 constexpr int kPd = sizeof(T) == 8 ? 1 : PD;
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+
+// Shape and z-chunk of a box that has neither set nor tuned: a wide (64 x 8) or a
+// narrow (32 x 8) tile.  Both run two waves per SIMD, so the sweeps of a round cost
+// the same; ms per step with diagnostics, wide against narrow:
+//  * FP32 state and register, array of structures: narrow, 3-6% faster at every
+//    size (its two workgroups per compute unit wait at separate barriers): 64^3
+//    0.035 / 0.036, 96^3 0.062 / 0.052, 128^3 0.085 / 0.083, 256^3 0.520 / 0.508,
+//    384^3 1.86 / 1.78, 640^3 8.40 / 7.98.  Whole columns in more than one round
+//    are the exception (512^3: 4.11 / 4.21); in two chunks they are not (4.03).
+//  * Otherwise wide, whose halo costs less where a cell's fields lie apart or the
+//    state is twice as large (FP32 one array per field 256^3 0.569 / 0.619, FP64
+//    512^3 7.55 / 8.11, 19-point FP32 256^3 0.759 / 0.840), unless the box is no
+//    wider than the narrow tile (32^3: FP32 0.032 / 0.028, FP64 0.038 / 0.034) or
+//    the wide tile needs over 6/5 of the narrow one's plane steps (FP64 96^3: 16
+//    against 13 per workgroup, 0.093 / 0.086; 150 x 75 x 101: 19 against 17, 0.116
+//    / 0.139).
+struct AutoShape {
+    int tile, zchunk;
+};
+template <typename T, typename TW, int VS, bool P19>
+AutoShape auto_shape(const Geom& g, int zchunk) {
+    constexpr bool pd1 = sizeof(T) == 8 || P19;  // (one plane ahead: 1-3% in 19-point FP32)
+    constexpr int wide = pd1 ? 2 : 6, narrow = pd1 ? 4 : 8;
+    const int cus = device_cus();
+    auto grid = [&](int tile) {
+        const int tx = kTiles[tile].tx, ty = kTiles[tile].ty;
+        return sweep_grid(g, tx, ty, zchunk, cus * (512 / (tx * ty)));
+    };
+    const SweepGrid n = grid(narrow);
+    const int rn = (n.blocks + 2 * cus - 1) / (2 * cus);
+    if (VS == 4 && std::is_same_v<T, float> && std::is_same_v<TW, float>) {
+        const bool columns = zchunk == 0 && rn > 1 && n.zlen >= g.nz;
+        return AutoShape{narrow, columns ? (g.nz + 1) / 2 : zchunk};
+    }
+    if (g.nx <= kTiles[narrow].tx) return AutoShape{narrow, zchunk};
+    const SweepGrid w = grid(wide);
+    const int rw = (w.blocks + cus - 1) / cus;
+    const long long cn = (long long)rn * (n.zlen + 2 * kR), cw = (long long)rw * (w.zlen + 2 * kR);
+    return AutoShape{6 * cn < 5 * cw ? narrow : wide, zchunk};
+}
 
 // Calls f(std::integral_constant<int, tile>) so that f can use kTiles[tile]
 // as template arguments; returns `bad` for an out-of-range tile.

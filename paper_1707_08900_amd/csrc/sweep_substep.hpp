@@ -1108,6 +1108,11 @@ hipError_t launch_substep55_vs(const Geom& g, Fields4<T> in, Fields4<T> out, Fie
         };
         return frc ? rhs(std::true_type{}) : rhs(std::false_type{});
     }
+    if (tile == kAutoTile) {
+        const AutoShape a = auto_shape<T, TW, VS, false>(g, zchunk);
+        tile = a.tile;
+        zchunk = a.zchunk;
+    }
     auto go = [&](auto force) -> hipError_t {
         constexpr bool FRC = decltype(force)::value;
         return with_tile(tile, hipErrorInvalidValue, [&](auto I) -> hipError_t {
@@ -1190,6 +1195,11 @@ hipError_t launch_substep19(const Geom& g, Fields4<T> in, Fields4<T> out, Fields
             return hipGetLastError();
         };
         return frc ? rhs(std::true_type{}) : rhs(std::false_type{});
+    }
+    if (tile == kAutoTile) {
+        const AutoShape a = auto_shape<T, TW, 1, true>(g, zchunk);
+        tile = a.tile;
+        zchunk = a.zchunk;
     }
     auto go = [&](auto force) -> hipError_t {
         constexpr bool FRC = decltype(force)::value;
