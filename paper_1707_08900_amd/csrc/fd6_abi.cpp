@@ -695,25 +695,13 @@ int export_host(fd6_box* b, double* const dst[4]) {
 
 template <typename T>
 int import_device(fd6_box* b, const double* const src[4]) {
-    for (int q = 0; q < 4; ++q)
-        HIPCHK(b, launch_import<T>(b->geom, src[q], static_cast<T*>(b->state[b->cur][q]), 0,
-                                   b->geom.nz, b->stream));
+    HIPCHK(b, launch_import4<T>(b->geom, src, fields_of<T>(b->state[b->cur]), b->stream));
     return FD6_OK;
 }
 
 template <typename T>
 int export_device(fd6_box* b, double* const dst[4]) {
-    for (int q = 0; q < 4; ++q)
-        HIPCHK(b, launch_export<T>(b->geom, static_cast<const T*>(b->state[b->cur][q]), dst[q], 0,
-                                   b->geom.nz, b->stream));
-    return FD6_OK;
-}
-
-int reset_w(fd6_box* b) {
-    if (b->wsize == 8)
-        HIPCHK(b, launch_zero_w<double>(b->geom, fields_of<double>(b->w), b->stream));
-    else
-        HIPCHK(b, launch_zero_w<float>(b->geom, fields_of<float>(b->w), b->stream));
+    HIPCHK(b, launch_export4<T>(b->geom, fields_of<T>(b->state[b->cur]), dst, b->stream));
     return FD6_OK;
 }
 
@@ -1400,8 +1388,6 @@ int fd6_init_fields(fd6_box* b, const double* lnrho, const double* ux, const dou
             return import_host<T>(b, src);
         });
         if (rc) return rc;
-        rc = reset_w(b);
-        if (rc) return rc;
         HIPCHK(b, hipStreamSynchronize(b->stream));
         b->have_fields = true;
         return FD6_OK;
@@ -1419,8 +1405,6 @@ int fd6_init_fields_device(fd6_box* b, const double* lnrho, const double* ux, co
             using T = std::remove_pointer_t<decltype(t)>;
             return import_device<T>(b, src);
         });
-        if (rc) return rc;
-        rc = reset_w(b);
         if (rc) return rc;
         b->have_fields = true;
         return FD6_OK;
@@ -1748,12 +1732,10 @@ int fd6_batch_init_fields(fd6_batch* b, int32_t box, const double* lnrho, const 
     if (!b || box < 0 || box >= b->n || !lnrho || !ux || !uy || !uz) return FD6_EINVAL;
     return guarded(b, [&]() -> int {
         const double* src[4] = {lnrho, ux, uy, uz};
-        int rc = batch_dispatch(b, [&](auto* t, auto* tw) -> int {
+        int rc = batch_dispatch(b, [&](auto* t, auto*) -> int {
             using T = std::remove_pointer_t<decltype(t)>;
-            using TW = std::remove_pointer_t<decltype(tw)>;
             int r = batch_import<T>(b, box, src);
             if (r) return r;
-            HIPCHK(b, launch_zero_w<TW>(b->geom[box], fields_of<TW>(b->w[box].data()), b->stream));
             HIPCHK(b, hipStreamSynchronize(b->stream));
             return FD6_OK;
         });

@@ -130,8 +130,12 @@ hipError_t launch_export(const Geom& g, const T* src, double* dst, long long zbe
 template <typename TW>
 hipError_t launch_export_w(const Geom& g, const TW* src, double* dst, int z0, int nplanes,
                            hipStream_t s);
-template <typename TW>
-hipError_t launch_zero_w(const Geom& g, Fields4<TW> w, hipStream_t s);
+// The whole box at once, between compact device arrays and the state.
+template <typename T>
+hipError_t launch_import4(const Geom& g, const double* const src[4], Fields4<T> dst,
+                          hipStream_t s);
+template <typename T>
+hipError_t launch_export4(const Geom& g, Fields4<T> src, double* const dst[4], hipStream_t s);
 
 // Kernel shape left to the launcher (auto_shape, by the box's size).
 constexpr int kAutoTile = -1;
