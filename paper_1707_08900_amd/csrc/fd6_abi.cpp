@@ -350,6 +350,14 @@ Coef<T> make_coef(const fd6_params& p) {
     double d2[3][4];
     for (int a = 0; a < 3; ++a) {
         for (int k = 0; k < 3; ++k) c.d1[a][k] = T(w1[k] / (60.0 * h[a]));
+        if (sizeof(T) == 4) {
+            // the smaller weights take up the largest one's rounding error e, so that
+            // the first and third moments stay those of the stencil: a derivative off
+            // by 3e-8 everywhere would shift every wave's phase in every step
+            const double e = (double)c.d1[a][0] - w1[0] / (60.0 * h[a]);
+            c.d1[a][1] = T(w1[1] / (60.0 * h[a]) - 0.8 * e);
+            c.d1[a][2] = T((0.5 / h[a] - (double)c.d1[a][0] - 2.0 * (double)c.d1[a][1]) / 3.0);
+        }
         for (int k = 0; k < 4; ++k) {
             d2[a][k] = w2[k] / (180.0 * h[a] * h[a]);
             c.d2[a][k] = T(d2[a][k]);
@@ -387,7 +395,12 @@ Coef<T> make_coef(const fd6_params& p) {
     // more than about a unit in its last place.
     // (FP64 sweeps use exact integers times entry 3 instead.)
     auto centre = [](const T* x, const T* y, T* z) {
-        if (sizeof(T) == 8) return T(-490.0 * ((double)x[3] + (double)y[3] + (double)z[3]));
+        if (sizeof(T) == 8) {
+            const long double s = (long double)x[3] + y[3] + z[3];
+            const T k = T(-490.0L * s);
+            z[3] = T(z[3] - (s + (long double)k / 490.0L));
+            return k;
+        }
         auto left = [&](double k) {
             double s = k;
             for (const T* w : {x, y, static_cast<const T*>(z)})

@@ -222,7 +222,10 @@ inline int sweep_block_width(int ntx, int nty, int tx, int ty, int per_xcd) {
 // many workgroups of the kernel the device holds at once.  The automatic
 // choice minimises (rounds of resident workgroups) x (planes swept per chunk,
 // including the 6 re-read planes), i.e. it prefers long chunks unless they
-// leave compute units idle.
+// leave compute units idle.  Chunks under 8 planes serve small boxes, where one
+// round of workgroups does not fill the device (a plane of such a chunk costs
+// 1.0 us in FP32, the refill and the launch 7 us: 32^3, ms per step with
+// diagnostics, 32 x 8 tiles: 0.049 with 8 planes, 0.037 with 4, 0.031 with 2).
 inline SweepGrid sweep_grid(const Geom& g, int tx, int ty, int zchunk, int resident) {
     SweepGrid s;
     s.ntx = (g.nx + tx - 1) / tx;
@@ -234,7 +237,7 @@ inline SweepGrid sweep_grid(const Geom& g, int tx, int ty, int zchunk, int resid
     } else {
         const long long res = resident > 0 ? resident : 1;
         long long best = -1;
-        for (int c = 1; c <= (g.nz + 7) / 8; ++c) {
+        for (int c = 1; c <= g.nz && (c <= (g.nz + 7) / 8 || tiles * c <= res); ++c) {
             const long long len = (g.nz + c - 1) / c;
             const long long cost = ((tiles * c + res - 1) / res) * (len + 2 * kR);
             if (best < 0 || cost < best) best = cost, nch = c;
@@ -393,7 +396,9 @@ struct AutoShape {
 };
 template <typename T, typename TW, int VS, bool P19>
 AutoShape auto_shape(const Geom& g, int zchunk) {
-    constexpr bool pd1 = sizeof(T) == 8 || P19;  // (one plane ahead: 1-3% in 19-point FP32)
+    // one plane ahead where two do not pay (1-3% in 19-point FP32, 0.7% with the FP64
+    // register)
+    constexpr bool pd1 = sizeof(T) == 8 || P19 || sizeof(TW) == 8;
     constexpr int wide = pd1 ? 2 : 6, narrow = pd1 ? 4 : 8;
     const int cus = device_cus();
     auto grid = [&](int tile) {
