@@ -226,7 +226,11 @@ inline int sweep_block_width(int ntx, int nty, int tx, int ty, int per_xcd) {
 // round of workgroups does not fill the device (a plane of such a chunk costs
 // 1.0 us in FP32, the refill and the launch 7 us: 32^3, ms per step with
 // diagnostics, 32 x 8 tiles: 0.049 with 8 planes, 0.037 with 4, 0.031 with 2).
-inline SweepGrid sweep_grid(const Geom& g, int tx, int ty, int zchunk, int resident) {
+// most > 0: the automatic choice stays within so many workgroups where it can (the
+// fused diagnostics have a slot each; 704^3 FP32 with 32 x 8 tiles in 5 chunks is past
+// them, and the separate pass costs 1.48 of the step's 11.4 ms).
+inline SweepGrid sweep_grid(const Geom& g, int tx, int ty, int zchunk, int resident,
+                            int most = 0) {
     SweepGrid s;
     s.ntx = (g.nx + tx - 1) / tx;
     s.nty = (g.ny + ty - 1) / ty;
@@ -238,6 +242,7 @@ inline SweepGrid sweep_grid(const Geom& g, int tx, int ty, int zchunk, int resid
         const long long res = resident > 0 ? resident : 1;
         long long best = -1;
         for (int c = 1; c <= g.nz && (c <= (g.nz + 7) / 8 || tiles * c <= res); ++c) {
+            if (most > 0 && c > 1 && tiles * c > most) break;
             const long long len = (g.nz + c - 1) / c;
             const long long cost = ((tiles * c + res - 1) / res) * (len + 2 * kR);
             if (best < 0 || cost < best) best = cost, nch = c;
@@ -384,6 +389,12 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 //    0.035 / 0.036, 96^3 0.062 / 0.052, 128^3 0.085 / 0.083, 256^3 0.520 / 0.508,
 //    384^3 1.86 / 1.78, 640^3 8.40 / 7.98.  Whole columns in more than one round
 //    are the exception (512^3: 4.11 / 4.21); in two chunks they are not (4.03).
+//    There substeps 2 and 3, which read two state sets and are bound by HBM, take wide
+//    columns if those need no more plane steps, one plane ahead with the diagnostics
+//    (the step in ms, all narrow in two chunks / substep 1 only: 512^3 4.04 / 3.93, 300
+//    x 512 x 512 2.41 / 2.33; in boxes that are swept in chunks anyway a change of shape
+//    between the substeps costs more than it gives: 576^3 5.78 / 5.80, 640^3 7.85 /
+//    7.90).
 //  * Otherwise wide, whose halo costs less where a cell's fields lie apart or the
 //    state is twice as large (FP32 one array per field 256^3 0.569 / 0.619, FP64
 //    512^3 7.55 / 8.11, 19-point FP32 256^3 0.759 / 0.840), unless the box is no
@@ -395,7 +406,7 @@ struct AutoShape {
     int tile, zchunk;
 };
 template <typename T, typename TW, int VS, bool P19>
-AutoShape auto_shape(const Geom& g, int zchunk) {
+AutoShape auto_shape(const Geom& g, int zchunk, int s, bool red, bool forced) {
     // one plane ahead where two do not pay (1-3% in 19-point FP32, 0.7% with the FP64
     // register)
     constexpr bool pd1 = sizeof(T) == 8 || P19 || sizeof(TW) == 8;
@@ -409,6 +420,13 @@ AutoShape auto_shape(const Geom& g, int zchunk) {
     const int rn = (n.blocks + 2 * cus - 1) / (2 * cus);
     if (VS == 4 && std::is_same_v<T, float> && std::is_same_v<TW, float>) {
         const bool columns = zchunk == 0 && rn > 1 && n.zlen >= g.nz;
+        if (columns && s > 1) {
+            const int tile = red ? 2 : forced ? wide : 10;
+            const SweepGrid w = grid(tile);
+            if (((w.blocks + cus - 1) / cus) * (long long)(w.zlen + 2 * kR) <=
+                rn * (long long)(n.zlen + 2 * kR))
+                return AutoShape{tile, zchunk};
+        }
         return AutoShape{narrow, columns ? (g.nz + 1) / 2 : zchunk};
     }
     if (g.nx <= kTiles[narrow].tx) return AutoShape{narrow, zchunk};

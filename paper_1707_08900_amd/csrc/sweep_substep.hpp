@@ -1109,7 +1109,8 @@ hipError_t launch_substep55_vs(const Geom& g, Fields4<T> in, Fields4<T> out, Fie
         return frc ? rhs(std::true_type{}) : rhs(std::false_type{});
     }
     if (tile == kAutoTile) {
-        const AutoShape a = auto_shape<T, TW, VS, false>(g, zchunk);
+        const AutoShape a =
+            auto_shape<T, TW, VS, false>(g, zchunk, s, s == 3 && partials, frc != nullptr);
         tile = a.tile;
         zchunk = a.zchunk;
     }
@@ -1128,7 +1129,8 @@ hipError_t launch_substep55_vs(const Geom& g, Fields4<T> in, Fields4<T> out, Fie
                 using K = K55<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, VS, FRC>;
                 using KR = KRed<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, VS, FRC>;
                 const int res = resident_blocks<K::template at<2>::fn>(k.tx * k.ty);
-                const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res);
+                const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res,
+                                                s == 3 && partials ? part_cap : 0);
                 // fuse only where the extra accumulators cost no occupancy
                 static const bool fuse_ok = [] {
                     int a = 0, b = 0;
@@ -1197,7 +1199,8 @@ hipError_t launch_substep19(const Geom& g, Fields4<T> in, Fields4<T> out, Fields
         return frc ? rhs(std::true_type{}) : rhs(std::false_type{});
     }
     if (tile == kAutoTile) {
-        const AutoShape a = auto_shape<T, TW, 1, true>(g, zchunk);
+        const AutoShape a =
+            auto_shape<T, TW, 1, true>(g, zchunk, s, s == 3 && partials, frc != nullptr);
         tile = a.tile;
         zchunk = a.zchunk;
     }
@@ -1212,7 +1215,8 @@ hipError_t launch_substep19(const Geom& g, Fields4<T> in, Fields4<T> out, Fields
                 using KR = K19Red<T, TW, k.tx, k.ty, kPd<T, k.pd>, k.nt, FRC>;
                 const int blk = k.tx * k.ty;
                 const int res = resident_blocks<K::template at<2>::fn>(blk);
-                const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res);
+                const SweepGrid sg = sweep_grid(g, k.tx, k.ty, zchunk, res,
+                                                s == 3 && partials ? part_cap : 0);
                 // fuse only where the extra accumulators cost no occupancy
                 if (s == 3 && partials && nparts && sg.blocks <= part_cap &&
                     resident_blocks<KR::fn>(blk) >= resident_blocks<K::template at<3>::fn>(blk)) {

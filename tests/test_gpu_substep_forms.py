@@ -82,9 +82,11 @@ def test_the_right_hand_side_leaves_a_run_alone(fd6, precision, layout):
 
 # Edges where the unset shape's rule turns: one narrow tile and one cell more, a
 # wide tile's last column nearly empty, fewer planes than one chunk of 8, chunks
-# down to one plane, and a box with more tiles than the device holds at once.
+# down to one plane, a box with more tiles than the device holds at once, and one of
+# whole columns in several rounds (wide ones from substep 2 on in the FP32 array of
+# structures).
 @pytest.mark.parametrize("shape", [(6, 8, 32), (7, 9, 33), (13, 75, 65), (32, 32, 32),
-                                   (41, 50, 150), (18, 300, 420)])
+                                   (41, 50, 150), (18, 300, 420), (8, 264, 1056)])
 @pytest.mark.parametrize("precision,variant,layout", [
     ("fp32", "55p", "aos"), ("fp32", "55p", "soa"), ("fp32", "19p", "soa"),
     ("fp64", "55p", "aos"), ("fp64", "19p", "soa"), ("fp32_acc64", "55p", "aos")])
