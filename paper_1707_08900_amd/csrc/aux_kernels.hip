@@ -133,14 +133,15 @@ __global__ __launch_bounds__(256) void transfer4_kernel(Geom g, Fields4<T> f, Fi
 
 template <typename TW>
 __global__ __launch_bounds__(256) void export_w_kernel(Geom g, const TW* __restrict__ src,
-                                                       double* __restrict__ dst, long long count) {
+                                                       double* __restrict__ dst, long long count,
+                                                       int stride) {
     const long long e0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     for (long long e = e0; e < count; e += (long long)gridDim.x * blockDim.x) {
         long long r = e / g.nx;
         int i = (int)(e - r * g.nx);
         int j = (int)(r % g.ny);
         long long k = r / g.ny;
-        dst[e] = (double)src[(k * g.wplane + (long long)j * g.wpx + i) * g.vs];
+        dst[e] = (double)src[(k * g.wplane + (long long)j * g.wpx + i) * stride];
     }
 }
 
@@ -285,8 +286,9 @@ hipError_t launch_export_w(const Geom& g, const TW* src, double* dst, int z0, in
                            hipStream_t s) {
     // planes [z0, z0 + nplanes) of the compact register, to dst[0 ..)
     const long long n = (long long)g.nx * g.ny * nplanes;
+    const int stride = g.vs == 4 && sizeof(TW) == 8 ? 2 : g.vs;  // doubles lie in pairs
     hipLaunchKernelGGL(export_w_kernel<TW>, dim3(grid_for(n, 256)), dim3(256), 0, s, g,
-                       src + (long long)z0 * g.wplane * g.vs, dst, n);
+                       src + (long long)z0 * g.wplane * stride, dst, n, stride);
     return hipGetLastError();
 }
 

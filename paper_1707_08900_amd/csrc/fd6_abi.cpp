@@ -225,7 +225,12 @@ int make_plan(const fd6_desc* d, Plan* p) {
             p->off_state[s][q] =
                 aos ? off + 4 * s * fbytes + (q + 3) % 4 * p->tsize : off + (4 * s + q) * fbytes;
     off += 8 * fbytes;
-    for (int q = 0; q < 4; ++q) p->off_w[q] = aos ? off + (q + 3) % 4 * p->wsize : off + q * wbytes;
+    for (int q = 0; q < 4; ++q) {
+        const size_t pos = (q + 3) % 4;  // within a point; doubles as pairs in two arrays
+        p->off_w[q] = !aos              ? off + q * wbytes
+                      : p->wsize == 8 ? off + pos / 2 * 2 * wbytes + pos % 2 * p->wsize
+                                      : off + pos * p->wsize;
+    }
     off += 4 * wbytes;
     p->off_div = off;
     if (d->variant == FD6_19P) off += fbytes;

@@ -327,7 +327,11 @@ __device__ __forceinline__ void load_prev(SweepRegs<T, TW, NH>& R, const Ctx& X,
         else
             return VS == 4 ? out.f[1] : out.f[0] + ((f + 1) & 3) * g.felems;
     };
-    if constexpr (VS == 4) {
+    if constexpr (REG && kWPairs<TW, VS>) {
+        const P* const p = base(0) + 2 * at;
+        bload_pairs<CP>(R.wq[RS], plane_rsrc(p, bytes), plane_rsrc(p + 2 * g.wfelems, bytes),
+                        lane);
+    } else if constexpr (VS == 4) {
         bload_point<CP>(R.wq[RS], plane_rsrc(base(0) + 4 * at, bytes), lane);
     } else {
 #pragma unroll
@@ -702,9 +706,14 @@ __device__ __forceinline__ void sweep_step(int t, int nplanes, int zb, SweepRegs
         if constexpr (VS == 4 && TB != 1) {
             if constexpr (S >= 1)
                 bstore_point<CP>(vout, plane_rsrc(out.f[1] + 4 * ocorner, ob), X.lane_o);
-            if constexpr (WOUT)
+            if constexpr (WOUT && kWPairs<TW, VS>) {
+                TW* const p = w.f[1] + 2 * (long long)o * g.wplane;
+                bstore_pairs<CP>(wout, plane_rsrc(p, wb), plane_rsrc(p + 2 * g.wfelems, wb),
+                                 X.lane_w);
+            } else if constexpr (WOUT) {
                 bstore_point<CP>(wout, plane_rsrc(w.f[1] + 4 * (long long)o * g.wplane, wb),
                                  X.lane_w);
+            }
         }
         // FP64 diagnostics of the new state, from the values just stored (the
         // same per-point quantities as the standalone reduction); without a
