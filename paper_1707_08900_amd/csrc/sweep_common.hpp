@@ -437,7 +437,15 @@ AutoShape auto_shape(const Geom& g, int zchunk, int s, bool red, bool forced) {
     // one plane ahead where two do not pay (1-3% in 19-point FP32, 0.7% with the FP64
     // register)
     constexpr bool pd1 = sizeof(T) == 8 || P19 || sizeof(TW) == 8;
-    constexpr int wide = pd1 ? 2 : 6, narrow = pd1 ? 4 : 8;
+    // cached stores for FP64 points, whose 32 bytes go out in two halves that the cache
+    // merges (ms per step with diagnostics, cached / past the caches: 512^3 7.33 / 7.47,
+    // 256^3 0.920 / 0.942, 400 x 300 x 500 3.50 / 3.58, 192^3 0.446 / 0.438)
+    constexpr bool halves = sizeof(T) == 8 && VS == 4;
+    // ... and two planes ahead in the diagnostics sweep beside the FP64 register (the
+    // step at 256^3 0.705 / 0.720 with one, 500 x 300 x 400 2.74 / 2.82; without
+    // diagnostics 512^3 5.81 / 5.70)
+    const int wide = halves ? 11 : !pd1 || (red && VS == 4 && !P19) ? 6 : 2;
+    constexpr int narrow = halves ? 13 : pd1 ? 4 : 8;
     const int cus = device_cus();
     auto grid = [&](int tile) {
         const int tx = kTiles[tile].tx, ty = kTiles[tile].ty;
