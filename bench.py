@@ -41,12 +41,15 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 # Algorithmic HBM bytes per grid-point update (one full RK3 step), the
-# method's own minimum: state read once per substep, w read when alpha != 0
-# and written when it is needed again, output written once; ghosts and halo
-# re-reads excluded.  55-point: 40 field accesses per step (16 of them to w);
-# 19-point: 76 (28 to w).
-ALG_BYTES = {("55p", "fp32"): 160, ("55p", "fp64"): 320, ("55p", "fp32_acc64"): 224,
-             ("19p", "fp32"): 304, ("19p", "fp64"): 608, ("19p", "fp32_acc64"): 416}
+# method's own minimum: each substep reads its input state and, from the
+# second on, the state before it (the RK3 register is formed from the two),
+# and writes its output once; ghosts and halo re-reads excluded.  55-point: 32
+# field accesses per step; 19-point: 47 (each substep also reads the velocity
+# and writes the divergence, which the main sweep reads).  With the FP64
+# register that is held in memory, read and written as an FP64 field instead
+# of the state before.
+ALG_BYTES = {("55p", "fp32"): 128, ("55p", "fp64"): 256, ("55p", "fp32_acc64"): 224,
+             ("19p", "fp32"): 188, ("19p", "fp64"): 376, ("19p", "fp32_acc64"): 284}
 LAUNCHES = {"55p": 3, "19p": 6}  # substep kernel launches per step
 PREC_TAG = {"fp32": "f32", "fp64": "f64", "fp32_acc64": "f32w64"}
 DTYPE = {"fp32": "f32", "fp64": "f64", "fp32_acc64": "f32 state, f64 RK3 register"}
@@ -505,7 +508,7 @@ def main():
         f"graph replay {head['graph_ms_per_step']:.3f} ms/step")
 
     # dominant kernel: the fused 55-point substep kernel (19-point: the
-    # average of its two passes)
+    # average of its two sweeps)
     alg_per_launch = n ** 3 * ALG_BYTES[(var, prec)] / (2 if a.fused12 else LAUNCHES[var])
     avg_launch_s = hx["kms"] * 1e-3 / hx["klaunch"]
     achieved = alg_per_launch / avg_launch_s / 1e9
@@ -516,7 +519,7 @@ def main():
                 "kernel": ("substep55_fused12 + substep55_sweep_red (average per launch)"
                            if a.fused12 else
                            f"substep55_sweep (fused RHS + RK3, {a.layout} layout)" if var == "55p"
-                           else "substep19_pass1 / substep19_pass2 (average per launch)"),
+                           else "substep19_div / substep19_sweep (average per launch)"),
                 "avg_launch_us": round(avg_launch_s * 1e6, 2), "launches": hx["klaunch"],
                 "alg_bytes_per_launch": alg_per_launch,
                 "ghost_fill_us_per_launch": round(hx["gms"] * 1e3 / max(hx["glaunch"], 1), 2),

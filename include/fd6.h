@@ -130,7 +130,8 @@ int fd6_set_stream(fd6_box *box, void *stream);
 int fd6_set_params(fd6_box *box, const fd6_params *params);
 
 /* Load the state from host FP64 arrays (converted to the storage precision
- * with round-to-nearest-even); resets the RK3 register. Synchronises. */
+ * with round-to-nearest-even); a following step starts a new RK3 step.
+ * Synchronises. */
 int fd6_init_fields(fd6_box *box, const double *lnrho, const double *ux, const double *uy,
                     const double *uz);
 
@@ -244,11 +245,11 @@ int fd6_set_forcing(fd6_box *box, const fd6_forcing *f);
 /* Temporal blocking of substeps 1 and 2 (the paper's discussion of Sec. 7
  * proposes it): with enable != 0 every step runs substeps 1 and 2 as ONE
  * launch in which a workgroup sweeps substep 1 over its 16 x 16 output tile
- * and a 3-column ring, keeps that substep's new state and RK3 register on
- * chip (LDS), and sweeps substep 2 of the tile from them; substep 3 follows
- * as usual.  The substep-1 state and register never reach HBM (112 -> 48
- * bytes per point for the two substeps, FP32), at the price of substep 1 on
- * 22 x 22 / (16 x 16) = 1.9 times the columns.  Results are bit for bit
+ * and a 3-column ring, keeps that substep's new state on chip (LDS), and
+ * sweeps substep 2 of the tile from it; substep 3 follows as usual.  Substep 2
+ * reads nothing from HBM (80 -> 48 bytes per point for the two substeps, FP32;
+ * a copy of 32 then puts the substep-1 state where substep 3 reads it), at the
+ * price of substep 1 on 22 x 22 / (16 x 16) = 1.9 times the columns.  Results are bit for bit
  * those of the plain launches.  An experimental schedule, off by default:
  * on MI355X at 512^3 the plain launches are 8.5 times faster (the fused
  * kernel spills the registers of its two column states to scratch memory
@@ -332,7 +333,7 @@ int fd6_batch_destroy(fd6_batch *batch);
  * Uploads the device descriptors (synchronises). */
 int fd6_batch_set_params(fd6_batch *batch, const fd6_params *per_box);
 
-/* State of box `box` from host FP64 arrays; resets its RK3 register. */
+/* State of box `box` from host FP64 arrays. */
 int fd6_batch_init_fields(fd6_batch *batch, int32_t box, const double *lnrho, const double *ux,
                           const double *uy, const double *uz);
 
