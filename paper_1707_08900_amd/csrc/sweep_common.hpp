@@ -427,8 +427,9 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 //    512^3 7.55 / 8.11, 19-point FP32 256^3 0.759 / 0.840), unless the box is no
 //    wider than the narrow tile (32^3: FP32 0.032 / 0.028, FP64 0.038 / 0.034) or
 //    the wide tile needs over 6/5 of the narrow one's plane steps (FP64 96^3: 16
-//    against 13 per workgroup, 0.093 / 0.086; 150 x 75 x 101: 19 against 17, 0.116
-//    / 0.139).
+//    against 13 per workgroup, 0.093 / 0.086), 3/2 with an FP32 state in one array per
+//    field, whose narrow tiles spend more on their halo (150 x 75 x 101: 19 against 17,
+//    0.116 / 0.139; 19-point 78 x 84 x 150: 20 against 16, 0.138 / 0.167).
 struct AutoShape {
     int tile, zchunk;
 };
@@ -468,7 +469,8 @@ AutoShape auto_shape(const Geom& g, int zchunk, int s, bool red, bool forced) {
     const SweepGrid w = grid(wide);
     const int rw = (w.blocks + cus - 1) / cus;
     const long long cn = (long long)rn * (n.zlen + 2 * kR), cw = (long long)rw * (w.zlen + 2 * kR);
-    return AutoShape{6 * cn < 5 * cw ? narrow : wide, zchunk};
+    const bool fewer = sizeof(T) == 4 && VS == 1 ? 3 * cn < 2 * cw : 6 * cn < 5 * cw;
+    return AutoShape{fewer ? narrow : wide, zchunk};
 }
 
 // Calls f(std::integral_constant<int, tile>) so that f can use kTiles[tile]
