@@ -249,13 +249,14 @@ int fd6_set_forcing(fd6_box *box, const fd6_forcing *f);
  * sweeps substep 2 of the tile from it; substep 3 follows as usual.  Substep 2
  * reads nothing from HBM (80 -> 48 bytes per point for the two substeps, FP32;
  * a copy of 32 then puts the substep-1 state where substep 3 reads it), at the
- * price of substep 1 on 22 x 22 / (16 x 16) = 1.9 times the columns.  Results are bit for bit
- * those of the plain launches.  An experimental schedule, off by default:
- * on MI355X at 512^3 the plain launches are 8.5 times faster (the fused
- * kernel spills the registers of its two column states to scratch memory
- * and does 1.7 times their arithmetic).  FP32 precision
- * and the 55-point method only (FD6_EUNSUPPORTED otherwise); ignored while a
- * force is set.  Drops captured steps when it changes. */
+ * price of substep 1 on 22 x 22 / (16 x 16) = 1.9 times the columns.  Results are
+ * bit for bit those of the plain launches.  An experimental schedule, off by
+ * default: on MI355X at 512^3 the two launches it replaces are 3.9 times faster
+ * (1.06 + 1.35 ms against 7.7 for the fused kernel, which holds two column
+ * states and spills 40-57 registers of them to scratch memory, + 1.6 for the copy).  FP32
+ * precision and the 55-point method only (FD6_EUNSUPPORTED otherwise); ignored
+ * while a force is set and with kernel shape 0, whose kernels keep the register
+ * elsewhere.  Drops captured steps when it changes. */
 int fd6_set_fused_substeps(fd6_box *box, int32_t enable);
 
 /* Graph mode (Algorithm 2 as one HIP graph per step): with enable != 0,

@@ -536,10 +536,15 @@ int force_sync(fd6_box* b) {
 }
 
 // Whether a step runs substeps 1 and 2 as one fused launch (fd6_set_fused_substeps).
-bool fused_step(const fd6_box* b) { return b->fused12 && !b->force_on; }
+// Not with the direct kernels: their substep 3 takes its register from w, where the
+// fused launch leaves the substep-1 state.
+bool fused_step(const fd6_box* b) {
+    return b->fused12 && !b->force_on && !substep55_reads_ghosts(b->run_tile());
+}
 
-// Substeps 1 and 2 in one launch: state[cur] -> state[cur ^ 1], w holding
-// the substep-2 register (one in/out swap instead of two).
+// Substeps 1 and 2 in one launch: state[cur] -> state[cur ^ 1], the substep-1 state
+// by way of w into state[cur], where substep 3 forms its register from it (one in/out
+// swap instead of two).
 template <typename T, typename TW>
 int fused12_substeps(fd6_box* b) {
     if constexpr (!std::is_same<T, float>::value || !std::is_same<TW, float>::value) {

@@ -1,0 +1,95 @@
+"""The library's host runtime (csrc/fd6_abi.cpp) on the CPU: compiled with the
+host compiler against a simulated device (host_runtime.cpp), whose log says
+which kernels a call would launch, with which shape, and whose clock gives the
+tuners their timings."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_1707_08900_amd as fd6
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_1707_08900_amd", "csrc")
+ROCM_INCLUDE = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")
+AUTO = -1
+
+
+@pytest.fixture(scope="module")
+def rt(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if not cxx or not os.path.isdir(ROCM_INCLUDE):
+        pytest.skip("no host C++ compiler or no HIP headers")
+    so = str(tmp_path_factory.mktemp("rt") / "libruntime.so")
+    # the simulated HIP functions bind inside the library whatever else is loaded
+    subprocess.run([cxx, "-O1", "-std=c++17", "-shared", "-fPIC", "-Wl,-Bsymbolic",
+                    "-D__HIP_PLATFORM_AMD__", "-D_GLIBCXX_ASSERTIONS", f"-I{ROCM_INCLUDE}",
+                    f"-I{CSRC}", os.path.join(HERE, "host_runtime.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so, mode=os.RTLD_LOCAL | os.RTLD_NOW)
+    lib.hr_log.restype = ctypes.c_char_p
+    lib.hr_cost.argtypes = [ctypes.c_int, ctypes.c_double]
+    lib.hr_chunk.argtypes = [ctypes.c_int, ctypes.c_double]
+    return lib
+
+
+class SimBox:
+    def __init__(self, lib, shape=(40, 24, 36), precision="fp32", variant="55p", layout="soa"):
+        lib.hr_reset()
+        self.lib = lib
+        nz, ny, nx = shape
+        d = fd6.Fd6Desc(nx, ny, nz, fd6.PRECISIONS[precision], fd6.VARIANTS[variant],
+                        fd6.LAYOUTS[layout])
+        need = ctypes.c_size_t()
+        assert lib.fd6_workspace_bytes(ctypes.byref(d), ctypes.byref(need)) == 0
+        self.h = ctypes.c_void_p()
+        assert lib.fd6_create(ctypes.byref(d), ctypes.c_void_p(1 << 40), need, None,
+                              ctypes.byref(self.h)) == 0
+        p = fd6.Fd6Params(1e-3, 1.0, 0.1, 0.1, 0.1, 0.01)
+        assert lib.fd6_set_params(self.h, ctypes.byref(p)) == 0
+        f = [ctypes.c_void_p((1 << 41) + i) for i in range(4)]  # the import is simulated
+        assert lib.fd6_init_fields_device(self.h, *f) == 0
+
+    def step(self, n=1):
+        """Kernels of n steps: ('substep', substep, shape, z-chunk) or (name,)."""
+        self.lib.hr_log()
+        assert self.lib.fd6_rk3_step(self.h, n) == 0
+        return self.log()
+
+    def log(self):
+        rows = [r.split() for r in self.lib.hr_log().decode().splitlines()]
+        return [(r[0], *map(int, r[1:])) for r in rows]
+
+    def schedule(self):
+        t, z = ctypes.c_int32(), ctypes.c_int32()
+        assert self.lib.fd6_get_schedule(self.h, ctypes.byref(t), ctypes.byref(z)) == 0
+        return t.value, z.value
+
+    def close(self):
+        self.lib.fd6_destroy(self.h)
+
+
+def plain(tile, zchunk=0):
+    return [("substep", s, tile, zchunk) for s in (1, 2, 3)]
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("fused_first", [False, True])
+def test_the_direct_kernels_run_plain_launches_where_substeps_are_fused(rt, fused_first, graph):
+    """Shape 0 keeps its register in memory, which the fused substeps do not
+    leave there: with it every step is three plain launches, eager and
+    captured, in whichever order the two were asked for; another shape brings
+    the fused launch back."""
+    b = SimBox(rt)
+    assert rt.fd6_set_graph(b.h, graph) == 0
+    for fused in ([True, False] if fused_first else [False, True]):
+        assert (rt.fd6_set_fused_substeps(b.h, 1) if fused else rt.fd6_set_tile(b.h, 0)) == 0
+    for _ in range(3):  # each state set and a replay
+        got = [k for k in b.step() if k[0] in ("substep", "fused12")]
+        assert got == plain(0) or (graph and not got)
+    assert rt.fd6_set_tile(b.h, 6) == 0
+    names = [k[:2] for k in b.step() if k[0] in ("substep", "fused12")]
+    assert names == [("fused12",), ("substep", 3)]
+    b.close()
