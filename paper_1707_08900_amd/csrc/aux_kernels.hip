@@ -1,5 +1,6 @@
 // Auxiliary kernels: periodic ghost fill, FP64 import/export of the state,
 // and the deterministic FP64 global reductions.
+#include "div_const.hpp"
 #include "exp_fp64.hpp"
 #include "fd6_internal.hpp"
 
@@ -85,47 +86,55 @@ __global__ __launch_bounds__(256) void export_kernel(Geom g, const T* __restrict
 }
 
 // All four fields of the whole box between compact FP64 device arrays and the
-// state, in one pass: a workgroup takes 4 rows at a time, a wave one row, so the
-// index arithmetic is one division per row, and a point of the array of
-// structures is one 16-byte access (two in FP64) instead of four strided ones in
-// four passes, each of which fetched every line.  Bound by HBM: 48 bytes per point
-// in FP32 (512^3 array of structures: export 2.4 -> 1.3 ms, import 4.1 -> 1.4 ms).
+// state, in one pass over the points, so that a point of the array of structures is
+// one 16-byte access (two in FP64) instead of four strided ones in four passes, each
+// of which fetched every line.  Bound by HBM: 48 bytes per point in FP32 (512^3 array
+// of structures, one pass per field / now: export 2.39 / 1.10 ms, import 4.92 / 1.16).
+// Points are numbered as the compact arrays hold them, 256 or 512 in a row to a
+// workgroup.  A wave to a row left its lanes idle where rows are short or end in a
+// short piece (export, ms, one pass per field / wave to a row / now: 580 x 271 x 6 FP64
+// one array per field 0.023 / 0.040 / 0.017, 865 x 207 x 83 0.217 / 0.278 / 0.167).
 template <typename T>
 struct Point4 {
     typedef T type __attribute__((ext_vector_type(4)));
 };
+// Points of a workgroup: an import's partly written lines are fewer with 512 (128^3
+// FP32 array of structures 18.2 / 15.4 us), an export's loads lie nearer with 256
+// (256^3 FP32 one array per field 0.116 ms, 0.168 with 1024).
+template <bool EXPORT>
+constexpr unsigned kSpan = EXPORT ? 256 : 512;
 template <typename T, int VS, bool EXPORT>
-__global__ __launch_bounds__(256) void transfer4_kernel(Geom g, Fields4<T> f, Fields4<double> c) {
-    const int lane = threadIdx.x & 63;
-    const long long rows = (long long)g.ny * g.nz;
-    for (long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows;
-         r += (long long)gridDim.x * 4) {
-        const int k = (int)(r / g.ny), j = (int)(r - (long long)k * g.ny);
-        const long long e0 = g.origin + (long long)k * g.plane + (long long)j * g.px;
-        const long long d0 = r * g.nx;
-        for (int i = lane; i < g.nx; i += 64) {
-            if constexpr (VS == 4) {  // ux, uy, uz, lnrho
-                using P = typename Point4<T>::type;
-                P* const p = reinterpret_cast<P*>(f.f[1]) + (e0 + i);
-                if constexpr (EXPORT) {
-                    const P v = *p;
+__global__ __launch_bounds__(256) void transfer4_kernel(Geom g, Fields4<T> f, Fields4<double> c,
+                                                        unsigned count, DivConst nx,
+                                                        DivConst ny) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        __builtin_nontemporal_store((double)v[(q + 3) & 3], c.f[q] + d0 + i);
-                } else {
-                    P v;
+    for (unsigned s = 0; s < kSpan<EXPORT>; s += 256) {
+        const unsigned e = blockIdx.x * kSpan<EXPORT> + s + threadIdx.x;
+        if (e >= count) return;
+        const unsigned r = e / nx, k = r / ny;
+        const int i = (int)(e - r * nx.d), j = (int)(r - k * ny.d);
+        const long long at = g.origin + (long long)k * g.plane + (long long)j * g.px + i;
+        if constexpr (VS == 4) {  // ux, uy, uz, lnrho
+            using P = typename Point4<T>::type;
+            P* const p = reinterpret_cast<P*>(f.f[1]) + at;
+            if constexpr (EXPORT) {
+                const P v = *p;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[(q + 3) & 3] = (T)c.f[q][d0 + i];
-                    *p = v;
-                }
+                for (int q = 0; q < 4; ++q)
+                    __builtin_nontemporal_store((double)v[(q + 3) & 3], c.f[q] + e);
             } else {
+                P v;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if constexpr (EXPORT)
-                        __builtin_nontemporal_store((double)f.f[q][e0 + i], c.f[q] + d0 + i);
-                    else
-                        f.f[q][e0 + i] = (T)c.f[q][d0 + i];
-                }
+                for (int q = 0; q < 4; ++q) v[(q + 3) & 3] = (T)c.f[q][e];
+                *p = v;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (EXPORT)
+                    __builtin_nontemporal_store((double)f.f[q][at], c.f[q] + e);
+                else
+                    f.f[q][at] = (T)c.f[q][e];
             }
         }
     }
@@ -294,11 +303,11 @@ hipError_t launch_export_w(const Geom& g, const TW* src, double* dst, int z0, in
 
 template <typename T, bool EXPORT>
 static hipError_t transfer4(const Geom& g, Fields4<T> f, Fields4<double> c, hipStream_t s) {
-    const dim3 grid(grid_for((long long)g.ny * g.nz, 4));
-    if (g.vs == 4)
-        hipLaunchKernelGGL((transfer4_kernel<T, 4, EXPORT>), grid, dim3(256), 0, s, g, f, c);
-    else
-        hipLaunchKernelGGL((transfer4_kernel<T, 1, EXPORT>), grid, dim3(256), 0, s, g, f, c);
+    const long long n = (long long)g.nx * g.ny * g.nz;  // below 2^31, as a field's elements
+    const dim3 grid((unsigned)((n + kSpan<EXPORT> - 1) / kSpan<EXPORT>));
+    const DivConst nx = div_const((unsigned)g.nx), ny = div_const((unsigned)g.ny);
+    auto k = g.vs == 4 ? transfer4_kernel<T, 4, EXPORT> : transfer4_kernel<T, 1, EXPORT>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, g, f, c, (unsigned)n, nx, ny);
     return hipGetLastError();
 }
 
