@@ -44,6 +44,13 @@ const char* hr_log() {
 void hr_cost(int tile, double ms) { g_cost[tile] = ms; }
 void hr_chunk(int zchunk, double factor) { g_chunk[zchunk] = factor; }
 void hr_fail_tile(int tile) { g_fail_tile = tile; }
+// b of the three substeps, c of the last two
+void hr_fp32_factors(double dt, float* f) {
+    const auto r = make_rk<float, float>(dt);
+    for (int s = 0; s < 3; ++s) f[s] = r[s].b;
+    f[3] = r[1].c;
+    f[4] = r[2].c;
+}
 void hr_reset() {
     g_log.str("");
     g_clock = g_capture = 0.0;

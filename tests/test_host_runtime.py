@@ -7,6 +7,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 import paper_1707_08900_amd as fd6
@@ -93,3 +94,39 @@ def test_the_direct_kernels_run_plain_launches_where_substeps_are_fused(rt, fuse
     names = [k[:2] for k in b.step() if k[0] in ("substep", "fused12")]
     assert names == [("fused12",), ("substep", 3)]
     b.close()
+
+
+def factors_by_trial(dt):
+    """Every one of the 243 sets, errors as they are defined (double, in order)."""
+    f32 = np.float32
+    h = float(f32(dt))
+    a, b = (0.0, -5.0 / 9.0, -153.0 / 128.0), (1.0 / 3.0, 15.0 / 16.0, 8.0 / 15.0)
+    exact = [b[0] * h, b[1] * h, b[2] * h, a[1] / (b[0] * h), a[2] / (b[1] * h)]
+    near = [[float(v), float(np.nextafter(v, f32(-np.inf))), float(np.nextafter(v, f32(np.inf)))]
+            for v in map(f32, exact)]
+    k = np.arange(243)
+    v = [np.array(n)[k // 3 ** i % 3] for i, n in enumerate(near)]
+    g = 1.0 + v[3] * v[0]
+    s = v[0] + v[1] * g
+    e1 = (s + v[2] * (1.0 + v[4] * v[1] * g)) / h - 1.0
+    e2 = 2.0 * (v[1] * v[0] + v[2] * (s + v[4] * v[1] * v[0])) / (h * h) - 1.0
+    e3 = 6.0 * v[2] * v[1] * v[0] / (h * h * h) - 1.0
+    e = np.maximum(np.maximum(np.abs(e1), np.abs(e2)), 0.3 * np.abs(e3))
+    best = int(np.argmin(e))  # the first among equals
+    return [float(x[best]) for x in v]
+
+
+def test_fp32_factors_of_a_step_are_those_of_the_whole_search(rt):
+    """The set of rounded RK3 factors found among the few that come near the least
+    error is that of trying all, for time steps of every magnitude and for powers
+    of two and their neighbours, where the errors tie."""
+    rng = np.random.default_rng(5)
+    dts = list(10.0 ** rng.uniform(-14, 14, 400)) + list(10.0 ** rng.uniform(-6, 0, 1500))
+    for e in range(-40, 40, 3):
+        p = np.float32(2.0) ** e
+        dts += [float(p), float(np.nextafter(p, np.float32(0))), float(p) / 3.0]
+    dts += [1.0 / n for n in range(1, 600)]
+    out = (ctypes.c_float * 5)()
+    for dt in dts:
+        rt.hr_fp32_factors(ctypes.c_double(dt), out)
+        assert list(out) == factors_by_trial(dt), dt
