@@ -208,7 +208,8 @@ int fd6_get_schedule(const fd6_box *box, int32_t *tile, int32_t *zchunk);
  * per candidate: call it before the fields of the actual run are set, or set
  * them again afterwards.  cache_path as for fd6_batch_tune (key: device name,
  * grid, precision, method, layout).  FD6_ESTATE before parameters and fields
- * are set.  Synchronises. */
+ * are set.  If a trial fails, the schedule in force before the call is restored
+ * and the failure returned.  Synchronises. */
 int fd6_tune(fd6_box *box, const char *cache_path);
 
 /* The candidates the box's last fd6_tune call timed, in order: kernel shape,

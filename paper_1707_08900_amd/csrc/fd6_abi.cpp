@@ -1658,7 +1658,8 @@ int fd6_tune(fd6_box* b, const char* cache_path) {
             using TW = std::remove_pointer_t<decltype(tw)>;
             EventPair ev;
             HIPCHK(b, ev.create());
-            const bool timing = b->timing;
+            const bool timing = b->timing, was_set = b->shape_set;
+            const int old_tile = b->tile, old_zc = b->zchunk;
             b->timing = false;
             // ms per reducing step of one schedule (one warm-up step first)
             auto trial = [&](int cand, int zc, float* ms) -> int {
@@ -1695,11 +1696,19 @@ int fd6_tune(fd6_box* b, const char* cache_path) {
                     best_ms = ms, best_zc = zc;
             }
             b->timing = timing;
+            if (rc != FD6_OK) {
+                // a failed trial leaves the schedule that was in force before
+                b->drop_graphs();
+                b->shape_set = was_set;
+                b->tile = old_tile;
+                b->zchunk = old_zc;
+                return rc;
+            }
             if (best_tile != b->tile || best_zc != b->zchunk) b->drop_graphs();
             b->tile = best_tile;
             b->zchunk = best_zc;
-            if (rc == FD6_OK && cache_path) write_tune_cache(cache_path, key, best_tile, best_zc);
-            return rc;
+            if (cache_path) write_tune_cache(cache_path, key, best_tile, best_zc);
+            return FD6_OK;
         });
     });
 }

@@ -30,7 +30,7 @@ def rt(tmp_path_factory):
                     "-D__HIP_PLATFORM_AMD__", "-D_GLIBCXX_ASSERTIONS", f"-I{ROCM_INCLUDE}",
                     f"-I{CSRC}", os.path.join(HERE, "host_runtime.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so, mode=os.RTLD_LOCAL | os.RTLD_NOW)
-    lib.hr_log.restype = ctypes.c_char_p
+    lib.hr_log.restype = lib.fd6_last_error.restype = ctypes.c_char_p
     lib.hr_cost.argtypes = [ctypes.c_int, ctypes.c_double]
     lib.hr_chunk.argtypes = [ctypes.c_int, ctypes.c_double]
     return lib
@@ -130,3 +130,26 @@ def test_fp32_factors_of_a_step_are_those_of_the_whole_search(rt):
     for dt in dts:
         rt.hr_fp32_factors(ctypes.c_double(dt), out)
         assert list(out) == factors_by_trial(dt), dt
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("before", [None, (3, 0), (4, 16)])
+@pytest.mark.parametrize("bad", [1, 5, 13])
+def test_a_failed_tuning_leaves_the_box_as_it_was(rt, bad, before, graph):
+    """Whichever candidate fails: the schedule, set or the library's own, and
+    what a step launches or replays are those from before the call."""
+    b = SimBox(rt, precision="fp64")
+    assert rt.fd6_set_graph(b.h, graph) == 0
+    if before:
+        assert rt.fd6_set_tile(b.h, before[0]) == 0 and rt.fd6_set_zchunk(b.h, before[1]) == 0
+    reported = b.schedule()
+    b.step(2)  # both state sets captured
+    rt.hr_fail_tile(bad)
+    assert rt.fd6_tune(b.h, None) == -4
+    assert b"simulated failure" in rt.fd6_last_error(b.h)
+    rt.hr_fail_tile(-100)
+    assert b.schedule() == reported
+    want = plain(*before) if before else plain(AUTO)
+    for _ in range(2):  # (a capture or a launch: nothing recorded by a trial replays)
+        assert [k for k in b.step() if k[0] == "substep"] == want
+    b.close()
