@@ -213,14 +213,23 @@ constexpr bool kInPlaneLds =
 template <typename T, int TX, int TY, int NF>
 constexpr int kInPlaneElems = kInPlaneLds<T, TX, TY, NF> ? 3 * kInPlane * TX * TY : 2;
 // LDS elements of the diagnostics' per-thread accumulators, which join the
-// in-plane values there.
+// in-plane values there where that costs no workgroup: a compute unit holds 512 threads
+// at two waves per SIMD.  Only the FP64 32 x 8 tile of the 19-point method is too full;
+// its accumulators stay in registers (3-9 spilled), and the diagnostics in the sweep,
+// instead of a pass of their own (ms per step with diagnostics, LDS and a pass /
+// registers: 2048 x 6 x 6 0.120 / 0.111, 1024 x 16 x 16 0.123 / 0.112, 96^3 0.141 / 0.136).
 template <typename T, int TX, int TY, int NF>
-constexpr int kRedElems =
-    kInPlaneLds<T, TX, TY, NF> &&
-            sizeof(T) * (2 * NF * SweepShape<T, TX, TY>::FS + (3 * kInPlane + 4) * TX * TY) <=
-                kLdsBytes - 1024
-        ? 4 * TX * TY
-        : 0;
+constexpr int kRedElems = [] {
+    constexpr int most = 512 / (TX * TY);
+    constexpr int base = (int)sizeof(T) *
+                         (2 * NF * SweepShape<T, TX, TY>::FS + 3 * kInPlane * TX * TY);
+    auto held = [](int bytes) {
+        const int n = kLdsBytes / (bytes + 1024);
+        return n < most ? n : most;
+    };
+    const int with = held(base + 4 * TX * TY * (int)sizeof(T));
+    return kInPlaneLds<T, TX, TY, NF> && with > 0 && with == held(base) ? 4 * TX * TY : 0;
+}();
 // Waves per SIMD the register budget is set for.
 constexpr int kMinWaves = 2;
 
