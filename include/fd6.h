@@ -196,23 +196,29 @@ int fd6_set_tile(fd6_box *box, int32_t tile);
  * do not depend on it (bit for bit).  FD6_EINVAL if zchunk < 0. */
 int fd6_set_zchunk(fd6_box *box, int32_t zchunk);
 
-/* The current kernel shape and z-chunk length (set or tuned). */
+/* The kernel shape and z-chunk length that were set or tuned.  Before that, and
+ * where fd6_tune kept the library's own choice, a shape for each substep runs
+ * that no pair names: the answer is then the shape given above, or the fastest
+ * pair the tuner timed, and setting it replaces the library's choice. */
 int fd6_get_schedule(const fd6_box *box, int32_t *tile, int32_t *zchunk);
 
 /* Autotuner of the kernel shape and z-chunk length (a speed choice only):
  * times every z-sweep shape the box's layout takes with the automatic
  * z-chunk, then z-chunk lengths 64, 128, 256 (those below nz) and nz for the
- * fastest shape -- one warm-up and 2 timed steps each, every step with its
+ * fastest shape, before and after them the library's own choice (its faster
+ * trial counts), and the fastest pair once more (which counts against that) --
+ * one warm-up and 2 timed steps each, every step with its
  * FP64 diagnostics as fd6_rk3_step_reduce computes them, HIP events on the
- * box's stream -- and keeps the fastest pair.  Advances the state by 3 steps
- * per candidate: call it before the fields of the actual run are set, or set
- * them again afterwards.  cache_path as for fd6_batch_tune (key: device name,
- * grid, precision, method, layout).  FD6_ESTATE before parameters and fields
- * are set.  If a trial fails, the schedule in force before the call is restored
- * and the failure returned.  Synchronises. */
+ * box's stream -- and keeps the fastest pair, or the library's own choice where
+ * no pair is faster.  Advances the state by 3 steps per trial: call it before
+ * the fields of the actual run are set, or set them again afterwards.
+ * cache_path as for fd6_batch_tune (key: device name, grid, precision, method,
+ * layout).  FD6_ESTATE before parameters and fields are set.  If a trial fails,
+ * the schedule in force before the call is restored and the failure returned.
+ * Synchronises. */
 int fd6_tune(fd6_box *box, const char *cache_path);
 
-/* The candidates the box's last fd6_tune call timed, in order: kernel shape,
+/* The pairs the box's last fd6_tune call timed, in order: kernel shape,
  * z-chunk length and milliseconds per step (the mean of its timed steps).
  * Fills min(cap, count) entries of the three arrays and sets *n = count (0
  * when the last call took a cached choice or no call was made).  cap = 0
@@ -370,7 +376,8 @@ int fd6_batch_set_schedule(fd6_batch *batch, int32_t tile, int32_t zchunk);
  * Advances every box by 36 steps per candidate: call it before the fields of
  * the actual run are set, or set them again afterwards.
  * cache_path (may be NULL) names a text file of "key tile zchunk" lines,
- * keyed by device name, precision, layout and box shapes: a cached entry is
+ * keyed by device name, precision, layout and box shapes ("|own" after the key
+ * where the library's own choice was kept): a cached entry is
  * applied without timing, a new result is appended (a file that cannot be
  * opened is ignored).  FD6_ESTATE before parameters
  * and fields are set.  If a trial fails, the schedule in force before the

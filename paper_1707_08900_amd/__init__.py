@@ -308,7 +308,8 @@ class Box:
         self._check(self.lib.fd6_set_zchunk(self.h, int(zchunk)), "fd6_set_zchunk")
 
     def get_schedule(self):
-        """(kernel shape, z-chunk length) currently in use."""
+        """(kernel shape, z-chunk length) set or tuned; where the library chooses by
+        itself, see fd6_get_schedule in include/fd6.h."""
         t, z = ctypes.c_int32(), ctypes.c_int32()
         self._check(self.lib.fd6_get_schedule(self.h, ctypes.byref(t), ctypes.byref(z)),
                     "fd6_get_schedule")
@@ -316,8 +317,9 @@ class Box:
 
     def tune(self, cache_path: Optional[str] = None):
         """The library's autotuner (fd6_tune; advances the state, so set the
-        fields again afterwards).  Returns (tile, zchunk); tune_log() lists
-        the candidates it timed."""
+        fields again afterwards).  Returns the fastest (tile, zchunk), which is in
+        force unless the library's own choice is at least as fast; tune_log() lists
+        the pairs it timed."""
         path = cache_path.encode() if cache_path else None
         self._check(self.lib.fd6_tune(self.h, path), "fd6_tune")
         return self.get_schedule()

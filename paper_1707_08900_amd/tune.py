@@ -3,7 +3,8 @@
 The search itself is the library's (fd6_tune, C ABI): every z-sweep shape the
 box's layout takes with the automatic z-chunk, then the z-chunk lengths 64,
 128, 256 (those below nz) and nz for the fastest shape, each on reducing
-steps timed with HIP events, keeping the fastest pair.  This module only runs
+steps timed with HIP events, keeping the fastest pair, or the library's own
+choice (a shape for each substep) where no pair is faster.  This module only runs
 it and returns the timings the library logged (fd6_get_tune_log).  Tuning
 runs real steps, so it advances the box's state: call it before init_fields
 of the actual run, or re-initialise afterwards.
@@ -17,7 +18,7 @@ from . import Box
 
 def tune(box: Box, cache_path: Optional[str] = None) -> dict:
     """Tune the box's schedule with the library's tuner; returns {tile,
-    zchunk, ms, timings (shape -> ms per step, automatic chunk),
+    zchunk, ms (of the fastest pair), timings (shape -> ms per step, automatic chunk),
     zchunk_timings (chunk -> ms per step, chosen shape)}."""
     tile, zchunk = box.tune(cache_path)
     log = box.tune_log()

@@ -153,3 +153,57 @@ def test_a_failed_tuning_leaves_the_box_as_it_was(rt, bad, before, graph):
     for _ in range(2):  # (a capture or a launch: nothing recorded by a trial replays)
         assert [k for k in b.step() if k[0] == "substep"] == want
     b.close()
+
+
+def tune(b, path):
+    assert b.lib.fd6_tune(b.h, str(path).encode()) == 0
+    b.log()
+    return [k for k in b.step() if k[0] == "substep"]
+
+
+@pytest.mark.parametrize("layout", ["soa", "aos"])
+def test_tuning_keeps_the_librarys_own_choice_where_nothing_is_faster(rt, tmp_path, layout):
+    """The launchers' choice (a shape for each substep) is a candidate: it stays
+    where no fixed schedule is faster, is found again in the cache by another
+    box, and gives way to a schedule that is set."""
+    path = tmp_path / "cache.txt"
+    b = SimBox(rt, shape=(80, 24, 36), layout=layout)
+    rt.hr_cost(AUTO, 0.9)
+    rt.hr_cost(5, 0.95)
+    rt.hr_chunk(64, 0.99)
+    assert rt.fd6_set_zchunk(b.h, 11) == 0  # a chunk set before is no part of the choice
+    assert tune(b, path) == plain(AUTO)
+    assert b.schedule() == (5, 64)  # reported: the fastest fixed one
+    assert len(path.read_text().splitlines()) == 1
+    n = ctypes.c_int32()
+    assert rt.fd6_get_tune_log(b.h, None, None, None, 0, ctypes.byref(n)) == 0
+    assert n.value == (13 if layout == "soa" else 12) + 2  # every shape, chunks 64 and 80
+    # a chunk asked for holds with the library's shape, a shape with that chunk
+    assert rt.fd6_set_zchunk(b.h, 16) == 0
+    assert [k for k in b.step() if k[0] == "substep"] == plain(AUTO, 16)
+    assert rt.fd6_set_tile(b.h, 4) == 0
+    assert [k for k in b.step() if k[0] == "substep"] == plain(4, 16)
+    assert tune(b, path) == plain(AUTO) and b.schedule() == (5, 64)  # from the cache
+    assert rt.fd6_set_tile(b.h, 5) == 0
+    assert [k for k in b.step() if k[0] == "substep"] == plain(5, 64)
+    b.close()
+    c = SimBox(rt, shape=(80, 24, 36), layout=layout)
+    assert tune(c, path) == plain(AUTO) and c.schedule() == (5, 64)
+    assert rt.fd6_get_tune_log(c.h, None, None, None, 0, ctypes.byref(n)) == 0 and n.value == 0
+    c.close()
+
+
+def test_tuning_takes_a_fixed_schedule_that_is_faster(rt, tmp_path):
+    path = tmp_path / "cache.txt"
+    b = SimBox(rt, shape=(80, 24, 36))
+    assert rt.fd6_set_graph(b.h, 1) == 0
+    rt.hr_cost(AUTO, 0.98)
+    rt.hr_cost(5, 0.95)
+    b.step(2)  # recorded steps of the library's choice
+    assert tune(b, path) == plain(5) and b.schedule() == (5, 0)
+    assert path.read_text().split()[-2:] == ["5", "0"]
+    b.close()
+    c = SimBox(rt, shape=(80, 24, 36))  # an earlier library's line reads the same
+    path.write_text(path.read_text().replace(" 5 0", " 2 64"))
+    assert tune(c, path) == plain(2, 64) and c.schedule() == (2, 64)
+    c.close()
