@@ -367,13 +367,15 @@ int fd6_batch_init_fields(fd6_batch *batch, int32_t box, const double *lnrho, co
 int fd6_batch_set_schedule(fd6_batch *batch, int32_t tile, int32_t zchunk);
 
 /* Autotuner of the ensemble schedule (the shape and chunk choice is the
- * caller's tuning concern, not the method's): times every z-sweep shape the
- * ensemble's layout takes with z-chunk lengths 0 (whole boxes), 32, 48 and 64,
- * FD6_BATCH_BALANCED and FD6_BATCH_PACKED, in two passes over the candidates
- * (each trial 10 warm-up steps, since the step time settles only after a
- * change of schedule, then 8 timed steps, HIP events on the ensemble's
- * stream; a candidate's time is its faster trial), and keeps the fastest.
- * Advances every box by 36 steps per candidate: call it before the fields of
+ * caller's tuning concern, not the method's): times the library's own schedule
+ * and every z-sweep shape the ensemble's layout takes with z-chunk lengths 0
+ * (whole boxes), 32, 48 and 64, FD6_BATCH_BALANCED and FD6_BATCH_PACKED, in two
+ * passes over the candidates (each trial 10 warm-up steps, since the step time
+ * settles only after a change of schedule, then 8 timed steps, HIP events on
+ * the ensemble's stream; a candidate's time is its faster trial), then the own
+ * schedule and the fastest pair once more (where the pair's last trial counts),
+ * and keeps the pair, or the library's own schedule if that is no slower.
+ * Advances every box by 18 steps per trial: call it before the fields of
  * the actual run are set, or set them again afterwards.
  * cache_path (may be NULL) names a text file of "key tile zchunk" lines,
  * keyed by device name, precision, layout and box shapes ("|own" after the key
@@ -384,7 +386,8 @@ int fd6_batch_set_schedule(fd6_batch *batch, int32_t tile, int32_t zchunk);
  * call is restored and the failure returned.  Synchronises. */
 int fd6_batch_tune(fd6_batch *batch, const char *cache_path);
 
-/* The current schedule (set or tuned). */
+/* The schedule that was set or tuned; where fd6_batch_tune kept the library's
+ * own, the fastest pair it timed. */
 int fd6_batch_get_schedule(const fd6_batch *batch, int32_t *tile, int32_t *zchunk);
 
 /* enable != 0 (default): steps replay a captured graph of the 3 substeps;

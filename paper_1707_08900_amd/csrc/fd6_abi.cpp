@@ -100,13 +100,19 @@ struct fd6_box {
     }
 };
 
+// Kernel shape of an ensemble that has no schedule set.
+constexpr int kOwnBatchTile = 8;
+
 // Ensemble of independent boxes advanced together (batched form).
 struct fd6_batch {
     int n = 0;
     int precision = 0;
-    int tile = 8;     // 32 x 8 z-sweep, two planes ahead
+    int tile = kOwnBatchTile;  // 32 x 8 z-sweep, two planes ahead
     int zchunk = 64;  // planes per work item at most (0: whole box)
-    bool schedule_set = false;  // otherwise the chunk length is fitted to the boxes
+    // otherwise the library's own schedule runs: that tile, chunks fitted to the boxes
+    // (where the tuner kept it, tile and zchunk report the fastest of the others)
+    bool schedule_set = false;
+    int run_tile = kOwnBatchTile;  // of the work lists
     bool aos = false;  // every box in the array-of-structures layout
     bool use_graph = true;
     hipStream_t stream = nullptr;   // caller's stream (graph launches, transfers)
@@ -1077,8 +1083,9 @@ int build_items(fd6_batch* b, int tile, int zchunk) {
     HIPCHK(b, hipMemcpyAsync(b->wg_first_dev, first.data(), sizeof(int) * first.size(),
                              hipMemcpyHostToDevice, b->stream));
     HIPCHK(b, hipStreamSynchronize(b->stream));
-    b->tile = tile;
+    b->tile = b->run_tile = tile;
     b->zchunk = zchunk;
+    b->schedule_set = true;
     b->nitems = (int)flat.size();
     b->grid = (int)first.size() - 1;
     b->drop_graphs();
@@ -1092,17 +1099,14 @@ int build_items(fd6_batch* b, int tile, int zchunk) {
 // times over; a few boxes in 64-plane chunks leave most workgroups without work
 // (12 boxes with edges 32-96 on 512 workgroups: 69 plane steps at 64, 37 at 32).
 template <typename T, typename TW>
-int fitted_chunk(fd6_batch* b) {
-    int tx = 0, ty = 0;
-    if (substep55_tile_dims(b->tile, &tx, &ty)) return b->zchunk;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
+int fitted_chunk(const fd6_batch* b) {
+    int tx = 0, ty = 0, dev = 0, cus = 0, best = 64;
+    if (substep55_tile_dims(kOwnBatchTile, &tx, &ty) || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return b->zchunk;
+        return best;
     const long long G = std::max<long long>(
-        1, (long long)cus * (b->aos ? batch55_blocks_per_cu_aos<T, TW>(b->tile)
-                                    : batch55_blocks_per_cu<T, TW>(b->tile)));
-    int best = b->zchunk;
+        1, (long long)cus * (b->aos ? batch55_blocks_per_cu_aos<T, TW>(kOwnBatchTile)
+                                    : batch55_blocks_per_cu<T, TW>(kOwnBatchTile)));
     long long least = -1;
     for (int zc : {64, 56, 48, 40, 32, 28, 24, 20, 16, 12, 8}) {
         std::array<long long, 65> count{};  // chunks by length
@@ -1125,12 +1129,24 @@ int fitted_chunk(fd6_batch* b) {
     return best;
 }
 
+// Work lists of the library's own schedule; what is reported stays.
+template <typename T, typename TW>
+int build_own_items(fd6_batch* b) {
+    const int tile = b->tile, zchunk = b->zchunk;
+    const int rc = build_items<T, TW>(b, kOwnBatchTile, fitted_chunk<T, TW>(b));
+    if (rc != FD6_OK) return rc;
+    b->tile = tile;
+    b->zchunk = zchunk;
+    b->schedule_set = false;
+    return FD6_OK;
+}
+
 template <typename T, typename TW>
 int batch_substeps(fd6_batch* b, hipStream_t st, int parity) {
     auto launch = b->aos ? launch_batch55_aos<T, TW> : launch_batch55<T, TW>;
     for (int s = 0; s < 3; ++s) {
         HIPCHK(b, launch(static_cast<const BatchBox<T, TW>*>(b->boxes_dev), b->items_dev,
-                         b->wg_first_dev, b->grid, parity, s + 1, b->tile, st));
+                         b->wg_first_dev, b->grid, parity, s + 1, b->run_tile, st));
         parity ^= 1;
     }
     return FD6_OK;
@@ -1161,10 +1177,7 @@ int build_graphs(fd6_batch* b) {
 template <typename T, typename TW>
 int batch_steps(fd6_batch* b, int nsteps) {
     if (b->nitems == 0) {
-        const int reported = b->zchunk;
-        int rc = build_items<T, TW>(
-            b, b->tile, b->schedule_set ? b->zchunk : fitted_chunk<T, TW>(b));
-        b->zchunk = reported;
+        int rc = build_own_items<T, TW>(b);
         if (rc) return rc;
     }
     if (b->use_graph && !b->graph_ok) {
@@ -1269,6 +1282,9 @@ constexpr int kBatchTuneWarmup = 10;
 constexpr int kBatchTuneSteps = 8;
 constexpr int kBatchTunePasses = 2;
 
+// The candidate that is the library's own schedule.
+constexpr int kOwn = -1;
+
 // Two timing events, destroyed with the scope.
 struct EventPair {
     hipEvent_t a = nullptr, b = nullptr;
@@ -1324,8 +1340,8 @@ std::string box_tune_key(const fd6_box* b) {
 constexpr int kBoxTuneSteps = 2;
 
 // Cache file: one "key tile zchunk" line per box or ensemble; the last match wins.
-// kOwn after the key: the library's own choice was no slower than that schedule.
-constexpr const char* kOwn = "|own";
+// kOwnMark after the key: the library's own choice was no slower than that schedule.
+constexpr const char* kOwnMark = "|own";
 
 bool read_tune_cache(const char* path, const std::string& key, int* tile, int* zchunk,
                      bool* own) {
@@ -1335,7 +1351,7 @@ bool read_tune_cache(const char* path, const std::string& key, int* tile, int* z
     int t = 0, z = 0;
     bool found = false;
     while (fscanf(f, "%511s %d %d", k, &t, &z) == 3)
-        if (key == k || key + kOwn == k)
+        if (key == k || key + kOwnMark == k)
             *tile = t, *zchunk = z, *own = key != k, found = true;
     fclose(f);
     return found;
@@ -1345,7 +1361,7 @@ void write_tune_cache(const char* path, const std::string& key, int tile, int zc
                       bool own) {
     FILE* f = fopen(path, "a");
     if (!f) return;  // the cache is an optimisation only
-    fprintf(f, "%s%s %d %d\n", key.c_str(), own ? kOwn : "", tile, zchunk);
+    fprintf(f, "%s%s %d %d\n", key.c_str(), own ? kOwnMark : "", tile, zchunk);
     fclose(f);
 }
 
@@ -1869,9 +1885,7 @@ int fd6_batch_set_schedule(fd6_batch* b, int32_t tile, int32_t zchunk) {
         return batch_dispatch(b, [&](auto* t, auto* tw) -> int {
             using T = std::remove_pointer_t<decltype(t)>;
             using TW = std::remove_pointer_t<decltype(tw)>;
-            const int rc = build_items<T, TW>(b, tile, zchunk);
-            if (rc == FD6_OK) b->schedule_set = true;
-            return rc;
+            return build_items<T, TW>(b, tile, zchunk);
         });
     });
 }
@@ -1912,21 +1926,21 @@ int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
         const std::string key = batch_tune_key(b);
         int tile = 0, zchunk = 0;
         bool own = false;
-        if (cache_path && read_tune_cache(cache_path, key, &tile, &zchunk, &own) &&
-            fd6_batch_set_schedule(b, tile, zchunk) == FD6_OK)
-            return FD6_OK;
+        const bool cached = cache_path && read_tune_cache(cache_path, key, &tile, &zchunk, &own) &&
+                            fd6_batch_set_schedule(b, tile, zchunk) == FD6_OK;
+        if (cached && !own) return FD6_OK;
         return batch_dispatch(b, [&](auto* t, auto* tw) -> int {
             using T = std::remove_pointer_t<decltype(t)>;
             using TW = std::remove_pointer_t<decltype(tw)>;
+            if (cached) return build_own_items<T, TW>(b);
             EventPair ev;
             HIPCHK(b, ev.create());
-            float best_ms = -1.0f;
             const int old_tile = b->tile, old_zc = b->zchunk;
-            int best_tile = old_tile, best_zc = old_zc;
+            const bool was_set = b->schedule_set;
             // time of one candidate schedule (warm-up steps, the first of
             // which captures its graphs, then kBatchTuneSteps timed steps)
             auto trial = [&](int cand, int zc, float* ms) -> int {
-                int r = build_items<T, TW>(b, cand, zc);
+                int r = cand == kOwn ? build_own_items<T, TW>(b) : build_items<T, TW>(b, cand, zc);
                 if (r == FD6_OK) r = batch_steps<T, TW>(b, kBatchTuneWarmup);
                 if (r) return r;
                 HIPCHK(b, hipEventRecord(ev.a, b->stream));
@@ -1936,7 +1950,8 @@ int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
                 HIPCHK(b, hipEventElapsedTime(ms, ev.a, ev.b));
                 return FD6_OK;
             };
-            std::vector<std::pair<int, int>> cands;  // (shape, z-chunk)
+            // (shape, z-chunk); the library's own schedule first
+            std::vector<std::pair<int, int>> cands{{kOwn, 0}};
             for (int cand = 1; cand < substep55_tile_count(); ++cand) {
                 int tx, ty;
                 if (substep55_tile_dims(cand, &tx, &ty) != 0) continue;
@@ -1951,21 +1966,24 @@ int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
                     if ((rc = trial(cands[k].first, cands[k].second, &ms)) != FD6_OK) break;
                     if (fastest[k] < 0.0f || ms < fastest[k]) fastest[k] = ms;
                 }
-            for (size_t k = 0; k < cands.size() && rc == FD6_OK; ++k)
-                if (best_ms < 0.0f || fastest[k] < best_ms)
-                    best_ms = fastest[k], best_tile = cands[k].first, best_zc = cands[k].second;
+            // the fastest pair, the luckiest of many, once more beside the own schedule
+            const size_t best = std::min_element(fastest.begin() + 1, fastest.end()) -
+                                fastest.begin();
+            float own_ms = 0.0f, best_ms = 0.0f;
+            if (rc == FD6_OK) rc = trial(kOwn, 0, &own_ms);
+            if (rc == FD6_OK) rc = trial(cands[best].first, cands[best].second, &best_ms);
+            own = std::min(fastest[0], own_ms) <= best_ms;
+            if (rc == FD6_OK && own) rc = build_own_items<T, TW>(b);
             if (rc != FD6_OK) {
                 // a failed trial leaves the schedule that was in force before
-                // (none set: it is fitted again by the next step)
+                // (the library's own: it is fitted again by the next step)
                 (void)build_items<T, TW>(b, old_tile, old_zc);
-                if (!b->schedule_set) b->nitems = 0;
+                b->schedule_set = was_set;
+                if (!was_set) b->nitems = 0;
                 return rc;
             }
-            rc = build_items<T, TW>(b, best_tile, best_zc);
-            if (rc == FD6_OK) b->schedule_set = true;
-            if (rc == FD6_OK && cache_path)
-                write_tune_cache(cache_path, key, best_tile, best_zc, false);
-            return rc;
+            if (cache_path) write_tune_cache(cache_path, key, b->tile, b->zchunk, own);
+            return FD6_OK;
         });
     });
 }

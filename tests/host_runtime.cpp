@@ -13,7 +13,7 @@ double g_clock = 0.0;           // ms
 double g_capture = 0.0;         // ms recorded by the capture in progress
 bool g_capturing = false;
 std::map<int, double> g_cost;   // ms per substep launch, by kernel shape
-std::map<int, double> g_chunk;  // factor, by z-chunk length
+std::map<int, double> g_chunk;  // factor, by z-chunk length (boxes) or grid (ensembles)
 int g_fail_tile = -100;
 constexpr int kShapes = 14;
 
@@ -159,14 +159,14 @@ hipError_t launch_substep19(const Geom&, Fields4<T>, Fields4<T>, Fields4<TW>, co
     return substep("substep", s, tile, zchunk);
 }
 template <typename T, typename TW>
-hipError_t launch_batch55(const BatchBox<T, TW>*, const BatchItem*, const int*, int, int, int s,
-                          int tile, hipStream_t) {
-    return substep("batch", s, tile, 0);
+hipError_t launch_batch55(const BatchBox<T, TW>*, const BatchItem*, const int*, int grid, int,
+                          int s, int tile, hipStream_t) {
+    return substep("batch", s, tile, grid);
 }
 template <typename T, typename TW>
-hipError_t launch_batch55_aos(const BatchBox<T, TW>*, const BatchItem*, const int*, int, int,
-                              int s, int tile, hipStream_t) {
-    return substep("batch", s, tile, 0);
+hipError_t launch_batch55_aos(const BatchBox<T, TW>*, const BatchItem*, const int*, int grid,
+                              int, int s, int tile, hipStream_t) {
+    return substep("batch", s, tile, grid);
 }
 template <typename T, typename TW>
 int batch55_blocks_per_cu(int) {

@@ -207,3 +207,91 @@ def test_tuning_takes_a_fixed_schedule_that_is_faster(rt, tmp_path):
     path.write_text(path.read_text().replace(" 5 0", " 2 64"))
     assert tune(c, path) == plain(2, 64) and c.schedule() == (2, 64)
     c.close()
+
+
+class SimBatch:
+    """Boxes of 64^3 on 256 compute units (512 workgroups of 32 x 8 tiles): one box
+    has 16 columns, the library fits chunks of 8 planes: 128 workgroups."""
+
+    def __init__(self, lib, layout="aos", reset=True):
+        if reset:
+            lib.hr_reset()
+        self.lib = lib
+        d = (fd6.Fd6Desc * 1)(fd6.Fd6Desc(64, 64, 64, fd6.PRECISIONS["fp32"], 0,
+                                          fd6.LAYOUTS[layout]))
+        need = ctypes.c_size_t()
+        assert lib.fd6_batch_workspace_bytes(1, d, ctypes.byref(need)) == 0
+        self.h = ctypes.c_void_p()
+        assert lib.fd6_batch_create(1, d, ctypes.c_void_p(1 << 40), need, None,
+                                    ctypes.byref(self.h)) == 0
+        p = (fd6.Fd6Params * 1)(fd6.Fd6Params(1e-3, 1.0, 0.1, 0.1, 0.1, 0.01))
+        assert lib.fd6_batch_set_params(self.h, p) == 0
+        f = np.zeros(64 ** 3).ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+        assert lib.fd6_batch_init_fields(self.h, 0, f, f, f, f) == 0
+        assert lib.fd6_batch_set_graph(self.h, 0) == 0
+
+    log = SimBox.log
+
+    def step(self):
+        """(shape, workgroups) of one step."""
+        self.lib.hr_log()
+        assert self.lib.fd6_batch_step(self.h, 1) == 0
+        rows = [k for k in self.log() if k[0] == "batch"]
+        assert len(rows) == 3 and len({k[2:] for k in rows}) == 1
+        return rows[0][2:]
+
+    def tune(self, path):
+        assert self.lib.fd6_batch_tune(self.h, str(path).encode()) == 0
+        return self.step()
+
+    def schedule(self):
+        t, z = ctypes.c_int32(), ctypes.c_int32()
+        assert self.lib.fd6_batch_get_schedule(self.h, ctypes.byref(t), ctypes.byref(z)) == 0
+        return t.value, z.value
+
+    def close(self):
+        self.lib.fd6_batch_destroy(self.h)
+
+
+OWN = (8, 128)
+
+
+@pytest.mark.parametrize("layout", ["soa", "aos"])
+def test_tuning_an_ensemble_keeps_the_librarys_own_schedule(rt, tmp_path, layout):
+    path = tmp_path / "cache.txt"
+    b = SimBatch(rt, layout)
+    assert b.step() == OWN
+    rt.hr_chunk(128, 0.5)
+    rt.hr_cost(5, 0.9)
+    rt.hr_chunk(16, 0.8)  # chunks of 64 planes with a wide tile: 8 columns; 32 planes: 16
+    assert b.tune(path) == OWN
+    assert b.schedule() == (5, 32)  # reported: the fastest pair
+    assert len(path.read_text().splitlines()) == 1
+    assert path.read_text().endswith(" 5 32\n")
+    assert rt.fd6_batch_set_schedule(b.h, 5, 32) == 0 and b.step() == (5, 16)
+    assert b.tune(path) == OWN and b.schedule() == (5, 32)  # from the cache
+    b.close()
+    c = SimBatch(rt, layout, reset=False)
+    rt.hr_chunk(128, 5.0)
+    assert c.tune(path) == OWN and c.schedule() == (5, 32)
+    path.unlink()
+    assert c.tune(path) == (5, 16) and c.schedule() == (5, 32)
+    assert path.read_text().endswith(" 5 32\n") and "|own" not in path.read_text()
+    c.close()
+
+
+def test_a_failed_tuning_leaves_the_ensemble_as_it_was(rt, tmp_path):
+    path = tmp_path / "cache.txt"
+    for before in (None, (3, 16), "tuned"):
+        b = SimBatch(rt)
+        rt.hr_chunk(128, 0.5)
+        if before == "tuned":
+            assert b.tune(path) == OWN
+        elif before:
+            assert rt.fd6_batch_set_schedule(b.h, *before) == 0
+        ran, reported = b.step(), b.schedule()
+        rt.hr_fail_tile(13)
+        assert rt.fd6_batch_tune(b.h, None) == -4
+        rt.hr_fail_tile(-100)
+        assert (b.step(), b.schedule()) == (ran, reported)
+        b.close()
