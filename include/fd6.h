@@ -386,8 +386,9 @@ int fd6_batch_set_schedule(fd6_batch *batch, int32_t tile, int32_t zchunk);
  * call is restored and the failure returned.  Synchronises. */
 int fd6_batch_tune(fd6_batch *batch, const char *cache_path);
 
-/* The schedule that was set or tuned; where fd6_batch_tune kept the library's
- * own, the fastest pair it timed. */
+/* The schedule that was set or tuned; before that the library's own, with the
+ * chunk length it fits to the boxes (64 without a device).  Where fd6_batch_tune
+ * kept the library's own, the fastest pair it timed. */
 int fd6_batch_get_schedule(const fd6_batch *batch, int32_t *tile, int32_t *zchunk);
 
 /* enable != 0 (default): steps replay a captured graph of the 3 substeps;

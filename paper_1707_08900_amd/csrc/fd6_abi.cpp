@@ -112,6 +112,7 @@ struct fd6_batch {
     // otherwise the library's own schedule runs: that tile, chunks fitted to the boxes
     // (where the tuner kept it, tile and zchunk report the fastest of the others)
     bool schedule_set = false;
+    bool named = false;            // tile and zchunk hold a schedule that was set or tuned
     int run_tile = kOwnBatchTile;  // of the work lists
     bool aos = false;  // every box in the array-of-structures layout
     bool use_graph = true;
@@ -1085,7 +1086,7 @@ int build_items(fd6_batch* b, int tile, int zchunk) {
     HIPCHK(b, hipStreamSynchronize(b->stream));
     b->tile = b->run_tile = tile;
     b->zchunk = zchunk;
-    b->schedule_set = true;
+    b->schedule_set = b->named = true;
     b->nitems = (int)flat.size();
     b->grid = (int)first.size() - 1;
     b->drop_graphs();
@@ -1133,11 +1134,13 @@ int fitted_chunk(const fd6_batch* b) {
 template <typename T, typename TW>
 int build_own_items(fd6_batch* b) {
     const int tile = b->tile, zchunk = b->zchunk;
+    const bool named = b->named;
     const int rc = build_items<T, TW>(b, kOwnBatchTile, fitted_chunk<T, TW>(b));
     if (rc != FD6_OK) return rc;
     b->tile = tile;
     b->zchunk = zchunk;
     b->schedule_set = false;
+    b->named = named;
     return FD6_OK;
 }
 
@@ -1197,7 +1200,7 @@ int batch_steps(fd6_batch* b, int nsteps) {
 }
 
 template <typename F>
-int batch_dispatch(fd6_batch* b, F&& f) {
+int batch_dispatch(const fd6_batch* b, F&& f) {
     switch (b->precision) {
     case FD6_FP64: return f((double*)nullptr, (double*)nullptr);
     case FD6_FP32: return f((float*)nullptr, (float*)nullptr);
@@ -1914,7 +1917,14 @@ int fd6_batch_get_schedule(const fd6_batch* b, int32_t* tile, int32_t* zchunk) {
     if (!b || !tile || !zchunk) return FD6_EINVAL;
     *tile = b->tile;
     *zchunk = b->zchunk;
-    return FD6_OK;
+    if (b->named) return FD6_OK;
+    // the library's own schedule, which the pair names: setting it changes nothing
+    return batch_dispatch(b, [&](auto* t, auto* tw) -> int {
+        using T = std::remove_pointer_t<decltype(t)>;
+        using TW = std::remove_pointer_t<decltype(tw)>;
+        *zchunk = fitted_chunk<T, TW>(b);
+        return FD6_OK;
+    });
 }
 
 int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
@@ -1936,7 +1946,7 @@ int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
             EventPair ev;
             HIPCHK(b, ev.create());
             const int old_tile = b->tile, old_zc = b->zchunk;
-            const bool was_set = b->schedule_set;
+            const bool was_set = b->schedule_set, was_named = b->named;
             // time of one candidate schedule (warm-up steps, the first of
             // which captures its graphs, then kBatchTuneSteps timed steps)
             auto trial = [&](int cand, int zc, float* ms) -> int {
@@ -1979,6 +1989,7 @@ int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
                 // (the library's own: it is fitted again by the next step)
                 (void)build_items<T, TW>(b, old_tile, old_zc);
                 b->schedule_set = was_set;
+                b->named = was_named;
                 if (!was_set) b->nitems = 0;
                 return rc;
             }

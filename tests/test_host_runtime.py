@@ -295,3 +295,13 @@ def test_a_failed_tuning_leaves_the_ensemble_as_it_was(rt, tmp_path):
         rt.hr_fail_tile(-100)
         assert (b.step(), b.schedule()) == (ran, reported)
         b.close()
+
+
+def test_setting_the_reported_schedule_of_an_ensemble_changes_nothing(rt):
+    b = SimBatch(rt)
+    assert b.schedule() == (8, 8)  # before the first step and after it
+    ran = b.step()
+    assert b.schedule() == (8, 8)
+    assert rt.fd6_batch_set_schedule(b.h, *b.schedule()) == 0
+    assert b.step() == ran == OWN and b.schedule() == (8, 8)
+    b.close()
