@@ -404,7 +404,7 @@ std::array<RKCoef<TW>, 3> make_rk(double dt) {
 }
 
 template <typename T>
-Coef<T> make_coef(const fd6_params& p) {
+Coef<T> make_coef(const fd6_params& p, int variant) {
     const double h[3] = {p.dx, p.dy, p.dz};
     const double w1[3] = {45.0, -9.0, 1.0};
     const double w2[4] = {-490.0, 270.0, -27.0, 2.0};
@@ -453,9 +453,13 @@ Coef<T> make_coef(const fd6_params& p) {
     // The second derivatives of a component must cancel on a constant: what the
     // rounded weights leave over damps or drives every mode alike, step after step
     // (512^3 FP32, 10 steps: the sums of the diagnostics off by 4.5e-7 instead of
-    // 4e-8, the fields by 9.7e-8 instead of 5.8e-8, both relative).  The centre weight therefore matches the rounded weights, and what its own
-    // rounding leaves goes into the last axis' weights, largest first, none by
-    // more than about a unit in its last place.
+    // 4e-8, the fields by 9.7e-8 instead of 5.8e-8, both relative).  The centre weight
+    // therefore matches the rounded weights, and what its own rounding leaves goes into
+    // the weights of one axis, largest first: up to two units in the last place along
+    // the axis of the least spacing, whose weights are the largest, but R^2 times as many
+    // along an axis R times wider (dz = 10 dx 1e-5 of the weight, dz = 100 dx 1e-3).  Even
+    // there that is the smaller error: left on the constant, a remainder r drives a mode
+    // of wave number k by r; in the weights along an axis it does by about r (k h)^2.
     // (FP64 sweeps use exact integers times entry 3 instead.)
     auto centre = [](const T* x, const T* y, T* z) {
         if (sizeof(T) == 8) {
@@ -474,10 +478,27 @@ Coef<T> make_coef(const fd6_params& p) {
         for (int i = 0; i < 3; ++i) z[i] = T((double)z[i] - 0.5 * left((double)k));
         return k;
     };
-    c.kc19 = centre(c.s[0], c.s[1], c.s[2]);
-    c.kc[0] = centre(c.s[1], c.s[2], c.s4[0]);
-    c.kc[1] = centre(c.s[0], c.s[2], c.s4[1]);
-    c.kc[2] = centre(c.s[0], c.s[1], c.s4[2]);
+    // the axes by spacing, the narrowest last (the later one of equals)
+    int by[3] = {0, 1, 2};
+    std::stable_sort(by, by + 3, [&](int i, int j) { return h[i] > h[j]; });
+    c.kc19 = centre(c.s[by[0]], c.s[by[1]], c.s[by[2]]);
+    if (variant == FD6_55P) {
+        // Component i has (4/3) the second derivative along its own axis i.  The widest
+        // axis' component comes first: it may change the plain weights of the narrowest,
+        // which every later one then takes as they are and leaves its remainder in its
+        // own (4/3) weights, the largest for the narrowest axis' component; only with
+        // three different spacings is the middle one's left along a wider axis.
+        bool used[3] = {false, false, false};
+        for (const int i : by) {
+            const int j = i == 0 ? 1 : 0, k = 3 - i - j;
+            T *own = c.s4[i], *other[2] = {c.s[j], c.s[k]}, *z = own;
+            for (int q = 0; q < 2; ++q)
+                if (!used[q == 0 ? j : k] && other[q][3] > z[3]) z = other[q];
+            c.kc[i] = z == own ? centre(c.s[j], c.s[k], own)
+                               : centre(z == c.s[j] ? c.s[k] : c.s[j], own, z);
+            used[j] = used[k] = true;
+        }
+    }
     for (int q = 0; q < 3; ++q)
         for (int k = 0; k < 4; ++k)
             c.m[q][k] = T(wm[k] * p.nu / (3.0 * 720.0 * h[pa[q]] * h[pb[q]]));
@@ -502,7 +523,7 @@ int do_substep(fd6_box* b, int s, const RKCoef<TW>& rk, double* red_out = nullpt
     Fields4<T> in = fields_of<T>(b->state[b->cur]);
     Fields4<T> out = fields_of<T>(b->state[b->cur ^ 1]);
     Fields4<TW> w = fields_of<TW>(b->w);
-    const Coef<T> c = make_coef<T>(b->params);
+    const Coef<T> c = make_coef<T>(b->params, b->desc.variant);
     const bool needs_ghosts = substep55_reads_ghosts(b->run_tile());
     int rc = FD6_OK;
     if (needs_ghosts && !b->ghosts_ok[b->cur]) {
@@ -610,7 +631,7 @@ int fused12_substeps(fd6_box* b) {
         return FD6_EUNSUPPORTED;
     } else {
         const std::array<RKCoef<TW>, 3> rk = make_rk<T, TW>(b->params.dt);
-        const Coef<T> c = make_coef<T>(b->params);
+        const Coef<T> c = make_coef<T>(b->params, b->desc.variant);
         int rc = timed(b, b->ev_kernel, [&]() -> int {
             HIPCHK(b, (launch_fused12<T, TW>(b->geom, fields_of<T>(b->state[b->cur]),
                                              fields_of<T>(b->state[b->cur ^ 1]),
@@ -916,7 +937,7 @@ int upload_boxes(fd6_batch* b) {
         h[i].st[0] = fields_of<T>(b->st[0][i].data());
         h[i].st[1] = fields_of<T>(b->st[1][i].data());
         h[i].w = fields_of<TW>(b->w[i].data());
-        h[i].cf = make_coef<T>(b->params[i]);
+        h[i].cf = make_coef<T>(b->params[i], FD6_55P);
         const std::array<RKCoef<TW>, 3> rk = make_rk<T, TW>(b->params[i].dt);
         for (int s = 0; s < 3; ++s) h[i].rk[s] = rk[s];
     }

@@ -305,3 +305,50 @@ def test_setting_the_reported_schedule_of_an_ensemble_changes_nothing(rt):
     assert rt.fd6_batch_set_schedule(b.h, *b.schedule()) == 0
     assert b.step() == ran == OWN and b.schedule() == (8, 8)
     b.close()
+
+
+def viscous(rt, nu, h, variant):
+    out = (ctypes.c_double * 22)()
+    rt.hr_fp32_viscous(ctypes.c_double(nu), (ctypes.c_double * 3)(*h), fd6.VARIANTS[variant], out)
+    v = np.array(out)
+    return v[:9].reshape(3, 3), v[9:18].reshape(3, 3), v[18:21], v[21]
+
+
+# along one axis, two or three the spacings differ, by little and by much
+SPACINGS = [(0.1, 0.1, 0.1), (0.1, 0.1, 1.0), (0.1, 1.0, 0.1), (1.0, 0.1, 0.1), (0.1, 0.1, 10.0),
+            (10.0, 0.1, 0.1), (0.1, 10.0, 10.0), (10.0, 0.1, 10.0), (10.0, 10.0, 0.1),
+            (0.07, 0.07, 0.0701), (0.0123, 0.0123, 0.26)]
+MIXED = [(0.1, 1.0, 10.0), (10.0, 1.0, 0.1), (1.0, 0.1, 10.0), (0.04, 0.08, 0.06),
+         (0.0123, 0.26, 0.05)]
+
+
+@pytest.mark.parametrize("variant", ["55p", "19p"])
+@pytest.mark.parametrize("h", SPACINGS + MIXED)
+def test_viscous_weights_cancel_on_constants_and_keep_their_last_place(rt, h, variant):
+    """The rounded second derivatives cancel on a constant to one unit in the last
+    place of the smallest weight of the axis that takes up the centre weight's
+    rounding.  No weight pays much for that, in units in the last place of its axis'
+    largest: a centre weight is at most 5.5 times the largest weight it goes with, so
+    half its unit is at most 4 of that weight's, 2 on either side, and rounding takes
+    half a unit: 3 in all.  The plain weights of the narrowest axis may take up two
+    centre weights (5), a wider axis what the narrowest's smallest weight could not
+    hold, a unit in its last place.  Only with three different spacings has the
+    component along the middle one just its own axis left: units of the narrowest."""
+    rng = np.random.default_rng(3)
+    ulp = lambda x: float(np.spacing(np.float32(abs(x))))
+    for nu in 10.0 ** rng.uniform(-5, 1, 40):
+        s, s4, kc, kc19 = viscous(rt, nu, h, variant)
+        exact = np.array([[nu * w / (180.0 * d * d) for w in (270.0, -27.0, 2.0)] for d in h])
+        if variant == "19p":
+            assert abs(kc19 + 2.0 * s.sum()) <= ulp(s[:, 2].max())
+        for i in range(3) if variant == "55p" else ():
+            j, k = [a for a in range(3) if a != i]
+            left = kc[i] + 2.0 * (s[j].sum() + s[k].sum() + s4[i].sum())
+            assert abs(left) <= ulp(max(s[j, 2], s[k, 2], s4[i, 2]))
+        for a in range(3):
+            rest = ulp(s[:, 2].max())
+            assert np.all(np.abs(s[a] - exact[a]) <= 5.0 * ulp(exact[a, 0]) + rest), (a, nu)
+            if variant == "55p":
+                want = exact[a] * 4.0 / 3.0
+                wide = (h[a] / min(h)) ** 2 if h in MIXED and h[a] == sorted(h)[1] else 1.0
+                assert np.all(np.abs(s4[a] - want) <= 3.0 * ulp(want[0]) * wide + rest), (a, nu)
