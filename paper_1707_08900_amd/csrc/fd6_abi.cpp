@@ -478,9 +478,11 @@ Coef<T> make_coef(const fd6_params& p, int variant) {
         for (int i = 0; i < 3; ++i) z[i] = T((double)z[i] - 0.5 * left((double)k));
         return k;
     };
-    // the axes by spacing, the narrowest last (the later one of equals)
+    // the axes by spacing, the narrowest last (the later one of equals); as they come in
+    // FP64, where a unit in the last place is too little to sort for
     int by[3] = {0, 1, 2};
-    std::stable_sort(by, by + 3, [&](int i, int j) { return h[i] > h[j]; });
+    if (sizeof(T) == 4)
+        std::stable_sort(by, by + 3, [&](int i, int j) { return h[i] > h[j]; });
     c.kc19 = centre(c.s[by[0]], c.s[by[1]], c.s[by[2]]);
     if (variant == FD6_55P) {
         // Component i has (4/3) the second derivative along its own axis i.  The widest
@@ -493,7 +495,7 @@ Coef<T> make_coef(const fd6_params& p, int variant) {
             const int j = i == 0 ? 1 : 0, k = 3 - i - j;
             T *own = c.s4[i], *other[2] = {c.s[j], c.s[k]}, *z = own;
             for (int q = 0; q < 2; ++q)
-                if (!used[q == 0 ? j : k] && other[q][3] > z[3]) z = other[q];
+                if (sizeof(T) == 4 && !used[q == 0 ? j : k] && other[q][3] > z[3]) z = other[q];
             c.kc[i] = z == own ? centre(c.s[j], c.s[k], own)
                                : centre(z == c.s[j] ? c.s[k] : c.s[j], own, z);
             used[j] = used[k] = true;
