@@ -423,7 +423,6 @@ Coef<T> make_coef(const fd6_params& p, int variant) {
         }
         for (int k = 0; k < 4; ++k) {
             d2[a][k] = w2[k] / (180.0 * h[a] * h[a]);
-            c.d2[a][k] = T(d2[a][k]);
             c.lp[a][k] = T(p.nu * d2[a][k]);
         }
     }
@@ -431,7 +430,6 @@ Coef<T> make_coef(const fd6_params& p, int variant) {
     for (int q = 0; q < 3; ++q)
         for (int k = 0; k < 3; ++k) {
             const double m = wm[k] / (720.0 * h[pa[q]] * h[pb[q]]);
-            c.mx[q][k] = T(m);
             c.mw[q][k] = T(p.nu * m / 3.0);
         }
     for (int i = 0; i < 3; ++i)

@@ -61,16 +61,14 @@ struct RKCoef {
 };
 
 // Finite-difference weights with the grid spacings folded in (Sec. 2.3).
-//   d1[a][k-1]  = {45, -9, 1}[k-1] / (60 h_a)          first derivative
-//   d2[a][k]    = {-490, 270, -27, 2}[k] / (180 h_a^2)  second derivative
-//   mx[p][k-1]  = {270, -27, 2}[k-1] / (720 h_a h_b)    mixed, p = xy, xz, yz
-// The fused kernel also uses combinations of these; the host precomputes
-// them in FP64 and rounds once to the working precision.
+//   first derivative     {45, -9, 1}[k-1] / (60 h_a)
+//   second derivative    {-490, 270, -27, 2}[k] / (180 h_a^2)
+//   mixed, p = xy, xz, yz  {270, -27, 2}[k-1] / (720 h_a h_b)
+// The kernels use the first as it stands (d1[a][k-1]) and the others in the
+// combinations below; the host forms them in FP64.
 template <typename T>
 struct Coef {
     T d1[3][3];
-    T d2[3][4];
-    T mx[3][3];
     T nu, cs2;
     // Linear viscous part of the momentum equation for component i:
     //   L_i = lap u_i + (1/3) d_i div u
