@@ -87,8 +87,8 @@ def source_sha(paths):
 
 def load_traffic(shape, layout, variant="55p", precision="fp32", n=512):
     """HBM bytes per launch from the committed rocprofv3 counter records (one
-    per kernel shape, z-chunk and layout), if one was taken on the current
-    kernel source with the schedule and layout of this run."""
+    per kernel shape, z-chunk and layout, and one for the library's own choice), if
+    one was taken on the current kernel source with the schedule and layout of this run."""
     try:
         with open(traffic_file(variant, precision, n)) as f:
             recs = json.load(f)
@@ -97,7 +97,9 @@ def load_traffic(shape, layout, variant="55p", precision="fp32", n=512):
     sha = source_sha(kernel_srcs(variant, precision))
     for t in (recs.get("records", []) if isinstance(recs, dict) else []):
         if (t.get("kernel_source_sha") == sha and t.get("layout", "soa") == layout and
-                (t.get("tile"), t.get("zchunk")) == (shape.get("tile"), shape.get("zchunk"))):
+                bool(t.get("own")) == bool(shape.get("own")) and
+                (shape.get("own") or (t.get("tile"), t.get("zchunk")) ==
+                 (shape.get("tile"), shape.get("zchunk")))):
             return t.get("traffic_bytes_per_launch")
     return None
 
@@ -184,6 +186,13 @@ def timed_steps(torch, box, red, steps, warmup, timing=True):
     return wall, ev_ms, tm
 
 
+def shape_of(tuned):
+    """The schedule's pair; with own, the library's own choice ran (a shape for each
+    substep) and the pair is the fastest its tuner timed."""
+    pair = {"tile": tuned["tile"], "zchunk": tuned["zchunk"]}
+    return {**pair, "own": True} if tuned.get("own") else pair
+
+
 def run_form(torch, fd6, w, dev_fields, prec, var, layout, steps, warmup, tile=None, zchunk=0,
              graph=False, error_steps=1, fused12=False):
     """Tune (or fix) the schedule, time `steps` reducing steps after `warmup`,
@@ -196,10 +205,12 @@ def run_form(torch, fd6, w, dev_fields, prec, var, layout, steps, warmup, tile=N
     box.init_fields(dev_fields)
     if tile is None:
         tuned = tuner.tune(box)
+    elif tile < 0:  # the library's own choice, untuned
+        tuned = {"tile": None, "zchunk": None, "own": True}
     else:
         box.set_tile(tile)
         box.set_zchunk(zchunk)
-        tuned = {"tile": tile, "zchunk": zchunk}
+        tuned = {"tile": tile, "zchunk": zchunk, "own": False}
     box.set_fused_substeps(fused12)
     box.init_fields(dev_fields)
     red = torch.zeros(8, dtype=torch.float64, device="cuda")
@@ -211,7 +222,7 @@ def run_form(torch, fd6, w, dev_fields, prec, var, layout, steps, warmup, tile=N
            "hbm_frac_step": v * ALG_BYTES[(var, prec)] / (HBM_PEAK_GBS * 1e9),
            "kernel_avg_launch_us": avg_launch_s * 1e6,
            "kernel_hbm_frac": alg_launch / avg_launch_s / (HBM_PEAK_GBS * 1e9),
-           "kernel_shape": {"tile": tuned["tile"], "zchunk": tuned["zchunk"]},
+           "kernel_shape": shape_of(tuned),
            "host_wall_ms_per_step": wall * 1e3 / steps,
            "diagnostics": red[:5].cpu().tolist()}
     extra = {"tuned": tuned, "kms": kms, "klaunch": klaunch, "gms": gms, "glaunch": glaunch}
@@ -352,8 +363,7 @@ def forced_form(torch, fd6, si, steps):
         res[forced] = e0.elapsed_time(e1) / steps
     box.close()
     return {"updates_per_s": n ** 3 / (res[True] * 1e-3), "ms_per_step": res[True],
-            "unforced_ms_per_step": res[False], "schedule": {"tile": tuned["tile"],
-                                                             "zchunk": tuned["zchunk"]},
+            "unforced_ms_per_step": res[False], "schedule": shape_of(tuned),
             "workload": "256^3, 19-point, FP32, nu = 1.4e-4, force drawn every step from "
                         "1 <= |k| <= 3, f0 = 0.02"}
 
@@ -441,7 +451,8 @@ def main():
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a plain 1 GiB device copy (counter calibration for rocprofv3)")
     ap.add_argument("--tile", type=int, default=None,
-                    help="kernel shape of the headline run (skips the autotuner)")
+                    help="kernel shape of the headline run (skips the autotuner; -1: the "
+                         "library's own choice)")
     ap.add_argument("--zchunk", type=int, default=0,
                     help="z-chunk length with --tile (0: automatic)")
     ap.add_argument("--layout", choices=("aos", "soa"), default="aos",
@@ -655,8 +666,7 @@ def main():
                                f"modes |k|<=16 A=0.1, nu=1e-3, cs=1, dt=0.4 CFL, FP64 reductions "
                                f"every step",
                    "grid": [n, n, n], "precision": prec, "variant": var,
-                   "layout": a.layout, "kernel_shape": {"tile": tuned["tile"],
-                                                        "zchunk": tuned["zchunk"]}},
+                   "layout": a.layout, "kernel_shape": shape_of(tuned)},
         "roofline": roofline,
         "cpu_baseline": cpu,
         "forms": forms,

@@ -11,6 +11,8 @@ of the actual run, or re-initialise afterwards.
 """
 from __future__ import annotations
 
+import os
+import tempfile
 from typing import Optional
 
 from . import Box
@@ -18,14 +20,24 @@ from . import Box
 
 def tune(box: Box, cache_path: Optional[str] = None) -> dict:
     """Tune the box's schedule with the library's tuner; returns {tile,
-    zchunk, ms (of the fastest pair), timings (shape -> ms per step, automatic chunk),
-    zchunk_timings (chunk -> ms per step, chosen shape)}."""
-    tile, zchunk = box.tune(cache_path)
-    log = box.tune_log()
+    zchunk, ms (of the fastest pair), own (the library's own choice runs; None
+    for a choice found in the cache), timings (shape -> ms per step, automatic
+    chunk), zchunk_timings (chunk -> ms per step, chosen shape)}."""
+    with tempfile.TemporaryDirectory() as tmp:
+        path = cache_path or os.path.join(tmp, "tune.txt")
+        tile, zchunk = box.tune(path)
+        log = box.tune_log()
+        own = None
+        if log:  # timed now: the cache's last line
+            try:
+                with open(path) as f:
+                    own = f.read().split()[-3].endswith("|own")
+            except (OSError, IndexError):
+                pass
     shapes = {str(t): ms for t, z, ms in log if z == 0}
     chunks = {str(z): ms for t, z, ms in log if z != 0 and t == tile}
     best = [ms for t, z, ms in log if (t, z) == (tile, zchunk)]
-    return {"tile": tile, "zchunk": zchunk, "ms": best[-1] if best else None,
+    return {"tile": tile, "zchunk": zchunk, "own": own, "ms": best[-1] if best else None,
             "timings": shapes, "zchunk_timings": chunks}
 
 
