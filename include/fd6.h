@@ -74,9 +74,9 @@ typedef enum { FD6_55P = 0, FD6_19P = 1 } fd6_variant;
  * each point with 16-byte accesses.  Results are bit for bit those of the
  * default layout.  The layout is internal: host and device field arrays at
  * this boundary keep the compact per-field layout either way.  Supported for
- * the 55-point method and the z-sweep shapes whose loader goes through
- * registers (fd6_set_tile and fd6_batch_set_schedule return FD6_EUNSUPPORTED
- * for the others); an ensemble takes one layout for all its boxes. */
+ * the 55-point method and every z-sweep shape but 9, an old number of shape 2
+ * (fd6_set_tile and fd6_batch_set_schedule return FD6_EUNSUPPORTED for it and
+ * for the direct kernels); an ensemble takes one layout for all its boxes. */
 #define FD6_LAYOUT_AOS 1
 
 typedef struct {
@@ -178,10 +178,11 @@ int fd6_rhs(fd6_box *box, double *r_lnrho, double *r_ux, double *r_uy, double *r
  * thread per point with every tap read through the caches from the ghost
  * zone, which a separate pass refreshes; 1 .. fd6_tile_count()-1 = z-sweep
  * kernels (periodic images resolved by their loaders, no ghost pass) with
- * different xy tile shapes, load pipelines and cache policies (most shapes
+ * different xy tile shapes, planes fetched ahead and cache policies (most shapes
  * stream the new state and the RK register past the caches; the last ones
  * keep them cached, which pays when the whole state fits in the device's
- * last-level cache).  Results agree up to rounding order (the z-sweep shapes
+ * last-level cache).  FP64 fetches one plane ahead in every shape, so 5, 6, 7, 8,
+ * 10 and 12 are 1, 2, 3, 4, 2 and 11 there; 9 is 2 in every precision.  Results agree up to rounding order (the z-sweep shapes
  * bit for bit with each other); the choice only changes speed (see the
  * autotuner).  FD6_EINVAL for an index out of range; FD6_EUNSUPPORTED for a
  * shape the box's layout does not take (FD6_LAYOUT_AOS).  Until a shape is set or

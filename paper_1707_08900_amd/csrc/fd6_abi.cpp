@@ -938,8 +938,12 @@ int upload_boxes(fd6_batch* b) {
         h[i].st[1] = fields_of<T>(b->st[1][i].data());
         h[i].w = fields_of<TW>(b->w[i].data());
         h[i].cf = make_coef<T>(b->params[i], FD6_55P);
+        if (i > 0 && b->params[i].dt == b->params[i - 1].dt) {
+            std::copy(h[i - 1].rk, h[i - 1].rk + 3, h[i].rk);
+            continue;
+        }
         const std::array<RKCoef<TW>, 3> rk = make_rk<T, TW>(b->params[i].dt);
-        for (int s = 0; s < 3; ++s) h[i].rk[s] = rk[s];
+        std::copy(rk.begin(), rk.end(), h[i].rk);
     }
     HIPCHK(b, hipMemcpyAsync(b->boxes_dev, h.data(), sizeof(BatchBox<T, TW>) * b->n,
                              hipMemcpyHostToDevice, b->stream));

@@ -129,3 +129,25 @@ def test_rounding_error_of_the_formed_register_up_to_the_diffusive_limit(fd6, or
     swept = (0.5 + x * x / 2) ** 2 + (0.32 - 8 / 15 * x) ** 2 + 1
     kept = (1 - 5 / 6 * x + x * x / 2) ** 2 + (1 - 8 / 15 * x) ** 2 + 1
     assert err[1] <= 1.1 * np.sqrt((swept / kept).max()) * err[0]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64", "fp32_acc64"])
+def test_an_ensemble_of_equal_and_unequal_time_steps(fd6, precision):
+    """Each box with its own time step, equal to its neighbour's or not: bit for bit
+    its single-box run."""
+    w = si.noise_box((9, 10, 40), seed=44)
+    dts = [w.dt, w.dt, 0.7 * w.dt, w.dt, 0.7 * w.dt, 0.7 * w.dt]
+    b = fd6.Batch([w.shape] * len(dts), precision)
+    b.set_params([(w.nu, w.cs, w.dx, w.dy, w.dz, dt) for dt in dts])
+    for i in range(len(dts)):
+        b.init_fields(i, w.fields)
+    b.step(2)
+    for i, dt in enumerate(dts):
+        box = fd6.Box(w.shape, precision)
+        box.set_params(w.nu, w.cs, w.dx, w.dy, w.dz, dt)
+        box.init_fields(w.fields)
+        box.step(2)
+        for x, y in zip(b.get_fields(i), box.get_fields()):
+            assert np.array_equal(x, y), (i, dt)
+        box.close()
+    b.close()
