@@ -403,14 +403,14 @@ std::array<RKCoef<TW>, 3> make_rk(double dt) {
     return r;
 }
 
+// direct: also the combinations that only the direct kernels read.
 template <typename T>
-Coef<T> make_coef(const fd6_params& p, int variant) {
+Coef<T> make_coef(const fd6_params& p, int variant, bool direct) {
     const double h[3] = {p.dx, p.dy, p.dz};
     const double w1[3] = {45.0, -9.0, 1.0};
     const double w2[4] = {-490.0, 270.0, -27.0, 2.0};
     const double wm[4] = {270.0, -27.0, 2.0, 1.0};
     Coef<T> c{};
-    double d2[3][4];
     for (int a = 0; a < 3; ++a) {
         for (int k = 0; k < 3; ++k) c.d1[a][k] = T(w1[k] / (60.0 * h[a]));
         if (sizeof(T) == 4) {
@@ -421,21 +421,22 @@ Coef<T> make_coef(const fd6_params& p, int variant) {
             c.d1[a][1] = T(w1[1] / (60.0 * h[a]) - 0.8 * e);
             c.d1[a][2] = T((0.5 / h[a] - (double)c.d1[a][0] - 2.0 * (double)c.d1[a][1]) / 3.0);
         }
-        for (int k = 0; k < 4; ++k) {
-            d2[a][k] = w2[k] / (180.0 * h[a] * h[a]);
-            c.lp[a][k] = T(p.nu * d2[a][k]);
-        }
     }
     const int pa[3] = {0, 0, 1}, pb[3] = {1, 2, 2};  // xy, xz, yz
-    for (int q = 0; q < 3; ++q)
-        for (int k = 0; k < 3; ++k) {
-            const double m = wm[k] / (720.0 * h[pa[q]] * h[pb[q]]);
-            c.mw[q][k] = T(p.nu * m / 3.0);
-        }
-    for (int i = 0; i < 3; ++i)
+    if (direct) {
         for (int a = 0; a < 3; ++a)
-            for (int k = 0; k < 4; ++k)
-                c.lw[i][a][k] = T(p.nu * (a == i ? 4.0 / 3.0 : 1.0) * d2[a][k]);
+            for (int k = 0; k < 4; ++k) {
+                const double d2 = w2[k] / (180.0 * h[a] * h[a]);
+                c.lp[a][k] = T(p.nu * d2);
+                for (int i = 0; i < 3; ++i)
+                    c.lw[i][a][k] = T(p.nu * (a == i ? 4.0 / 3.0 : 1.0) * d2);
+            }
+        for (int q = 0; q < 3; ++q)
+            for (int k = 0; k < 3; ++k) {
+                const double m = wm[k] / (720.0 * h[pa[q]] * h[pb[q]]);
+                c.mw[q][k] = T(p.nu * m / 3.0);
+            }
+    }
     c.nu = T(p.nu);
     c.cs2 = T(p.cs * p.cs);
     c.nu3 = p.nu / 3.0;
@@ -466,21 +467,23 @@ Coef<T> make_coef(const fd6_params& p, int variant) {
             z[3] = T(z[3] - (s + (long double)k / 490.0L));
             return k;
         }
-        auto left = [&](double k) {
-            double s = k;
-            for (const T* w : {x, y, static_cast<const T*>(z)})
-                for (int i = 0; i < 3; ++i) s += 2.0 * (double)w[i];
-            return s;
-        };
-        const T k = T(-left(0.0));
-        for (int i = 0; i < 3; ++i) z[i] = T((double)z[i] - 0.5 * left((double)k));
+        // (sums of few FP32 numbers of near magnitude: exact in FP64)
+        auto sum = [](const T* w) { return 2.0 * ((double)w[0] + (double)w[1] + (double)w[2]); };
+        const double all = sum(x) + sum(y) + sum(z);
+        const T k = T(-all);
+        double left = all + (double)k;
+        for (int i = 0; i < 3; ++i) {
+            const T w = T((double)z[i] - 0.5 * left);
+            left += 2.0 * ((double)w - (double)z[i]);
+            z[i] = w;
+        }
         return k;
     };
     // the axes by spacing, the narrowest last (the later one of equals); as they come in
     // FP64, where a unit in the last place is too little to sort for
     int by[3] = {0, 1, 2};
     if (sizeof(T) == 4)
-        std::stable_sort(by, by + 3, [&](int i, int j) { return h[i] > h[j]; });
+        std::sort(by, by + 3, [&](int i, int j) { return h[i] > h[j] || (h[i] == h[j] && i < j); });
     c.kc19 = centre(c.s[by[0]], c.s[by[1]], c.s[by[2]]);
     if (variant == FD6_55P) {
         // Component i has (4/3) the second derivative along its own axis i.  The widest
@@ -523,8 +526,8 @@ int do_substep(fd6_box* b, int s, const RKCoef<TW>& rk, double* red_out = nullpt
     Fields4<T> in = fields_of<T>(b->state[b->cur]);
     Fields4<T> out = fields_of<T>(b->state[b->cur ^ 1]);
     Fields4<TW> w = fields_of<TW>(b->w);
-    const Coef<T> c = make_coef<T>(b->params, b->desc.variant);
     const bool needs_ghosts = substep55_reads_ghosts(b->run_tile());
+    const Coef<T> c = make_coef<T>(b->params, b->desc.variant, needs_ghosts);
     int rc = FD6_OK;
     if (needs_ghosts && !b->ghosts_ok[b->cur]) {
         rc = timed(b, b->ev_ghost, [&]() -> int {
@@ -631,7 +634,7 @@ int fused12_substeps(fd6_box* b) {
         return FD6_EUNSUPPORTED;
     } else {
         const std::array<RKCoef<TW>, 3> rk = make_rk<T, TW>(b->params.dt);
-        const Coef<T> c = make_coef<T>(b->params, b->desc.variant);
+        const Coef<T> c = make_coef<T>(b->params, b->desc.variant, false);
         int rc = timed(b, b->ev_kernel, [&]() -> int {
             HIPCHK(b, (launch_fused12<T, TW>(b->geom, fields_of<T>(b->state[b->cur]),
                                              fields_of<T>(b->state[b->cur ^ 1]),
@@ -937,7 +940,7 @@ int upload_boxes(fd6_batch* b) {
         h[i].st[0] = fields_of<T>(b->st[0][i].data());
         h[i].st[1] = fields_of<T>(b->st[1][i].data());
         h[i].w = fields_of<TW>(b->w[i].data());
-        h[i].cf = make_coef<T>(b->params[i], FD6_55P);
+        h[i].cf = make_coef<T>(b->params[i], FD6_55P, false);
         if (i > 0 && b->params[i].dt == b->params[i - 1].dt) {
             std::copy(h[i - 1].rk, h[i - 1].rk + 3, h[i].rk);
             continue;

@@ -54,7 +54,7 @@ void hr_fp32_factors(double dt, float* f) {
 // FP32 weights of the viscous term for spacings h: second derivatives s[3][3] and
 // (4/3) s[3][3], the centre weights of the three components, that of the 19-point method
 void hr_fp32_viscous(double nu, const double* h, int variant, double* out) {
-    const Coef<float> c = make_coef<float>(fd6_params{nu, 1.0, h[0], h[1], h[2], 1.0}, variant);
+    const Coef<float> c = make_coef<float>(fd6_params{nu, 1.0, h[0], h[1], h[2], 1.0}, variant, false);
     for (int a = 0; a < 3; ++a)
         for (int k = 0; k < 3; ++k) *out++ = c.s[a][k];
     for (int a = 0; a < 3; ++a)
