@@ -429,7 +429,11 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 //    the wide tile needs over 6/5 of the narrow one's plane steps (FP64 96^3: 16
 //    against 13 per workgroup, 0.093 / 0.086), 3/2 with an FP32 state in one array per
 //    field, whose narrow tiles spend more on their halo (150 x 75 x 101: 19 against 17,
-//    0.116 / 0.139; 19-point 78 x 84 x 150: 20 against 16, 0.138 / 0.167).
+//    0.116 / 0.139; 19-point 78 x 84 x 150: 20 against 16, 0.138 / 0.167).  Plane steps
+//    alone do not decide: over 33 random boxes of 0.3 to 8 million points whose wide
+//    tiles need 1.05-1.55 times the steps, wide / narrow was 0.89-1.19 in FP64 with one
+//    array per field (1.02-1.27 with the array of structures), 0.79-1.22 in FP32 and
+//    0.77-1.25 with the 19-point method in FP32.
 struct AutoShape {
     int tile, zchunk;
 };
@@ -440,7 +444,8 @@ AutoShape auto_shape(const Geom& g, int zchunk, int s, bool red, bool forced) {
     constexpr bool pd1 = sizeof(T) == 8 || P19 || sizeof(TW) == 8;
     // cached stores for FP64 points, whose 32 bytes go out in two halves that the cache
     // merges (ms per step with diagnostics, cached / past the caches: 512^3 7.33 / 7.47,
-    // 256^3 0.920 / 0.942, 400 x 300 x 500 3.50 / 3.58, 192^3 0.446 / 0.438)
+    // 256^3 0.920 / 0.942, 400 x 300 x 500 3.50 / 3.58; 192^3 0.446 / 0.438 loses 2%, and
+    // no line is drawn for it)
     constexpr bool halves = sizeof(T) == 8 && VS == 4;
     // ... and two planes ahead in the diagnostics sweep beside the FP64 register (the
     // step at 256^3 0.705 / 0.720 with one, 500 x 300 x 400 2.74 / 2.82; without

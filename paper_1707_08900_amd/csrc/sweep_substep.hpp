@@ -26,12 +26,11 @@
 //  * The z loop is unrolled by 8 so every ring index is a compile-time
 //    register; the workgroup-to-tile map gives each XCD a near-square block
 //    of neighbouring tiles, so most halo cells are served from its L2.
-//  * What bounds it, at 512^3 in the array-of-structures layout (64 x 8 tiles, two
-//    waves per SIMD): FP32 HBM, 4.7 TB/s of its actual traffic where a 1 GiB copy
-//    runs at 5.1 (S1 1.20-1.27 ms, S2 and S3 1.31-1.38, S3 with diagnostics
-//    1.48-1.55; VALU busy 67-70%, 227 vector instructions per point against 255
-//    before, LDS 51%).  FP64 the same since two waves fit a SIMD: 7.33 ms per step
-//    against 10.2 with one wave (5.0 TB/s).
+//  * What bounds it, at 512^3 in the array-of-structures layout with diagnostics: FP32
+//    3.91 ms per step, HBM in substeps 2 and 3 (4.8-5.0 TB/s of their actual traffic,
+//    where a 1 GiB copy runs at 5.1) and instruction issue in substep 1 (VALU busy 90%
+//    of the cycles; 223-274 vector instructions per point, 254-312 before).  FP64 HBM
+//    since two waves fit a SIMD: 7.35 ms per step against 10.2 with one wave.
 //  * Template switches: VS = 4 reads and writes the array-of-structures
 //    layout (one 16-byte access per cell and field set); NT streams the new
 //    state and the RK3 register past the caches; FRC adds the external
@@ -78,8 +77,14 @@ __device__ __forceinline__ void assemble_rhs(const T u[3], const T g[3], const T
 // with diagnostics and a snapshot: 49.0 -> 45.5 ms; FP64, 4 steps: 50.7 -> 42.8
 // ms).  It also follows the rounding of the
 // stored states: of the errors e1, e2, e3 made when the three substeps round
-// their new states, e1 / 2 + 0.32 e2 + e3 remains after the step, against
-// e1 + e2 + e3 with the register kept apart.
+// their new states, on a mode whose time step times eigenvalue is z,
+//   (1/2 + z^2/2) e1 + (0.32 + (8/15) z) e2 + e3
+// remains after the step, with the register kept apart
+//   (1 + (5/6) z + z^2/2) e1 + (1 + (8/15) z) e2 + e3.
+// That is less on waves and on modes that decay slowly, more on those near the
+// scheme's diffusive limit z = -2.51: the error of one FP32 step of grid-scale noise
+// is 0.69 of the direct kernel's (which keeps it) where viscosity takes z to -0.1,
+// 0.85 at -0.6, 1.06 at -1 and 1.4 from -2 on.
 template <int S, typename T>
 __device__ __forceinline__ T rk_update(T in, T r, T prev, const RKCoef<T>& rk) {
     T q = r;
@@ -98,7 +103,8 @@ __device__ __forceinline__ T rk_update(T in, T r, T prev, const RKCoef<T>& rk) {
 // times e.  Rounding errors are white in space, so z = i y with y^2 = 0.2 (a
 // velocity) to 0.6 (lnrho) in the mean at Courant number 0.4: k = 4 leaves 0.07
 // and 0.05 of e's variance in substep 1 (forming w from the states is k = 3:
-// 0.16 and 0.05), k = 80/51 the least in substep 2.
+// 0.16 and 0.05), k = 80/51 the least in substep 2.  (On decaying modes it leaves less
+// of e down to z = -0.6, more beyond.)
 template <int S, typename T, typename TW>
 __device__ __forceinline__ T rk_update_reg(T in, T r, TW& w, const RKCoef<TW>& rk) {
     TW wn = rk.dt * TW(r);
