@@ -280,6 +280,7 @@ def batch_form(torch, fd6, orc, si, steps, threads, layout="aos", schedule=None,
     library's autotuner (or fixed by `schedule`); every box is then checked
     against the oracle after one step."""
     import numpy as np
+    from paper_1707_08900_amd import tune as tuner
     members = si.ensemble(64)
     ws = [m.workload for m in members]
     pts = sum(int(np.prod(w.shape)) for w in ws)
@@ -293,10 +294,12 @@ def batch_form(torch, fd6, orc, si, steps, threads, layout="aos", schedule=None,
     reinit()
     t0 = time.perf_counter()
     if schedule is None:
-        best = b.tune()  # the library's autotuner (every shape x chunk choice)
+        best = tuner.tune_batch(b)  # the library's autotuner (every shape x chunk choice)
+    elif schedule[0] < 0:  # the library's own schedule, untuned
+        best = dict(zip(("tile", "zchunk"), b.get_schedule()), own=True)
     else:
         b.set_schedule(*schedule)
-        best = b.get_schedule()
+        best = dict(zip(("tile", "zchunk"), b.get_schedule()))
     tune_s = time.perf_counter() - t0
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
@@ -324,7 +327,7 @@ def batch_form(torch, fd6, orc, si, steps, threads, layout="aos", schedule=None,
         by_edge[str(w.shape[0])] = max(by_edge.get(str(w.shape[0]), 0.0), e)
     return {"updates_per_s": pts / (ms * 1e-3), "ms_per_step": ms, "boxes": len(ws),
             "points": pts, "sizes": sorted(set(w.shape[0] for w in ws)),
-            "schedule": {"tile": best[0], "zchunk": best[1]},
+            "schedule": shape_of(best),
             "tuning_s": round(tune_s, 2),
             "hbm_frac_step": pts / (ms * 1e-3) * ALG_BYTES[("55p", "fp32")] / (HBM_PEAK_GBS * 1e9),
             "all_finite": all(r["nonfinite"] == 0 for r in red),

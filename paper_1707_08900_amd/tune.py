@@ -15,7 +15,23 @@ import os
 import tempfile
 from typing import Optional
 
-from . import Box
+from . import Batch, Box
+
+
+def _tune_and_see(handle, cache_path: Optional[str]):
+    """(tile, zchunk) of handle.tune(), and whether the library kept its own choice:
+    the line the cache file ended with tells (None where the file cannot)."""
+    with tempfile.TemporaryDirectory() as tmp:
+        path = cache_path or os.path.join(tmp, "tune.txt")
+        before = os.path.getsize(path) if os.path.exists(path) else 0
+        pair = handle.tune(path)
+        try:
+            with open(path) as f:
+                f.seek(before)
+                own = f.read().split()[-3].endswith("|own")
+        except (OSError, IndexError):
+            own = None
+    return pair, own
 
 
 def tune(box: Box, cache_path: Optional[str] = None) -> dict:
@@ -23,22 +39,19 @@ def tune(box: Box, cache_path: Optional[str] = None) -> dict:
     zchunk, ms (of the fastest pair), own (the library's own choice runs; None
     for a choice found in the cache), timings (shape -> ms per step, automatic
     chunk), zchunk_timings (chunk -> ms per step, chosen shape)}."""
-    with tempfile.TemporaryDirectory() as tmp:
-        path = cache_path or os.path.join(tmp, "tune.txt")
-        tile, zchunk = box.tune(path)
-        log = box.tune_log()
-        own = None
-        if log:  # timed now: the cache's last line
-            try:
-                with open(path) as f:
-                    own = f.read().split()[-3].endswith("|own")
-            except (OSError, IndexError):
-                pass
+    (tile, zchunk), own = _tune_and_see(box, cache_path)
+    log = box.tune_log()
     shapes = {str(t): ms for t, z, ms in log if z == 0}
     chunks = {str(z): ms for t, z, ms in log if z != 0 and t == tile}
     best = [ms for t, z, ms in log if (t, z) == (tile, zchunk)]
     return {"tile": tile, "zchunk": zchunk, "own": own, "ms": best[-1] if best else None,
             "timings": shapes, "zchunk_timings": chunks}
+
+
+def tune_batch(batch: Batch, cache_path: Optional[str] = None) -> dict:
+    """The same for an ensemble: {tile, zchunk, own}."""
+    (tile, zchunk), own = _tune_and_see(batch, cache_path)
+    return {"tile": tile, "zchunk": zchunk, "own": own}
 
 
 def main(argv=None) -> int:
