@@ -27,9 +27,10 @@
 //    register; the workgroup-to-tile map gives each XCD a near-square block
 //    of neighbouring tiles, so most halo cells are served from its L2.
 //  * What bounds it, at 512^3 in the array-of-structures layout with diagnostics: FP32
-//    3.91 ms per step, HBM in substeps 2 and 3 (4.8-5.0 TB/s of their actual traffic,
-//    where a 1 GiB copy runs at 5.1) and instruction issue in substep 1 (VALU busy 90%
-//    of the cycles; 223-274 vector instructions per point, 254-312 before).  FP64 HBM
+//    3.91 ms per step, HBM in substeps 2 and 3 (4.8 and 4.3 TB/s of their actual
+//    traffic in the mean of a trace, 5.1 and 4.6 at best, where a 1 GiB copy runs at
+//    5.1) and instruction issue in substep 1 (VALU busy 90% of the cycles; 223-273
+//    vector instructions per point, 254-312 before).  FP64 HBM
 //    since two waves fit a SIMD: 7.35 ms per step against 10.2 with one wave.
 //  * Template switches: VS = 4 reads and writes the array-of-structures
 //    layout (one 16-byte access per cell and field set); NT streams the new
