@@ -206,13 +206,13 @@ int fd6_get_schedule(const fd6_box *box, int32_t *tile, int32_t *zchunk);
 /* Autotuner of the kernel shape and z-chunk length (a speed choice only):
  * times every z-sweep shape the box's layout takes with the automatic
  * z-chunk, then z-chunk lengths 64, 128, 256 (those below nz) and nz for the
- * fastest shape, before and after them the library's own choice (its faster
- * trial counts), and the fastest pair once more (which counts against that) --
- * one warm-up and 2 timed steps each, every step with its
+ * fastest shape, then the library's own choice and the fastest pair four times
+ * in turn -- one warm-up and 2 timed steps each, every step with its
  * FP64 diagnostics as fd6_rk3_step_reduce computes them, HIP events on the
  * box's stream -- and keeps the fastest pair, or the library's own choice where
- * no pair is faster.  Advances the state by 3 steps per trial: call it before
- * the fields of the actual run are set, or set them again afterwards.
+ * the pair's best of these four is no faster.  Advances the state by 3 steps per
+ * trial: call it before the fields of the actual run are set, or set them again
+ * afterwards.
  * cache_path as for fd6_batch_tune (key: device name, grid, precision, method,
  * layout).  FD6_ESTATE before parameters and fields are set.  If a trial fails,
  * the schedule in force before the call is restored and the failure returned.
@@ -374,8 +374,8 @@ int fd6_batch_set_schedule(fd6_batch *batch, int32_t tile, int32_t zchunk);
  * passes over the candidates (each trial 10 warm-up steps, since the step time
  * settles only after a change of schedule, then 8 timed steps, HIP events on
  * the ensemble's stream; a candidate's time is its faster trial), then the own
- * schedule and the fastest pair once more (where the pair's last trial counts),
- * and keeps the pair, or the library's own schedule if that is no slower.
+ * schedule and the fastest pair twice more in turn, and keeps the pair, or the
+ * library's own schedule where the pair's better of these two is no faster.
  * Advances every box by 18 steps per trial: call it before the fields of
  * the actual run are set, or set them again afterwards.
  * cache_path (may be NULL) names a text file of "key tile zchunk" lines,

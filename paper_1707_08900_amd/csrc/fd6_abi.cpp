@@ -1369,6 +1369,7 @@ std::string box_tune_key(const fd6_box* b) {
 }
 
 constexpr int kBoxTuneSteps = 2;
+constexpr int kBoxTuneRunoff = 4;  // trials of the fastest pair and of the own choice
 
 // Cache file: one "key tile zchunk" line per box or ensemble; the last match wins.
 // kOwnMark after the key: the library's own choice was no slower than that schedule.
@@ -1749,14 +1750,8 @@ int fd6_tune(fd6_box* b, const char* cache_path) {
                 if (rc == FD6_OK) b->tune_log.push_back(fd6_box::TuneTrial{cand, zc, *ms});
                 return rc;
             };
-            // The launchers' own choice is a shape for each substep, which no
-            // (shape, z-chunk) names.  It is timed before the others and after them,
-            // and stays unless the fastest of them is faster than its faster trial in
-            // a second one (the first was the luckiest of many: 3% at 256^3).
-            float own_ms = 0.0f, best_ms = -1.0f, ms = 0.0f;
-            int best_tile = old_tile, best_zc = old_zc;
-            apply(old_tile, old_zc, true);
-            int rc = measure(&own_ms);
+            float best_ms = -1.0f, ms = 0.0f;
+            int best_tile = old_tile, best_zc = old_zc, rc = FD6_OK;
             for (int cand = 1; cand < substep55_tile_count() && rc == FD6_OK; ++cand) {
                 if (b->geom.vs == 4 && !substep55_aos_tile_ok(cand)) continue;
                 if ((rc = trial(cand, 0, &ms)) == FD6_OK && (best_ms < 0.0f || ms < best_ms))
@@ -1772,14 +1767,15 @@ int fd6_tune(fd6_box* b, const char* cache_path) {
                 if ((rc = trial(best_tile, zc, &ms)) == FD6_OK && ms < best_ms)
                     best_ms = ms, best_zc = zc;
             }
-            for (const bool lib : {true, false}) {
-                if (rc != FD6_OK) break;
-                apply(best_tile, best_zc, lib);
-                if ((rc = measure(&ms)) != FD6_OK) break;
-                if (lib)
-                    own_ms = std::min(own_ms, ms);
-                else
-                    best_ms = ms;
+            // The launchers' own choice is a shape for each substep, which no
+            // (shape, z-chunk) names.  It and the fastest pair (the luckiest of many
+            // trials: 3% at 256^3) are timed in turn, and the faster one's best trial
+            // decides.
+            float last[2] = {-1.0f, -1.0f};  // the pair, the own choice
+            for (int k = 0; k < 2 * kBoxTuneRunoff && rc == FD6_OK; ++k) {
+                apply(best_tile, best_zc, k % 2 == 0);
+                float& least = last[k % 2 == 0];
+                if ((rc = measure(&ms)) == FD6_OK && (least < 0.0f || ms < least)) least = ms;
             }
             b->timing = timing;
             if (rc != FD6_OK) {
@@ -1788,7 +1784,7 @@ int fd6_tune(fd6_box* b, const char* cache_path) {
                 b->shape_set = was_set;
                 return rc;
             }
-            own = own_ms <= best_ms;
+            own = last[1] <= last[0];
             apply(best_tile, best_zc, own);
             if (cache_path) write_tune_cache(cache_path, key, best_tile, best_zc, own);
             return FD6_OK;
@@ -2004,13 +2000,17 @@ int fd6_batch_tune(fd6_batch* b, const char* cache_path) {
                     if ((rc = trial(cands[k].first, cands[k].second, &ms)) != FD6_OK) break;
                     if (fastest[k] < 0.0f || ms < fastest[k]) fastest[k] = ms;
                 }
-            // the fastest pair, the luckiest of many, once more beside the own schedule
+            // the own schedule and the fastest pair, the luckiest of many, once more in turn
             const size_t best = std::min_element(fastest.begin() + 1, fastest.end()) -
                                 fastest.begin();
-            float own_ms = 0.0f, best_ms = 0.0f;
-            if (rc == FD6_OK) rc = trial(kOwn, 0, &own_ms);
-            if (rc == FD6_OK) rc = trial(cands[best].first, cands[best].second, &best_ms);
-            own = std::min(fastest[0], own_ms) <= best_ms;
+            float last[2] = {-1.0f, -1.0f};  // the own schedule, the pair
+            for (int k = 0; k < 2 * kBatchTunePasses && rc == FD6_OK; ++k) {
+                const auto& c = cands[k % 2 == 0 ? 0 : best];
+                float ms = 0.0f, &least = last[k % 2];
+                if ((rc = trial(c.first, c.second, &ms)) == FD6_OK && (least < 0.0f || ms < least))
+                    least = ms;
+            }
+            own = last[0] <= last[1];
             if (rc == FD6_OK && own) rc = build_own_items<T, TW>(b);
             if (rc != FD6_OK) {
                 // a failed trial leaves the schedule that was in force before
