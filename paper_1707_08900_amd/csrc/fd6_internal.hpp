@@ -65,11 +65,18 @@ struct RKCoef {
 //   second derivative    {-490, 270, -27, 2}[k] / (180 h_a^2)
 //   mixed, p = xy, xz, yz  {270, -27, 2}[k-1] / (720 h_a h_b)
 // The kernels use the first as it stands (d1[a][k-1]) and the others in the
-// combinations below; the host forms them in FP64.
+// combinations below; the host forms them in FP64.  What a kernel reads lies
+// together, the direct kernels' weights before d1, nu and cs2 and the sweeps'
+// after: scalar loads of whole runs.  With d1, nu and cs2 before the direct
+// kernels' (us per step) 101 x 75 x 150 FP32, one array per field: 76.7, now
+// 75.9; 256^3 FP64, direct: 6880, now 6829.
 template <typename T>
 struct Coef {
-    T d1[3][3];
-    T nu, cs2;
+    // 19-point method: nu-scaled plain second-derivative weights (nu lap u),
+    // and nu / 3 for the gradient of the divergence (in FP64 for the direct
+    // pass 2, whose factor is dt (nu / 3)).
+    T lp[3][4];
+    double nu3;
     // Linear viscous part of the momentum equation for component i:
     //   L_i = lap u_i + (1/3) d_i div u
     //       = sum_a (1 + delta_ia / 3) D2_a u_i + (1/3) sum_{j != i} D_ij u_j
@@ -77,12 +84,8 @@ struct Coef {
     // (nu folded in), mw[p][k-1]: mixed weights / 3 (nu folded in).
     T lw[3][3][4];
     T mw[3][3];
-    // 19-point method: nu-scaled plain second-derivative weights (nu lap u),
-    // and nu / 3 for the gradient of the divergence (in FP64 for the direct
-    // pass 2, whose factor is dt (nu / 3)).
-    T lp[3][4];
-    double nu3;
-    T n3;
+    T d1[3][3];
+    T nu, cs2;
     // Weights of the sweeps (w = 270, -27, 2 for k = 1, 2, 3):
     //   s[a][k-1]  = nu w / (180 h_a^2),  s4 = (4/3) s   second derivatives
     //                (entry 3 of s, s4 and m: the factor of w)
@@ -90,6 +93,7 @@ struct Coef {
     //   m[p][k-1]  = nu w / (3 * 720 h_a h_b), p = xy, xz, yz
     //   tn         = (2/3) nu
     T s[3][4], s4[3][4], kc[3], kc19, m[3][4], tn;
+    T n3;
 };
 
 // External force of the momentum equation, one Fourier mode of eq. (forcing)
